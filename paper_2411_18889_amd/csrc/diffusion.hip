@@ -6,165 +6,175 @@
 // FMAs).
 //
 // The step moves 8 bytes per point at best (one read, one write) against 13
-// flops, so it is bound by HBM. A workgroup of TK x TJ lanes owns a (k, j)
-// tile and marches along i over CI planes: the i-1, i, i+1 values of its
-// column stay in registers, the current plane of the tile plus a one-point
-// halo goes through LDS for the j and k neighbours, so every grid value is
-// read from HBM about once (plus the halos, which the neighbouring tiles read
-// as their own interior and mostly hit in L2). Loads along k are contiguous
-// across a wave (coalesced), and every load index is clamped into the grid.
+// flops, so it is bound by memory: HBM where f and fn exceed the 256 MB
+// last-level cache, that cache (and, for small grids, latency) below.
+//
+// A lane owns 4 consecutive k points of R rows and marches along i over a
+// slab of CI planes; planes i - 1, i, i + 1 of its points stay in registers,
+// plane i + 2 and the two outer rows (j - 1, j + R) of plane i + 1 are already
+// loading while plane i is computed. There is no LDS and no barrier: rows
+// above and below come from L1 / L2, where the neighbouring lanes' own loads
+// put them, and the k neighbours of a lane's 4 points from the adjacent
+// lanes (DPP wave shifts).
+//
+// 16-byte accesses need only 4-byte alignment here, so every nz >= 4 and every
+// array alignment takes them: the last lane of a row is shifted back to end at
+// the row's end (where nz is no multiple of 4 it repeats, with the same
+// values, points its neighbour also writes).
 #include "common.h"
 
 namespace nb {
 
 namespace {
 
-constexpr int TK = 64;  // lanes along k (one wave per row of the tile)
-constexpr int TJ = 8;   // rows along j
-constexpr int CI = 32;  // planes along i per workgroup
-
 struct Coef {
     float cc, ce, cw, cn, cs, ct, cb;
 };
 
-__global__ __launch_bounds__(TK * TJ) void diffusion_kernel(int nx, int ny, int nz, Coef c,
-                                                            const float* __restrict__ f,
-                                                            float* __restrict__ fn) {
-    __shared__ float pl[TJ + 2][TK + 2];
-    const int tx = threadIdx.x, ty = threadIdx.y;
-    const int k = blockIdx.x * TK + tx, j = blockIdx.y * TJ + ty;
-    const int kc = min(k, nz - 1), jc = min(j, ny - 1);
-    const int i0 = blockIdx.z * CI, i1 = min(i0 + CI, nx);
-    const int64_t plane = (int64_t)ny * nz;
-    const int64_t col = (int64_t)jc * nz + kc;
-    const int64_t col_km = (int64_t)jc * nz + max(k - 1, 0);
-    const int64_t col_kp = (int64_t)jc * nz + min(k + 1, nz - 1);
-    const int64_t col_jm = (int64_t)max(j - 1, 0) * nz + kc;
-    const int64_t col_jp = (int64_t)min(j + 1, ny - 1) * nz + kc;
-    const bool store = k < nz && j < ny;
+typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
 
-    float prev = f[(int64_t)max(i0 - 1, 0) * plane + col];
-    float cur = f[(int64_t)i0 * plane + col];
+constexpr int TPB = 256;
+
+struct DiffArgs {
+    int nx, ny, nz;
+    Coef c;
+    const float* f;
+    float* fn;
+    int ci;              // planes per slab
+    int row_lanes;       // lanes per row
+    int lanes;           // lanes per plane
+    int chunks, blocks;  // workgroups per slab, in all
+};
+
+__device__ __forceinline__ v4f load4(const float* p) { return *reinterpret_cast<const v4f*>(p); }
+
+template <int R>
+__global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
+    // workgroups are dealt to the 8 XCDs round-robin: give each XCD one
+    // contiguous run of the grid, so that rows and planes which neighbouring
+    // workgroups share are read into one L2 (256^3: 25.4 -> 22.7 us, 512^3
+    // 218 -> 203 us)
+    const int per = (a.blocks + 7) / 8;
+    const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (b >= a.blocks) return;
+    const int slab = b / a.chunks;
+    const int t = (b - slab * a.chunks) * TPB + threadIdx.x;
+    if (t >= a.lanes) return;
+
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const Coef c = a.c;
+    const int lane = threadIdx.x & 63;
+    const int jb = t / a.row_lanes, l = t - jb * a.row_lanes;
+    const int j0 = jb * R;
+    const int k0 = min(4 * l, nz - 4);
+    const bool kfirst = k0 == 0, klast = k0 + 4 == nz;
+    // lanes whose left / right neighbour point is not at the end of the
+    // adjacent lane's 4: loaded
+    const bool left = !kfirst && (lane == 0 || k0 != 4 * l);
+    const bool right = !klast && (lane == 63 || k0 + 8 > nz);
+    const int64_t plane = (int64_t)ny * nz;
+    const int i0 = slab * a.ci, i1 = min(i0 + a.ci, nx);
+    int off[R + 2];  // rows j0 - 1 .. j0 + R, clamped into the grid
+#pragma unroll
+    for (int r = 0; r < R + 2; ++r) off[r] = min(max(j0 - 1 + r, 0), ny - 1) * nz + k0;
+
+    v4f prev[R], cur[R], next[R];
+    float el[R], er[R];
+    const float* p = a.f + (int64_t)i0 * plane;
+    const float* pm = a.f + (int64_t)max(i0 - 1, 0) * plane;
+    const float* pn = a.f + (int64_t)min(i0 + 1, nx - 1) * plane;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        prev[r] = load4(pm + off[r + 1]);
+        cur[r] = load4(p + off[r + 1]);
+        next[r] = load4(pn + off[r + 1]);
+        el[r] = left ? p[off[r + 1] - 1] : 0.f;
+        er[r] = right ? p[off[r + 1] + 4] : 0.f;
+    }
+    v4f jm = load4(p + off[0]), jp = load4(p + off[R + 1]);
     for (int i = i0; i < i1; ++i) {
-        const int64_t base = (int64_t)i * plane;
-        const float next = f[(int64_t)min(i + 1, nx - 1) * plane + col];
-        __syncthreads();  // the previous plane has been read by every lane
-        pl[ty + 1][tx + 1] = cur;
-        if (tx == 0) pl[ty + 1][0] = f[base + col_km];
-        if (tx == TK - 1) pl[ty + 1][TK + 1] = f[base + col_kp];
-        if (ty == 0) pl[0][tx + 1] = f[base + col_jm];
-        if (ty == TJ - 1) pl[TJ + 1][tx + 1] = f[base + col_jp];
-        __syncthreads();
-        if (store) {
-            float r = c.cc * cur;
-            r = __builtin_fmaf(c.ce, next, r);
-            r = __builtin_fmaf(c.cw, prev, r);
-            r = __builtin_fmaf(c.cn, pl[ty + 2][tx + 1], r);
-            r = __builtin_fmaf(c.cs, pl[ty][tx + 1], r);
-            r = __builtin_fmaf(c.ct, pl[ty + 1][tx + 2], r);
-            r = __builtin_fmaf(c.cb, pl[ty + 1][tx], r);
-            fn[base + col] = r;
+        const float* p1 = a.f + (int64_t)min(i + 1, nx - 1) * plane;
+        const float* p2 = a.f + (int64_t)min(i + 2, nx - 1) * plane;
+        v4f after[R];
+        float eln[R], ern[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) after[r] = load4(p2 + off[r + 1]);
+        const v4f jmn = load4(p1 + off[0]), jpn = load4(p1 + off[R + 1]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            eln[r] = left ? p1[off[r + 1] - 1] : 0.f;
+            ern[r] = right ? p1[off[r + 1] + 4] : 0.f;
         }
-        prev = cur;
-        cur = next;
+        float* o = a.fn + (int64_t)i * plane;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float km = __int_as_float(__builtin_amdgcn_update_dpp(
+                0, __float_as_int(cur[r].w), 0x138, 0xF, 0xF, false));  // lane - 1
+            float kp = __int_as_float(__builtin_amdgcn_update_dpp(
+                0, __float_as_int(cur[r].x), 0x130, 0xF, 0xF, false));  // lane + 1
+            // the ends of the grid have themselves as neighbours
+            km = kfirst ? cur[r].x : (left ? el[r] : km);
+            kp = klast ? cur[r].w : (right ? er[r] : kp);
+            const v4f up = r < R - 1 ? cur[r < R - 1 ? r + 1 : r] : jp;
+            const v4f dn = r > 0 ? cur[r > 0 ? r - 1 : 0] : jm;
+            v4f q;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float kpe = e < 3 ? cur[r][e < 3 ? e + 1 : 3] : kp;
+                const float kme = e > 0 ? cur[r][e > 0 ? e - 1 : 0] : km;
+                float s = c.cc * cur[r][e];
+                s = __builtin_fmaf(c.ce, next[r][e], s);
+                s = __builtin_fmaf(c.cw, prev[r][e], s);
+                s = __builtin_fmaf(c.cn, up[e], s);
+                s = __builtin_fmaf(c.cs, dn[e], s);
+                s = __builtin_fmaf(c.ct, kpe, s);
+                q[e] = __builtin_fmaf(c.cb, kme, s);
+            }
+            // streaming store: fn is not read again by this step
+            if (j0 + r < ny) __builtin_nontemporal_store(q, reinterpret_cast<v4f*>(o + off[r + 1]));
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            prev[r] = cur[r];
+            cur[r] = next[r];
+            next[r] = after[r];
+            el[r] = eln[r];
+            er[r] = ern[r];
+        }
+        jm = jmn;
+        jp = jpn;
     }
 }
 
-// Vector form for nz % 4 == 0: every lane owns 4 consecutive k points
-// (16-byte loads and stores), a wave covers 256 k points of one row, a
-// workgroup TJ4 rows; the plane two steps ahead is already in flight while
-// the current one is computed, so each wave keeps 2 KB of loads outstanding.
-// The j +- 1 rows go through LDS (row layout [.., 256 points at V_OFF..] with
-// V_OFF = 4 so each lane's 4 points are a 16-byte access); the k +- 1
-// neighbours of a lane's 4 points are the adjacent lanes' end points, taken
-// with DPP wave shifts -- reading them from LDS at a 4-float stride cost
-// 4-way bank conflicts (a third of the LDS cycles) and 6-9 % at 512^3.
-constexpr int TK4 = 256;
-constexpr int TJ4 = 16;
-constexpr int CI4 = 64;
-constexpr int V_OFF = 4;
-constexpr int ROW = TK4 + 2 * V_OFF;
-
-__device__ __forceinline__ float4 load_row4(const float* __restrict__ f, int64_t row, int k0, int nz) {
-    // the 4 points k0..k0+3 of a row; lanes past the end of the row take the
-    // row's last point in every slot, which is what the clamped neighbour rule
-    // asks of the point before them
-    if (k0 < nz) return *reinterpret_cast<const float4*>(f + row + k0);
-    const float e = f[row + nz - 1];
-    return make_float4(e, e, e, e);
-}
-
-__global__ __launch_bounds__(64 * TJ4) void diffusion_kernel4(int nx, int ny, int nz, Coef c,
+// Rows shorter than one 16-byte access (nz < 4): a thread per point.
+__global__ __launch_bounds__(TPB) void diffusion_point_kernel(int nx, int ny, int nz, Coef c,
                                                               const float* __restrict__ f,
                                                               float* __restrict__ fn) {
-    __shared__ __align__(16) float pl[TJ4 + 2][ROW];
-    const int lane = threadIdx.x, ty = threadIdx.y;
-    const int k0 = blockIdx.x * TK4 + 4 * lane;
-    const int j = blockIdx.y * TJ4 + ty;
-    const int jc = min(j, ny - 1);
-    const int i0 = blockIdx.z * CI4, i1 = min(i0 + CI4, nx);
+    const int64_t t = blockIdx.x * (int64_t)TPB + threadIdx.x;
+    const int64_t row = t / nz;
+    const int k = (int)(t - row * nz);
+    const int i = (int)(row / ny), j = (int)(row - (int64_t)i * ny);
+    if (i >= nx) return;
     const int64_t plane = (int64_t)ny * nz;
-    const int64_t row = (int64_t)jc * nz;
-    const int64_t row_jm = (int64_t)max(j - 1, 0) * nz;
-    const int64_t row_jp = (int64_t)min(j + 1, ny - 1) * nz;
-    const int kl = blockIdx.x * TK4 - 1, kr = blockIdx.x * TK4 + TK4;  // tile halo points
-    const bool store = k0 < nz && j < ny;
+    float s = c.cc * f[t];
+    s = __builtin_fmaf(c.ce, f[i + 1 < nx ? t + plane : t], s);
+    s = __builtin_fmaf(c.cw, f[i > 0 ? t - plane : t], s);
+    s = __builtin_fmaf(c.cn, f[j + 1 < ny ? t + nz : t], s);
+    s = __builtin_fmaf(c.cs, f[j > 0 ? t - nz : t], s);
+    s = __builtin_fmaf(c.ct, f[k + 1 < nz ? t + 1 : t], s);
+    fn[t] = __builtin_fmaf(c.cb, f[k > 0 ? t - 1 : t], s);
+}
 
-    float4 prev = load_row4(f, (int64_t)max(i0 - 1, 0) * plane + row, k0, nz);
-    float4 cur = load_row4(f, (int64_t)i0 * plane + row, k0, nz);
-    float4 next = load_row4(f, (int64_t)min(i0 + 1, nx - 1) * plane + row, k0, nz);
-    for (int i = i0; i < i1; ++i) {
-        const int64_t base = (int64_t)i * plane;
-        const float4 after = load_row4(f, (int64_t)min(i + 2, nx - 1) * plane + row, k0, nz);
-        __syncthreads();  // the previous plane has been read by every lane
-        *reinterpret_cast<float4*>(&pl[ty + 1][V_OFF + 4 * lane]) = cur;
-        // k neighbours across lanes come from the adjacent lanes (DPP wave
-        // shifts); the tile's two halo points, needed by lanes 0 and 63 only,
-        // are read by the whole wave from one address each
-        const float hl = f[base + row + max(kl, 0)];
-        const float hr = f[base + row + min(kr, nz - 1)];
-        if (ty == 0) {
-            *reinterpret_cast<float4*>(&pl[0][V_OFF + 4 * lane]) = load_row4(f, base + row_jm, k0, nz);
-        }
-        if (ty == TJ4 - 1) {
-            *reinterpret_cast<float4*>(&pl[TJ4 + 1][V_OFF + 4 * lane]) = load_row4(f, base + row_jp, k0, nz);
-        }
-        __syncthreads();
-        if (store) {
-            const float4 jp = *reinterpret_cast<const float4*>(&pl[ty + 2][V_OFF + 4 * lane]);
-            const float4 jm = *reinterpret_cast<const float4*>(&pl[ty][V_OFF + 4 * lane]);
-            const float km0 = __int_as_float(__builtin_amdgcn_update_dpp(
-                __float_as_int(hl), __float_as_int(cur.w), 0x138, 0xF, 0xF, false));  // lane - 1
-            const float kp3 = __int_as_float(__builtin_amdgcn_update_dpp(
-                __float_as_int(hr), __float_as_int(cur.x), 0x130, 0xF, 0xF, false));  // lane + 1
-            // the last point of the grid has itself as its k+1 neighbour
-            const float kp3c = (k0 + 4 < nz) ? kp3 : cur.w;
-            const float km0c = (k0 > 0) ? km0 : cur.x;
-            float4 r;
-#define NB_DIFF_POINT(OUT, C, N, P, JP, JM, KP, KM)                 \
-    {                                                               \
-        float t = c.cc * (C);                                       \
-        t = __builtin_fmaf(c.ce, (N), t);                           \
-        t = __builtin_fmaf(c.cw, (P), t);                           \
-        t = __builtin_fmaf(c.cn, (JP), t);                          \
-        t = __builtin_fmaf(c.cs, (JM), t);                          \
-        t = __builtin_fmaf(c.ct, (KP), t);                          \
-        OUT = __builtin_fmaf(c.cb, (KM), t);                        \
-    }
-            NB_DIFF_POINT(r.x, cur.x, next.x, prev.x, jp.x, jm.x, cur.y, km0c)
-            NB_DIFF_POINT(r.y, cur.y, next.y, prev.y, jp.y, jm.y, cur.z, cur.x)
-            NB_DIFF_POINT(r.z, cur.z, next.z, prev.z, jp.z, jm.z, cur.w, cur.y)
-            NB_DIFF_POINT(r.w, cur.w, next.w, prev.w, jp.w, jm.w, kp3c, cur.z)
-#undef NB_DIFF_POINT
-            // streaming store: fn is not read again by this step
-            typedef float v4f __attribute__((ext_vector_type(4)));
-            const v4f rv = {r.x, r.y, r.z, r.w};
-            __builtin_nontemporal_store(rv, reinterpret_cast<v4f*>(fn + base + row + k0));
-        }
-        prev = cur;
-        cur = next;
-        next = after;
-    }
+template <int R>
+hipError_t launch_rows(DiffArgs a, int64_t ci, hipStream_t stream) {
+    a.ci = (int)ci;
+    a.row_lanes = (a.nz + 3) / 4;
+    a.lanes = a.row_lanes * ((a.ny + R - 1) / R);
+    a.chunks = (a.lanes + TPB - 1) / TPB;
+    a.blocks = a.chunks * (int)((a.nx + ci - 1) / ci);
+    hipLaunchKernelGGL((diffusion_rows_kernel<R>), dim3((unsigned)((a.blocks + 7) / 8 * 8)),
+                       dim3(TPB), 0, stream, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -177,20 +187,35 @@ hipError_t launch_diffusion3d(int64_t nx, int64_t ny, int64_t nz, double dx, dou
     c.cn = c.cs = float(cn);
     c.ct = c.cb = float(ct);
     c.cc = float(1.0 - 2.0 * (ce + cn + ct));
-    const bool vec = nz % 4 == 0 && reinterpret_cast<uintptr_t>(f) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(fn) % 16 == 0 && (ny + TJ4 - 1) / TJ4 <= 65535;
-    if (vec) {
-        const dim3 grid4((unsigned)((nz + TK4 - 1) / TK4), (unsigned)((ny + TJ4 - 1) / TJ4),
-                         (unsigned)((nx + CI4 - 1) / CI4));
-        hipLaunchKernelGGL(diffusion_kernel4, grid4, dim3(64, TJ4), 0, stream, (int)nx, (int)ny, (int)nz,
-                           c, f, fn);
+    if (nz < 4) {
+        hipLaunchKernelGGL(diffusion_point_kernel, dim3((unsigned)((nx * ny * nz + TPB - 1) / TPB)),
+                           dim3(TPB), 0, stream, (int)nx, (int)ny, (int)nz, c, f, fn);
         return hipGetLastError();
     }
-    const dim3 grid((unsigned)((nz + TK - 1) / TK), (unsigned)((ny + TJ - 1) / TJ),
-                    (unsigned)((nx + CI - 1) / CI));
-    hipLaunchKernelGGL(diffusion_kernel, grid, dim3(TK, TJ), 0, stream, (int)nx, (int)ny, (int)nz, c, f,
-                       fn);
-    return hipGetLastError();
+    DiffArgs a{};
+    a.nx = (int)nx;
+    a.ny = (int)ny;
+    a.nz = (int)nz;
+    a.c = c;
+    a.f = f;
+    a.fn = fn;
+    // Rows per lane and planes per slab, measured on MI355X (us per step):
+    //  * beyond the last-level cache (f and fn together over 256 MB) four rows
+    //    per lane, which asks the L2 for 1.5 rows per row computed instead of
+    //    3, in slabs of 8 planes: 384^3 93.5 against 98.8 with one row, 512^3
+    //    201.9 against 245, 700 x 430 x 444 242.9 against 269 (slabs of 64:
+    //    126, 203, 289). The former 256 x 16 LDS tile with a barrier per plane
+    //    and slabs of 64: 148, 204, 318;
+    //  * within it one row per lane (52 VGPRs against 126: more loads in
+    //    flight), 256^3 21.8 against 23.0, 150 x 175 x 201 9.9 against 12.9;
+    //    slabs of 16 planes, thinner where that would leave the chip short of
+    //    lanes: about 3 waves per SIMD are enough (150 x 175 x 201: 8 planes
+    //    9.9, 16 12.6; 128^3: 2 planes 5.0, 4 5.3, 16 13.4; 64^3: one plane
+    //    2.8, 16 10.2; former kernel: 79, 42, 67, 63).
+    const int64_t points = nx * ny * nz;
+    if (2 * points * (int64_t)sizeof(float) > (int64_t(256) << 20)) return launch_rows<4>(a, 8, stream);
+    const int64_t work = (nz + 3) / 4 * ny * nx;  // lanes times planes
+    return launch_rows<1>(a, std::min<int64_t>(16, std::max<int64_t>(1, work / 196608)), stream);
 }
 
 }  // namespace nb

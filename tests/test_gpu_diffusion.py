@@ -61,3 +61,22 @@ def test_mass_conserved_on_gpu():
     fn = nb.api.diffusion3d_step(fd, **PARAMS)
     s0, s1 = float(fd.double().sum()), float(fn.double().sum())
     assert abs(s1 - s0) <= 1e-6 * s0
+
+
+@pytest.mark.parametrize("shape", [(3, 5, 3), (1, 1, 2), (5, 1, 4), (1, 9, 5), (9, 3, 7), (2, 6, 8),
+                                   (20, 33, 255), (18, 5, 257), (17, 31, 259), (300, 3, 9),
+                                   (337, 317, 315), (130, 509, 508), (9, 2051, 2049)])
+def test_ragged_rows(shape):
+    """Row lengths around the 4 points of a lane and the 256 of a wave, rows
+    shorter than a lane, slabs that end inside the grid; from the last-level
+    cache's size on (the last three) four rows per lane, with rows left over.
+    Unaligned input and output: both start one element into their storage."""
+    n = int(np.prod(shape))
+    f = np.random.default_rng(n).uniform(-1, 1, size=shape).astype(np.float32)
+    fd = torch.empty(n + 1, dtype=torch.float32, device=DEV)[1:].view(shape)
+    fd.copy_(torch.tensor(f))
+    guard = torch.full((n + 2,), 7.0, dtype=torch.float32, device=DEV)
+    fn = nb.api.diffusion3d_step(fd, out=guard[1:-1].view(shape), **PARAMS)
+    ref = oracle.diffusion3d(f.astype(np.float64), **PARAMS)
+    assert np.abs(fn.cpu().numpy() - ref).max() <= 1e-6 * np.abs(ref).max()
+    assert float(guard[0]) == 7.0 and float(guard[-1]) == 7.0
