@@ -51,19 +51,22 @@ struct AdjArgs {
     pos_t *vx, *vy, *vz;   // velocity in/out (update_state)
     pos_t *gx, *gy, *gz;   // lam_x in/out
     double* gm;            // lam_m in/out
-    pos_t *rx, *ry, *rz;   // x of the next step's reverse drift, or nullptr
-    pos_t *rlx, *rly, *rlz;  // lam_v written by that drift
-    double dt;
+    WalkArgs<pos_t> next;  // next.x == nullptr: nothing
     double* part;          // [nsplit][NQ][n] or nullptr
 };
 
-template <class Pol>
+// NEXT: also enter the walk's next step (the reduction; the pair kernel would
+// pay for it in registers).
+template <class Pol, bool NEXT>
 __device__ __forceinline__ void finish_adj(const AdjArgs<Pol>& a, int i, const double q[NQ]) {
     using pos_t = typename Pol::pos_t;
     const double G = a.G, c = a.c;
-    a.gx[i] = pos_t(double(a.gx[i]) + c * (G * q[3]));
-    a.gy[i] = pos_t(double(a.gy[i]) + c * (G * q[4]));
-    a.gz[i] = pos_t(double(a.gz[i]) + c * (G * q[5]));
+    const pos_t gx = pos_t(double(a.gx[i]) + c * (G * q[3]));
+    const pos_t gy = pos_t(double(a.gy[i]) + c * (G * q[4]));
+    const pos_t gz = pos_t(double(a.gz[i]) + c * (G * q[5]));
+    a.gx[i] = gx;
+    a.gy[i] = gy;
+    a.gz[i] = gz;
     a.gm[i] = a.gm[i] + c * (-G * q[6]);
     if (a.update_state) {
         const pos_t ax = pos_t(G * q[0]), ay = pos_t(G * q[1]), az = pos_t(G * q[2]);
@@ -75,19 +78,12 @@ __device__ __forceinline__ void finish_adj(const AdjArgs<Pol>& a, int i, const d
         a.vy[i] = fmat(-h, ay, a.vy[i]);
         a.vz[i] = fmat(-h, az, a.vz[i]);
     }
-    if (a.rx) {  // the next step's reverse drift, as the reverse-drift kernel does it
-        const pos_t h = pos_t(a.h), dt = pos_t(a.dt);
-        a.rlx[i] = fmat(dt, a.gx[i], a.rlx[i]);
-        a.rly[i] = fmat(dt, a.gy[i], a.rly[i]);
-        a.rlz[i] = fmat(dt, a.gz[i], a.rlz[i]);
-        const pos_t vx = fmat(-h, a.ax[i], a.vx[i]), vy = fmat(-h, a.ay[i], a.vy[i]),
-                    vz = fmat(-h, a.az[i], a.vz[i]);
-        a.vx[i] = vx;
-        a.vy[i] = vy;
-        a.vz[i] = vz;
-        a.rx[i] = fmat(-dt, vx, a.rx[i]);
-        a.ry[i] = fmat(-dt, vy, a.ry[i]);
-        a.rz[i] = fmat(-dt, vz, a.rz[i]);
+    if (NEXT && a.next.x) {
+        const size_t n = a.n, n3 = 3 * n;
+        const pos_t h = pos_t(a.h);
+        a.next.apply(i, n3, h, gx, a.vx, a.ax);
+        a.next.apply(n + i, n3, h, gy, a.vx, a.ax);
+        a.next.apply(2 * n + i, n3, h, gz, a.vx, a.ax);
     }
 }
 
@@ -204,35 +200,44 @@ __global__ __launch_bounds__(BS) void adjoint_kernel(AdjArgs<Pol> a) {
         if (a.part) {
             double* out = a.part + (size_t)blockIdx.y * NQ * a.n;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) out[(size_t)q * a.n + i] = s[k][q].total();
+            for (int q = F ? 0 : 3; q < NQ; ++q) out[(size_t)q * a.n + i] = s[k][q].total();
         } else {
             double t[NQ];
 #pragma unroll
             for (int q = 0; q < NQ; ++q) t[q] = s[k][q].total();
-            finish_adj<Pol>(a, i, t);
+            finish_adj<Pol, false>(a, i, t);
         }
     }
 }
 
-template <class Pol>
+// The partial sums in the fixed order of the force pass's reduction: wave g of
+// a workgroup takes ranges g, g + 4, ... of 64 sinks, the first wave adds the
+// four sums and finishes. F as the pair kernel's.
+template <class Pol, bool F>
 __global__ __launch_bounds__(256) void adjoint_reduce_kernel(AdjArgs<Pol> a, int nsplit) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= a.n) return;
+    constexpr int Q0 = F ? 0 : 3;
+    __shared__ double other[3][NQ][64];
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;
     double t[NQ] = {0, 0, 0, 0, 0, 0, 0};
-    // four ranges' loads in flight together, the adds in range order
+    if (i < a.n) {
 #pragma unroll 4
-    for (int sp = 0; sp < nsplit; ++sp) {
-        const double* q = a.part + (size_t)sp * NQ * a.n;
+        for (int sp = g; sp < nsplit; sp += 4) {
+            const double* q = a.part + (size_t)sp * NQ * a.n + i;
 #pragma unroll
-        for (int c = 0; c < NQ; ++c) t[c] += q[(size_t)c * a.n + i];
+            for (int c = Q0; c < NQ; ++c) t[c] += q[(size_t)c * a.n];
+        }
     }
-    finish_adj<Pol>(a, i, t);
-}
-
-int split_span(int64_t n, int split, int block) {
-    int64_t per = (n + split - 1) / split;
-    per = (per + block - 1) / block * block;
-    return (int)per;
+    if (g)
+#pragma unroll
+        for (int c = Q0; c < NQ; ++c) other[g - 1][c][lane] = t[c];
+    __syncthreads();
+    if (g || i >= a.n) return;
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+#pragma unroll
+        for (int c = Q0; c < NQ; ++c) t[c] += other[v][c][lane];
+    finish_adj<Pol, true>(a, i, t);
 }
 
 template <class Pol, int BS, int K>
@@ -259,7 +264,7 @@ hipError_t launch_any(const Shape& sh, AdjArgs<Pol> a, int nsplit, hipStream_t s
 
 }  // namespace
 
-Shape choose_adjoint_shape(int prec, int64_t n) {
+Shape choose_adjoint_shape(int prec, int64_t n, bool least) {
     // Measured on MI355X: one sink per lane (the fused pair body is long
     // enough to hide latency on its own; two sinks per lane run 13 % slower),
     // 512-lane workgroups from 2^19 sinks up, 256 from 4096, 64 below; a
@@ -267,7 +272,6 @@ Shape choose_adjoint_shape(int prec, int64_t n) {
     // >= 2 tiles long (4 below 32768 sinks) -- or, below 16384 sinks, as
     // short as one tile up to 32 ranges (2.2-2.8x faster at N = 1024 and
     // 2048, where the pass is otherwise a handful of workgroups).
-    (void)prec;
     Shape s{1, n >= (1 << 19) ? 512 : (n <= 2048 ? 64 : 256), 1};
     const int64_t waves = (n + s.block - 1) / s.block * (s.block / 64);
     const int64_t want = 131072;
@@ -278,6 +282,13 @@ Shape choose_adjoint_shape(int prec, int64_t n) {
     if (split > max_ranges) split = max_ranges;
     if (split > 256) split = 256;
     if (split < 1) split = 1;
+    // ranges as short as one tile until there are 8 waves per SIMD, as the
+    // force pass (and not for the same two policies): entry pass 37.0 instead
+    // of 56.9 us at 2500 particles, 39.1 instead of 59.6 at 5003, 84.9
+    // instead of 96.5 at 10000
+    if (!least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN)
+        split = std::max<int64_t>(split_ranges(n, split, s.block),
+                                  short_tile_ranges(n, s.block, waves));
     s.split = (int)split;
     return s;
 }
@@ -294,9 +305,9 @@ size_t adjoint_partials_bytes(const Shape& s, int64_t n) {
 hipError_t launch_adjoint(int prec, const Shape& sh, int64_t n, const void* x, const void* m,
                           const void* lam_v, double eps, double G, double c, bool update_state,
                           double h, void* acc, void* v, void* lam_x, double* lam_m, void* ws,
-                          hipStream_t stream, void* drift_x, double drift_dt, bool* drifted) {
+                          hipStream_t stream, const WalkNext& next, bool* entered) {
     hipError_t err = hipErrorInvalidValue;
-    if (drifted) *drifted = false;
+    if (entered) *entered = false;
     dispatch_prec(prec, [&](auto tag) {
         using Pol = decltype(tag);
         using pos_t = typename Pol::pos_t;
@@ -322,26 +333,23 @@ hipError_t launch_adjoint(int prec, const Shape& sh, int64_t n, const void* x, c
         a.gx = pg; a.gy = pg + n; a.gz = pg + 2 * n;
         a.gm = lam_m;
         const int span = split_span(n, sh.split, sh.block);
-        const int nsplit = (int)((n + span - 1) / span);
+        const int nsplit = split_ranges(n, sh.split, sh.block);
         a.jspan = span;
         if (nsplit == 1) {  // sinks finish while others still read x and lam_v: no drift
             a.part = nullptr;
             err = launch_any<Pol>(sh, a, 1, stream);
             return;
         }
-        if (drift_x) {
-            pos_t* prx = static_cast<pos_t*>(drift_x);
-            pos_t* prl = static_cast<pos_t*>(const_cast<void*>(lam_v));
-            a.rx = prx; a.ry = prx + n; a.rz = prx + 2 * n;
-            a.rlx = prl; a.rly = prl + n; a.rlz = prl + 2 * n;
-            a.dt = drift_dt;
-            if (drifted) *drifted = true;
-        }
+        a.next = WalkArgs<pos_t>(next, lam_v);
+        if (entered) *entered = next.x != nullptr;
         a.part = static_cast<double*>(ws);
         err = launch_any<Pol>(sh, a, nsplit, stream);
         if (err != hipSuccess) return;
-        hipLaunchKernelGGL((adjoint_reduce_kernel<Pol>), dim3((a.n + 255) / 256), dim3(256), 0,
-                           stream, a, nsplit);
+        const dim3 grid((a.n + 63) / 64);
+        if (update_state)
+            hipLaunchKernelGGL((adjoint_reduce_kernel<Pol, true>), grid, dim3(256), 0, stream, a, nsplit);
+        else
+            hipLaunchKernelGGL((adjoint_reduce_kernel<Pol, false>), grid, dim3(256), 0, stream, a, nsplit);
         err = hipGetLastError();
     });
     return err;

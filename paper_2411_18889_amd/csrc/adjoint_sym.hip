@@ -46,9 +46,7 @@ struct ASymFinishArgs {
     pos_t *vx, *vy, *vz;
     pos_t *gx, *gy, *gz;
     double* gm;
-    pos_t *rx, *ry, *rz;     // x of the next step's reverse drift, or nullptr
-    pos_t *rlx, *rly, *rlz;  // lam_v written by that drift
-    double dt;
+    WalkArgs<pos_t> next;  // next.x == nullptr: nothing
 };
 
 // Slot-ordered FP64 sum of the partials, then the reverse-walk epilogue:
@@ -85,9 +83,12 @@ __global__ __launch_bounds__(256) void adjoint_sym_finish_kernel(ASymFinishArgs<
         for (int c = Q0; c < NQ; ++c) q[c] += double(a.part[b.offset(k, c - Q0, i)]);
     }
     const double G = a.G, c = a.c;
-    a.gx[i] = pos_t(double(a.gx[i]) + c * (G * q[3]));
-    a.gy[i] = pos_t(double(a.gy[i]) + c * (G * q[4]));
-    a.gz[i] = pos_t(double(a.gz[i]) + c * (G * q[5]));
+    const pos_t gx = pos_t(double(a.gx[i]) + c * (G * q[3]));
+    const pos_t gy = pos_t(double(a.gy[i]) + c * (G * q[4]));
+    const pos_t gz = pos_t(double(a.gz[i]) + c * (G * q[5]));
+    a.gx[i] = gx;
+    a.gy[i] = gy;
+    a.gz[i] = gz;
     a.gm[i] = a.gm[i] + c * (-G * q[6]);
     if (F) {
         const pos_t ax = pos_t(G * q[0]), ay = pos_t(G * q[1]), az = pos_t(G * q[2]);
@@ -99,19 +100,12 @@ __global__ __launch_bounds__(256) void adjoint_sym_finish_kernel(ASymFinishArgs<
         a.vy[i] = fmat(-h, ay, a.vy[i]);
         a.vz[i] = fmat(-h, az, a.vz[i]);
     }
-    if (a.rx) {  // the next step's reverse drift, as the reverse-drift kernel does it
-        const pos_t h = pos_t(a.h), dt = pos_t(a.dt);
-        a.rlx[i] = fmat(dt, a.gx[i], a.rlx[i]);
-        a.rly[i] = fmat(dt, a.gy[i], a.rly[i]);
-        a.rlz[i] = fmat(dt, a.gz[i], a.rlz[i]);
-        const pos_t vx = fmat(-h, a.ax[i], a.vx[i]), vy = fmat(-h, a.ay[i], a.vy[i]),
-                    vz = fmat(-h, a.az[i], a.vz[i]);
-        a.vx[i] = vx;
-        a.vy[i] = vy;
-        a.vz[i] = vz;
-        a.rx[i] = fmat(-dt, vx, a.rx[i]);
-        a.ry[i] = fmat(-dt, vy, a.ry[i]);
-        a.rz[i] = fmat(-dt, vz, a.rz[i]);
+    if (a.next.x) {
+        const size_t n = a.n, n3 = 3 * n;
+        const pos_t h = pos_t(a.h);
+        a.next.apply(i, n3, h, gx, a.vx, a.ax);
+        a.next.apply(n + i, n3, h, gy, a.vx, a.ax);
+        a.next.apply(2 * n + i, n3, h, gz, a.vx, a.ax);
     }
 }
 
@@ -212,7 +206,7 @@ hipError_t launch_adjoint_sym_pol(int prec, const SymShape& sh, int64_t n, const
                                   const void* m, const void* lam_v, double eps, double G,
                                   double c, bool update_state, double h, void* acc, void* v,
                                   void* lam_x, double* lam_m, void* ws, size_t ws_bytes,
-                                  hipStream_t stream, void* drift_x, double drift_dt) {
+                                  hipStream_t stream, const WalkNext& next) {
     using pos_t = typename Pol::pos_t;
     using mass_t = typename Pol::mass_t;
     using calc_t = typename Pol::calc_t;
@@ -252,13 +246,8 @@ hipError_t launch_adjoint_sym_pol(int prec, const SymShape& sh, int64_t n, const
     f.vx = pv; f.vy = pv + n; f.vz = pv + 2 * n;
     f.gx = pg; f.gy = pg + n; f.gz = pg + 2 * n;
     f.gm = lam_m;
-    if (drift_x) {  // each fold finishes particles after every read of their x and lam_v
-        pos_t* prx = static_cast<pos_t*>(drift_x);
-        pos_t* prl = static_cast<pos_t*>(const_cast<void*>(lam_v));
-        f.rx = prx; f.ry = prx + n; f.rz = prx + 2 * n;
-        f.rlx = prl; f.rly = prl + n; f.rlz = prl + 2 * n;
-        f.dt = drift_dt;
-    }
+    // each fold finishes particles after every read of their x and lam_v
+    f.next = WalkArgs<pos_t>(next, lam_v);
     a.part = parts;
     f.part = parts;
     f.nb = L.nb;
@@ -286,30 +275,28 @@ hipError_t launch_adjoint_sym(int prec, const SymShape& sh, int64_t n, const voi
                               const void* m, const void* lam_v, double eps, double G, double c,
                               bool update_state, double h, void* acc, void* v, void* lam_x,
                               double* lam_m, void* ws, size_t ws_bytes, hipStream_t stream,
-                              void* drift_x, double drift_dt, bool* drifted) {
-    if (drifted) *drifted = false;
+                              const WalkNext& next, bool* entered) {
+    if (entered) *entered = false;
     if ((int64_t)sh.waves * sh.ipl == 0) return hipErrorInvalidValue;
     hipError_t e = hipErrorInvalidValue;
     switch (prec) {
     case NB_MIX_TILEC:
         e = launch_adjoint_sym_pol<PolMixTileC>(prec, sh, n, x, m, lam_v, eps, G, c, update_state,
                                                 h, acc, v, lam_x, lam_m, ws, ws_bytes, stream,
-                                                drift_x, drift_dt);
+                                                next);
         break;
     case NB_F32:
         e = launch_adjoint_sym_pol<PolF32>(prec, sh, n, x, m, lam_v, eps, G, c, update_state, h,
-                                           acc, v, lam_x, lam_m, ws, ws_bytes, stream, drift_x,
-                                           drift_dt);
+                                           acc, v, lam_x, lam_m, ws, ws_bytes, stream, next);
         break;
     case NB_F64:
         e = launch_adjoint_sym_pol<PolF64>(prec, sh, n, x, m, lam_v, eps, G, c, update_state, h,
-                                           acc, v, lam_x, lam_m, ws, ws_bytes, stream, drift_x,
-                                           drift_dt);
+                                           acc, v, lam_x, lam_m, ws, ws_bytes, stream, next);
         break;
     default:
         break;
     }
-    if (e == hipSuccess && drifted) *drifted = drift_x != nullptr;
+    if (e == hipSuccess && entered) *entered = next.x != nullptr;
     return e;
 }
 

@@ -240,9 +240,29 @@ struct Shape {
     int split;  // j-ranges per sink
 };
 
-// Library choice of shape for ni sinks, nj sources.
-Shape choose_force_shape(int prec, int64_t ni, int64_t nj);
-Shape choose_adjoint_shape(int prec, int64_t n);
+// A split of nj sources gives ranges of whole tiles (`block` sources): their
+// length, and how many there are.
+inline int split_span(int64_t nj, int split, int block) {
+    const int64_t per = (nj + split - 1) / split;
+    return (int)((per + block - 1) / block * block);
+}
+inline int split_ranges(int64_t nj, int64_t split, int block) {
+    const int64_t span = split_span(nj, (int)split, block);
+    return (int)((nj + span - 1) / span);
+}
+// The most ranges of equal numbers of tiles, at most 256, with which `waves`
+// wavefronts a range make at most 8192 (8 per SIMD).
+inline int64_t short_tile_ranges(int64_t nj, int block, int64_t waves) {
+    const int64_t tiles = (nj + block - 1) / block;
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(256, 8192 / waves));
+    const int64_t per = (tiles + most - 1) / most;
+    return (tiles + per - 1) / per;
+}
+
+// Library choice of shape for ni sinks, nj sources. least: the shape with the
+// smaller workspace that a call takes when the first one's does not fit.
+Shape choose_force_shape(int prec, int64_t ni, int64_t nj, bool least = false);
+Shape choose_adjoint_shape(int prec, int64_t n, bool least = false);
 // Shapes the one-sided force / adjoint kernels are built for.
 bool shape_supported(const Shape& s);
 bool adjoint_shape_supported(const Shape& s);
@@ -253,18 +273,81 @@ size_t force_partials_bytes(const Shape& s, int64_t ni);
 size_t force_partials_bound(int64_t n);
 size_t adjoint_partials_bytes(const Shape& s, int64_t n);
 
-// Force: acc (and pot) of ni sinks. self_set: xi and xj are the same set.
-// kick_v (optional, 3 ni pos elements): also apply v <- v + kick_h * acc in
-// the epilogue, with acc as stored (the leapfrog's closing half-kick).
-// drift_x (optional, with kick_v, self set): then also the next step's
-// kick and drift, v <- v + kick_h * acc; x <- x + drift_dt * v, when the
-// pass has a finishing kernel that runs after every read of x; *drifted
-// (if given) tells whether it did.
+// What a leapfrog's force pass does to each particle once its acceleration is
+// stored, in this order (each part optional):
+//   v         closing half-kick v <- v + h acc, with acc as stored;
+//   store     a checkpoint slot receives (x, v, acc), 3 x 3n elements;
+//   drift_x   (with v) the next step's kick and drift, v <- v + h acc; x <- x +
+//             dt v, in a kernel that runs after every read of x (*drifted).
+struct StepTail {
+    void* v = nullptr;
+    double h = 0.0;
+    void* store = nullptr;
+    const void* store_v = nullptr;  // v of the slot where v is not kicked
+    void* drift_x = nullptr;
+    double dt = 0.0;
+};
+
+// The tail as the kernels take it, in the state type.
+template <typename T>
+struct TailArgs {
+    T* v = nullptr;
+    T* store = nullptr;
+    const T* store_v = nullptr;
+    T* x = nullptr;
+    T h = T(0), dt = T(0);
+    TailArgs() = default;
+    explicit TailArgs(const StepTail& t)
+        : v(static_cast<T*>(t.v)), store(static_cast<T*>(t.store)),
+          store_v(static_cast<const T*>(t.store_v)), x(static_cast<T*>(t.v ? t.drift_x : nullptr)),
+          h(T(t.h)), dt(T(t.dt)) {}
+    // particle i of n, at pos (rows of n), with the acceleration as stored
+    __device__ __forceinline__ void apply(int n, int i, const T* pos, T ax, T ay, T az) const {
+        if (!v && !store) return;
+        const size_t iy = (size_t)n + i, iz = 2 * (size_t)n + i;
+        T vx = T(0), vy = T(0), vz = T(0);
+        if (v) {  // the same FMAs as the kick-drift kernel's
+            vx = fmat(h, ax, v[i]);
+            vy = fmat(h, ay, v[iy]);
+            vz = fmat(h, az, v[iz]);
+        } else {
+            vx = store_v[i];
+            vy = store_v[iy];
+            vz = store_v[iz];
+        }
+        if (store) {
+            const size_t n3 = 3 * (size_t)n;
+            store[i] = pos[i];
+            store[iy] = pos[iy];
+            store[iz] = pos[iz];
+            store[n3 + i] = vx;
+            store[n3 + iy] = vy;
+            store[n3 + iz] = vz;
+            store[2 * n3 + i] = ax;
+            store[2 * n3 + iy] = ay;
+            store[2 * n3 + iz] = az;
+        }
+        if (!v) return;
+        if (x) {
+            vx = fmat(h, ax, vx);
+            vy = fmat(h, ay, vy);
+            vz = fmat(h, az, vz);
+            x[i] = fmat(dt, vx, x[i]);
+            x[iy] = fmat(dt, vy, x[iy]);
+            x[iz] = fmat(dt, vz, x[iz]);
+        }
+        v[i] = vx;
+        v[iy] = vy;
+        v[iz] = vz;
+    }
+};
+
+// Force: acc (and pot) of ni sinks. self_set: xi and xj are the same set (the
+// tail needs it).
 hipError_t launch_force(int prec, const Shape& shape, int64_t ni, const void* xi,
                         int64_t nj, const void* xj, const void* mj, double eps,
                         double G, bool self_set, void* acc, void* pot, void* ws,
-                        hipStream_t stream, void* kick_v = nullptr, double kick_h = 0.0,
-                        void* drift_x = nullptr, double drift_dt = 0.0,
+                        hipStream_t stream, const StepTail& tail = StepTail{},
                         bool* drifted = nullptr);
 
 // Symmetric (third-law) force pass of one set on itself, NB_MIX_TILEC, NB_F32
@@ -424,33 +507,69 @@ SymShape choose_sym_shape(int prec, int64_t n, bool pot = false);
 bool sym_shape_supported(int prec, const SymShape& s);
 // The band layout of the symmetric force pass.
 SymLayout sym_layout(int prec, const SymShape& s, int64_t n, bool pot = false);
-// acc = a(x) (and with kick_v, v <- v + kick_h * acc; with pot, the
-// potential with the j = i term removed); ws holds ws_bytes >=
-// sym_min_bytes(sym_layout(prec, sh, n, pot != nullptr)) bytes, used in
-// bands as above (one band when it holds every partial).
-// drift_x / drift_dt / drifted: as launch_force (each finishing kernel runs
-// after every read of its particles' positions, so the drift is always taken
-// when asked for).
+// acc = a(x) (with pot, the potential with the j = i term removed); ws holds
+// ws_bytes >= sym_min_bytes(sym_layout(prec, sh, n, pot != nullptr)) bytes,
+// used in bands as above (one band when it holds every partial).
+// tail, drifted: as launch_force (each finishing kernel runs after every read
+// of its particles' positions, so the drift is always taken when asked for).
 hipError_t launch_force_sym(int prec, const SymShape& sh, int64_t n, const void* x,
                             const void* m, double eps, double G, void* acc, void* ws,
-                            size_t ws_bytes, hipStream_t stream, void* kick_v = nullptr,
-                            double kick_h = 0.0, void* pot = nullptr, void* drift_x = nullptr,
-                            double drift_dt = 0.0, bool* drifted = nullptr);
+                            size_t ws_bytes, hipStream_t stream, void* pot = nullptr,
+                            const StepTail& tail = StepTail{}, bool* drifted = nullptr);
+
+// What an adjoint pass does to each particle after its own update, to enter
+// the walk's next step, where the pass has a finishing kernel that runs after
+// every read of x and lam_v (*entered tells whether it did): lam_v += dt lam_x,
+// and then the reverse drift, v -= h acc; x -= dt v, or, with `slot` (x, v, acc
+// of a checkpoint), the state it reloads: x, and v and acc where `whole` (a
+// next step that is reloaded again reads neither).
+struct WalkNext {
+    void* x = nullptr;  // nullptr: nothing
+    double dt = 0.0;
+    const void* slot = nullptr;
+    bool whole = true;
+};
+
+// The same as the kernels take it, in the state type.
+template <typename T>
+struct WalkArgs {
+    T* x = nullptr;
+    T* lv = nullptr;
+    const T* slot = nullptr;
+    T dt = T(0);
+    int whole = 1;
+    WalkArgs() = default;
+    WalkArgs(const WalkNext& w, const void* lam_v)
+        : x(static_cast<T*>(w.x)), lv(static_cast<T*>(const_cast<void*>(lam_v))),
+          slot(static_cast<const T*>(w.slot)), dt(T(w.dt)), whole(w.whole) {}
+    // component k of 3n; lx, a: lam_x and acc as stored (a is not read where a
+    // slot is given); vel, acc: the state's arrays. The same FMAs as the
+    // reverse-drift and reload kernels'.
+    __device__ __forceinline__ void apply(size_t k, size_t n3, T h, T lx, T* vel, T* acc) const {
+        lv[k] = fmat(dt, lx, lv[k]);
+        if (slot) {
+            x[k] = slot[k];
+            if (whole) {
+                vel[k] = slot[n3 + k];
+                acc[k] = slot[2 * n3 + k];
+            }
+            return;
+        }
+        const T vh = fmat(-h, acc[k], vel[k]);
+        vel[k] = vh;
+        x[k] = fmat(-dt, vh, x[k]);
+    }
+};
 
 // Fused adjoint pair pass at x with adjoint lam_v: computes a(x), J^T lam_v,
 // G^T lam_v and applies the epilogue
 //   lam_x += c J^T lam_v;  lam_m += c G^T lam_v;
 //   if update_state: acc = a(x); v = v - h acc.
-// drift_x (optional): then also the next step's reverse drift,
-//   lam_v += drift_dt lam_x; v -= h acc; x -= drift_dt v,
-// where the pass has a finishing kernel that runs after every read of x and
-// lam_v (*drifted, if given, tells whether it did).
 hipError_t launch_adjoint(int prec, const Shape& shape, int64_t n, const void* x,
                           const void* m, const void* lam_v, double eps, double G,
                           double c, bool update_state, double h, void* acc, void* v,
                           void* lam_x, double* lam_m, void* ws, hipStream_t stream,
-                          void* drift_x = nullptr, double drift_dt = 0.0,
-                          bool* drifted = nullptr);
+                          const WalkNext& next = WalkNext{}, bool* entered = nullptr);
 
 // Symmetric form of the fused adjoint pass (NB_MIX_TILEC, NB_F32, NB_F64),
 // same contract as launch_adjoint; ws holds ws_bytes >= sym_min_bytes(
@@ -464,19 +583,22 @@ hipError_t launch_adjoint_sym(int prec, const SymShape& sh, int64_t n, const voi
                               const void* lam_v, double eps, double G, double c,
                               bool update_state, double h, void* acc, void* v, void* lam_x,
                               double* lam_m, void* ws, size_t ws_bytes, hipStream_t stream,
-                              void* drift_x = nullptr, double drift_dt = 0.0,
-                              bool* drifted = nullptr);
+                              const WalkNext& next = WalkNext{}, bool* entered = nullptr);
 
 // O(N) leapfrog kernels over the 3n components of a pos array.
 hipError_t launch_kick_drift(int prec, int64_t n, void* x, void* v, const void* acc,
                              double h, double dt, hipStream_t stream);
+// A checkpoint slot (3 x 3n elements) receives (x, v, acc).
+hipError_t launch_store(int prec, int64_t n, const void* x, const void* v, const void* acc,
+                        void* slot, hipStream_t stream);
 // Reverse drift: lam_v += dt lam_x; v <- v - h acc; x <- x - dt v.
 hipError_t launch_reverse_drift(int prec, int64_t n, void* x, void* v, const void* acc,
                                 const void* lam_x, void* lam_v, double h, double dt,
                                 hipStream_t stream);
-// lam_v += dt lam_x only (before a checkpoint reload).
-hipError_t launch_axpy_pos(int prec, int64_t n3, void* y, const void* xv, double a,
-                           hipStream_t stream);
+// lam_v += dt lam_x, then the state of a checkpoint slot: x, and v and acc
+// where `whole`.
+hipError_t launch_reload(int prec, int64_t n, void* x, void* v, void* acc, const void* lam_x,
+                         void* lam_v, double dt, const void* slot, bool whole, hipStream_t stream);
 
 // One step of the 3-D diffusion stencil (FP32 grid, k fastest).
 hipError_t launch_diffusion3d(int64_t nx, int64_t ny, int64_t nz, double dx, double dy, double dz,
@@ -488,7 +610,8 @@ hipError_t launch_diffusion3d(int64_t nx, int64_t ny, int64_t nz, double dx, dou
 // The pass nbody_accel runs for a call, once its arguments are checked.
 struct AccelPlan {
     SymShape sym;   // the symmetric pass (sym.waves != 0), or
-    Shape sh;       // the one-sided kernel in this shape
+    Shape sh;       // the one-sided kernel in this shape, or, where the scratch
+    Shape least;    // is too small for it, in this one
     bool self_set;
     size_t need;    // scratch bytes the pass needs at least
     size_t full;    // scratch bytes it uses at most (every partial at once)

@@ -45,14 +45,14 @@ struct ForceArgs {
     double G;
     int self_pot;         // remove the j = i term m_i / eps from the potential
     pos_t *ax, *ay, *az, *pot;  // final outputs (part == nullptr)
-    pos_t *vx, *vy, *vz;  // velocities to kick, or nullptr
-    double h;             // kick: v <- v + h a, with a as stored
-    pos_t *dx, *dy, *dz;  // with vx: positions of the next step's drift, or nullptr
-    double dt;            // drift: v <- v + h a; x <- x + dt v (after the kick)
+    TailArgs<pos_t> tail;
     double* part;         // [nsplit][NQ][ni] FP64 partial sums, or nullptr
 };
 
-template <class Pol, bool POT>
+// TAIL: also the leapfrog's tail. The pair kernel leaves it out (it costs
+// registers, and with them waves, there: 46 -> 91 VGPRs and 20 % with Kahan
+// sums at 262144).
+template <class Pol, bool POT, bool TAIL>
 __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, double sx, double sy,
                                             double sz, double sp) {
     using pos_t = typename Pol::pos_t;
@@ -61,22 +61,7 @@ __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, doub
     a.ax[i] = ax;
     a.ay[i] = ay;
     a.az[i] = az;
-    if (a.vx) {  // the leapfrog's closing half-kick, same arithmetic as the kick kernel
-        const pos_t h = pos_t(a.h);
-        pos_t vx = fmat(h, ax, a.vx[i]), vy = fmat(h, ay, a.vy[i]), vz = fmat(h, az, a.vz[i]);
-        if (a.dx) {  // and the next step's kick and drift, as the kick-drift kernel does them
-            const pos_t dt = pos_t(a.dt);
-            vx = fmat(h, ax, vx);
-            vy = fmat(h, ay, vy);
-            vz = fmat(h, az, vz);
-            a.dx[i] = fmat(dt, vx, a.dx[i]);
-            a.dy[i] = fmat(dt, vy, a.dy[i]);
-            a.dz[i] = fmat(dt, vz, a.dz[i]);
-        }
-        a.vx[i] = vx;
-        a.vy[i] = vy;
-        a.vz[i] = vz;
-    }
+    if (TAIL) a.tail.apply(a.ni, i, a.xi, ax, ay, az);
     if (POT) {
         double self = 0.0;
         if (a.self_pot) {
@@ -185,28 +170,50 @@ __global__ __launch_bounds__(BS) void force_kernel(ForceArgs<Pol> a) {
             }
             if (POT) q[(size_t)3 * a.ni + i] = sp[k].total();
         } else if (ACC) {
-            finish_sink<Pol, POT>(a, i, sx[k].total(), sy[k].total(), sz[k].total(), sp[k].total());
+            finish_sink<Pol, POT, false>(a, i, sx[k].total(), sy[k].total(), sz[k].total(), sp[k].total());
         }
     }
 }
 
-// Adds the nsplit partial sums of every sink in split order, then finishes.
+// Adds the nsplit partial sums of every sink in a fixed order, then finishes:
+// wave g of a workgroup adds ranges g, g + 4, ... of 64 sinks (four ranges'
+// loads in flight together), and the first wave the four sums in wave order.
+// At small ni the kernel is one load latency after another, so four waves
+// share them.
 template <class Pol, bool POT>
 __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int nsplit) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= a.ni) return;
+    constexpr int N = POT ? 4 : 3;
+    __shared__ double other[3][N][64];
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;
     const size_t stride = (size_t)NQ * a.ni;
-    double sx = 0, sy = 0, sz = 0, sp = 0;
-    // eight ranges' loads in flight together, the adds in range order
-#pragma unroll 8
-    for (int s = 0; s < nsplit; ++s) {
-        const double* q = a.part + s * stride;
-        sx += q[i];
-        sy += q[(size_t)a.ni + i];
-        sz += q[(size_t)2 * a.ni + i];
-        if (POT) sp += q[(size_t)3 * a.ni + i];
+    double s[N] = {};
+    if (i < a.ni) {
+#pragma unroll 4
+        for (int r = g; r < nsplit; r += 4) {
+            const double* q = a.part + r * stride + i;
+#pragma unroll
+            for (int c = 0; c < N; ++c) s[c] += q[(size_t)c * a.ni];
+        }
     }
-    finish_sink<Pol, POT>(a, i, sx, sy, sz, sp);
+    if (g)
+#pragma unroll
+        for (int c = 0; c < N; ++c) other[g - 1][c][lane] = s[c];
+    __syncthreads();
+    if (g || i >= a.ni) return;
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+#pragma unroll
+        for (int c = 0; c < N; ++c) s[c] += other[v][c][lane];
+    finish_sink<Pol, POT, true>(a, i, s[0], s[1], s[2], POT ? s[N - 1] : 0.0);
+}
+
+// The leapfrog's tail after a pass in one range, whose workgroups finish their
+// own sinks while others still read the positions.
+template <class Pol>
+__global__ __launch_bounds__(256) void force_tail_kernel(ForceArgs<Pol> a) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < a.ni) a.tail.apply(a.ni, i, a.xi, a.ax[i], a.ay[i], a.az[i]);
 }
 
 template <class Pol>
@@ -233,12 +240,6 @@ ForceArgs<Pol> make_args(int64_t ni, const void* xi, int64_t nj, const void* xj,
     return a;
 }
 
-int split_span(int64_t nj, int split, int block) {
-    int64_t per = (nj + split - 1) / split;
-    per = (per + block - 1) / block * block;
-    return (int)per;
-}
-
 template <class Pol, bool ACC, bool POT, int BS, int K>
 hipError_t launch_shape(ForceArgs<Pol> a, int nsplit, hipStream_t stream) {
     dim3 grid((a.ni + BS * K - 1) / (BS * K), nsplit);
@@ -263,21 +264,20 @@ template <class Pol, bool ACC, bool POT>
 hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_only,
                      hipStream_t stream, bool* drifted = nullptr) {
     const int span = split_span(a.nj, sh.split, sh.block);
-    const int nsplit = (a.nj + span - 1) / span;
+    const int nsplit = split_ranges(a.nj, sh.split, sh.block);
     a.jspan = span;
+    if (drifted) *drifted = a.tail.x != nullptr;
     if (nsplit == 1 && !partials_only) {
-        // each workgroup finishes its own sinks while others may still read
-        // their positions as sources: no drift here
-        a.dx = a.dy = a.dz = nullptr;
-        if (drifted) *drifted = false;
         a.part = nullptr;
-        return launch_any<Pol, ACC, POT>(sh, a, 1, stream);
+        const hipError_t e = launch_any<Pol, ACC, POT>(sh, a, 1, stream);
+        if (e != hipSuccess || (!a.tail.v && !a.tail.store)) return e;
+        hipLaunchKernelGGL(force_tail_kernel<Pol>, dim3((a.ni + 255) / 256), dim3(256), 0, stream, a);
+        return hipGetLastError();
     }
-    if (drifted) *drifted = a.dx != nullptr;
     a.part = static_cast<double*>(ws);
     hipError_t e = launch_any<Pol, ACC, POT>(sh, a, nsplit, stream);
     if (e != hipSuccess || partials_only) return e;
-    hipLaunchKernelGGL((force_reduce_kernel<Pol, POT>), dim3((a.ni + 255) / 256), dim3(256), 0,
+    hipLaunchKernelGGL((force_reduce_kernel<Pol, POT>), dim3((a.ni + 63) / 64), dim3(256), 0,
                        stream, a, nsplit);
     return hipGetLastError();
 }
@@ -314,7 +314,7 @@ size_t force_partials_bound(int64_t n) {
     return (size_t)rows * NQ * sizeof(double);
 }
 
-Shape choose_force_shape(int prec, int64_t ni, int64_t nj) {
+Shape choose_force_shape(int prec, int64_t ni, int64_t nj, bool least) {
     // Measured on MI355X (launch-shape sweeps at N = 2^10 .. 2^20):
     //  * FP32 pair arithmetic: 1 sink per lane in 256-lane workgroups up to
     //    12288 sinks, then 2 sinks per lane, 128-lane workgroups, and
@@ -347,34 +347,33 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj) {
     if (split > max_ranges) split = max_ranges;
     if (split > 256) split = 256;
     if (split < 1) split = 1;
+    // Ranges as short as one tile, whatever nj, until there are 8192 waves (8
+    // per SIMD): with fewer, the pass takes as long as one range does (the
+    // rule above rounds 5003 sources in 19 ranges up to 10 ranges of two
+    // tiles on 800 waves). Not for the policies that keep a plain or
+    // compensated FP32 sum over the range: its length is part of their
+    // arithmetic. With both changes of the reduction and the ranges a pass
+    // takes 13.7 us instead of 21.9 at 1000 particles, 20.3 instead of 23.8
+    // at 5003 and 49.5 instead of 52.6 at 10000.
+    if (!least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN) {
+        split = std::max<int64_t>(split_ranges(nj, split, s.block),
+                                  short_tile_ranges(nj, s.block, waves));
+    }
     s.split = (int)split;
     return s;
 }
 
 hipError_t launch_force(int prec, const Shape& shape, int64_t ni, const void* xi, int64_t nj,
                         const void* xj, const void* mj, double eps, double G, bool self_set,
-                        void* acc, void* pot, void* ws, hipStream_t stream, void* kick_v,
-                        double kick_h, void* drift_x, double drift_dt, bool* drifted) {
+                        void* acc, void* pot, void* ws, hipStream_t stream, const StepTail& tail,
+                        bool* drifted) {
     hipError_t err = hipErrorInvalidValue;
     if (drifted) *drifted = false;
     dispatch_prec(prec, [&](auto tag) {
         using Pol = decltype(tag);
         using pos_t = typename Pol::pos_t;
         auto a = make_args<Pol>(ni, xi, nj, xj, mj, eps, G, self_set, acc, pot);
-        if (kick_v) {
-            pos_t* pv = static_cast<pos_t*>(kick_v);
-            a.vx = pv;
-            a.vy = pv + ni;
-            a.vz = pv + 2 * ni;
-            a.h = kick_h;
-            if (drift_x && self_set) {
-                pos_t* px = static_cast<pos_t*>(drift_x);
-                a.dx = px;
-                a.dy = px + ni;
-                a.dz = px + 2 * ni;
-                a.dt = drift_dt;
-            }
-        }
+        if (self_set) a.tail = TailArgs<pos_t>(tail);
         err = pot ? run_force<Pol, true, true>(shape, a, ws, false, stream, drifted)
                   : run_force<Pol, true, false>(shape, a, ws, false, stream, drifted);
     });

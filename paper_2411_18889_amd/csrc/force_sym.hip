@@ -107,10 +107,8 @@ struct SymFinishArgs {
     double G;
     typename Pol::pos_t *ax, *ay, *az;
     typename Pol::pos_t* pot;           // or nullptr
-    typename Pol::pos_t *vx, *vy, *vz;  // or nullptr
-    double h;
-    typename Pol::pos_t *dx, *dy, *dz;  // with vx: the next step's drift, or nullptr
-    double dt;
+    const typename Pol::pos_t* x;
+    TailArgs<typename Pol::pos_t> tail;
 };
 
 // One tile of sources against the K sinks of this lane. The tile is held as
@@ -280,8 +278,8 @@ __global__ __launch_bounds__(W * 64) void force_sym_kernel(SymArgs<Pol> a) {
 // The fold of one band (SymFinishArgs): adds a particle's partials in slot
 // order (in fin_t: FP64 for the tile-compensated and FP64 policies, FP32 for
 // the FP32 one) to its running sum; when its slots are complete, stores
-// a = G * sum and applies the optional half-kick v <- v + h a, with a as
-// stored; with P, also the potential -G (sum - m_i / eps).
+// a = G * sum and applies the leapfrog's tail; with P, also the potential
+// -G (sum - m_i / eps).
 template <class Pol, bool P>
 __global__ __launch_bounds__(256) void force_sym_finish_kernel(SymFinishArgs<Pol> a) {
     using pos_t = typename Pol::pos_t;
@@ -334,22 +332,7 @@ __global__ __launch_bounds__(256) void force_sym_finish_kernel(SymFinishArgs<Pol
     a.ax[i] = ax;
     a.ay[i] = ay;
     a.az[i] = az;
-    if (a.vx) {  // the leapfrog's closing half-kick, in the state type
-        const pos_t h = pos_t(a.h);
-        pos_t vx = fmat(h, ax, a.vx[i]), vy = fmat(h, ay, a.vy[i]), vz = fmat(h, az, a.vz[i]);
-        if (a.dx) {  // and the next step's kick and drift, as the kick-drift kernel does them
-            const pos_t dt = pos_t(a.dt);
-            vx = fmat(h, ax, vx);
-            vy = fmat(h, ay, vy);
-            vz = fmat(h, az, vz);
-            a.dx[i] = fmat(dt, vx, a.dx[i]);
-            a.dy[i] = fmat(dt, vy, a.dy[i]);
-            a.dz[i] = fmat(dt, vz, a.dz[i]);
-        }
-        a.vx[i] = vx;
-        a.vy[i] = vy;
-        a.vz[i] = vz;
-    }
+    a.tail.apply(a.n, i, a.x, ax, ay, az);
 }
 
 template <class Pol, int W, int K>
@@ -368,7 +351,7 @@ hipError_t launch_sym(const SymArgs<Pol>& a, bool pot, hipStream_t stream) {
 template <class Pol>
 hipError_t run_sym(const SymShape& sh, int64_t n, const void* x, const void* m, double eps,
                    double G, void* acc, void* ws, size_t ws_bytes, hipStream_t stream,
-                   void* kick_v, double kick_h, void* pot, void* drift_x, double drift_dt) {
+                   void* pot, const StepTail& tail) {
     using pos_t = typename Pol::pos_t;
     using calc_t = typename Pol::calc_t;
     using fin_t = typename Pol::fin_t;
@@ -402,20 +385,8 @@ hipError_t run_sym(const SymShape& sh, int64_t n, const void* x, const void* m, 
     f.ax = po;
     f.ay = po + n;
     f.az = po + 2 * n;
-    if (kick_v) {
-        pos_t* pv = static_cast<pos_t*>(kick_v);
-        f.vx = pv;
-        f.vy = pv + n;
-        f.vz = pv + 2 * n;
-        f.h = kick_h;
-        if (drift_x) {
-            pos_t* px = static_cast<pos_t*>(drift_x);
-            f.dx = px;
-            f.dy = px + n;
-            f.dz = px + 2 * n;
-            f.dt = drift_dt;
-        }
-    }
+    f.x = p;
+    f.tail = TailArgs<pos_t>(tail);
     a.part = parts;
     f.part = parts;
     f.nb = L.nb;
@@ -500,20 +471,16 @@ SymShape choose_sym_shape(int prec, int64_t n, bool pot) {
 
 hipError_t launch_force_sym(int prec, const SymShape& sh, int64_t n, const void* x,
                             const void* m, double eps, double G, void* acc, void* ws,
-                            size_t ws_bytes, hipStream_t stream, void* kick_v, double kick_h,
-                            void* pot, void* drift_x, double drift_dt, bool* drifted) {
+                            size_t ws_bytes, hipStream_t stream, void* pot,
+                            const StepTail& tail, bool* drifted) {
     if ((int64_t)sh.waves * sh.ipl == 0) return hipErrorInvalidValue;
-    if (!kick_v) drift_x = nullptr;
-    if (drifted) *drifted = drift_x != nullptr;
+    if (drifted) *drifted = tail.v && tail.drift_x;
     if (prec == NB_MIX_TILEC)
-        return run_sym<SymTileC>(sh, n, x, m, eps, G, acc, ws, ws_bytes, stream, kick_v, kick_h,
-                                 pot, drift_x, drift_dt);
+        return run_sym<SymTileC>(sh, n, x, m, eps, G, acc, ws, ws_bytes, stream, pot, tail);
     if (prec == NB_F32)
-        return run_sym<SymF32>(sh, n, x, m, eps, G, acc, ws, ws_bytes, stream, kick_v, kick_h,
-                               pot, drift_x, drift_dt);
+        return run_sym<SymF32>(sh, n, x, m, eps, G, acc, ws, ws_bytes, stream, pot, tail);
     if (prec == NB_F64)
-        return run_sym<SymF64>(sh, n, x, m, eps, G, acc, ws, ws_bytes, stream, kick_v, kick_h,
-                               pot, drift_x, drift_dt);
+        return run_sym<SymF64>(sh, n, x, m, eps, G, acc, ws, ws_bytes, stream, pot, tail);
     return hipErrorInvalidValue;
 }
 

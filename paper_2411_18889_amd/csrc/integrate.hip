@@ -47,12 +47,36 @@ __global__ __launch_bounds__(TPB) void reverse_drift_kernel(T* __restrict__ x, T
     }
 }
 
+// A checkpoint slot receives (x, v, a): one launch for the three arrays.
 template <typename T>
-__global__ __launch_bounds__(TPB) void axpy_kernel(T* __restrict__ y, const T* __restrict__ x, T a,
-                                                   int64_t count) {
+__global__ __launch_bounds__(TPB) void store_kernel(const T* __restrict__ x, const T* __restrict__ v,
+                                                    const T* __restrict__ a, T* __restrict__ slot,
+                                                    int64_t count) {
     for (int64_t k = blockIdx.x * (int64_t)TPB + threadIdx.x; k < count;
-         k += (int64_t)gridDim.x * TPB)
-        y[k] = y[k] + a * x[k];
+         k += (int64_t)gridDim.x * TPB) {
+        slot[k] = x[k];
+        slot[count + k] = v[k];
+        slot[2 * count + k] = a[k];
+    }
+}
+
+// lam_v <- lam_v + dt lam_x, and the state of a checkpoint slot: x, and v and
+// a where whole.
+template <typename T>
+__global__ __launch_bounds__(TPB) void reload_kernel(T* __restrict__ x, T* __restrict__ v,
+                                                     T* __restrict__ a, const T* __restrict__ lx,
+                                                     T* __restrict__ lv, T dt,
+                                                     const T* __restrict__ slot, int whole,
+                                                     int64_t count) {
+    for (int64_t k = blockIdx.x * (int64_t)TPB + threadIdx.x; k < count;
+         k += (int64_t)gridDim.x * TPB) {
+        lv[k] = fmat(dt, lx[k], lv[k]);
+        x[k] = slot[k];
+        if (whole) {
+            v[k] = slot[count + k];
+            a[k] = slot[2 * count + k];
+        }
+    }
 }
 
 }  // namespace
@@ -88,15 +112,36 @@ hipError_t launch_reverse_drift(int prec, int64_t n, void* x, void* v, const voi
     return hipGetLastError();
 }
 
-hipError_t launch_axpy_pos(int prec, int64_t count, void* y, const void* x, double a,
-                           hipStream_t stream) {
-    if (prec == NB_F32)
-        hipLaunchKernelGGL(axpy_kernel<float>, grid_for(count), dim3(TPB), 0, stream,
-                           static_cast<float*>(y), static_cast<const float*>(x), float(a), count);
-    else
-        hipLaunchKernelGGL(axpy_kernel<double>, grid_for(count), dim3(TPB), 0, stream,
-                           static_cast<double*>(y), static_cast<const double*>(x), a, count);
+namespace {
+template <typename T>
+hipError_t store_any(int64_t c, const void* x, const void* v, const void* acc, void* slot,
+                     hipStream_t stream) {
+    hipLaunchKernelGGL(store_kernel<T>, grid_for(c), dim3(TPB), 0, stream, static_cast<const T*>(x),
+                       static_cast<const T*>(v), static_cast<const T*>(acc), static_cast<T*>(slot), c);
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t reload_any(int64_t c, void* x, void* v, void* acc, const void* lam_x, void* lam_v,
+                      double dt, const void* slot, bool whole, hipStream_t stream) {
+    hipLaunchKernelGGL(reload_kernel<T>, grid_for(c), dim3(TPB), 0, stream, static_cast<T*>(x),
+                       static_cast<T*>(v), static_cast<T*>(acc), static_cast<const T*>(lam_x),
+                       static_cast<T*>(lam_v), T(dt), static_cast<const T*>(slot), int(whole), c);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_store(int prec, int64_t n, const void* x, const void* v, const void* acc,
+                        void* slot, hipStream_t stream) {
+    return prec == NB_F32 ? store_any<float>(3 * n, x, v, acc, slot, stream)
+                          : store_any<double>(3 * n, x, v, acc, slot, stream);
+}
+
+hipError_t launch_reload(int prec, int64_t n, void* x, void* v, void* acc, const void* lam_x,
+                         void* lam_v, double dt, const void* slot, bool whole, hipStream_t stream) {
+    return prec == NB_F32
+               ? reload_any<float>(3 * n, x, v, acc, lam_x, lam_v, dt, slot, whole, stream)
+               : reload_any<double>(3 * n, x, v, acc, lam_x, lam_v, dt, slot, whole, stream);
 }
 
 }  // namespace nb

@@ -107,6 +107,10 @@ int hip_status(hipError_t e) {
 
 namespace {
 
+// Scratch bytes a call may use beyond its least: none at a NULL or misaligned
+// pointer (which is an error only where the least is more than none).
+size_t usable_ws(const void* ws, size_t ws_bytes) { return ws && aligned(ws, 256) ? ws_bytes : 0; }
+
 int check_ws(void* ws, size_t ws_bytes, size_t need) {
     if (need == 0) return NB_OK;
     if (!ws || !aligned(ws, 256) || ws_bytes < need) return NB_EWORKSPACE;
@@ -115,10 +119,6 @@ int check_ws(void* ws, size_t ws_bytes, size_t need) {
 
 size_t accel_ws(const Shape& s, int64_t ni) {
     return s.split > 1 ? force_partials_bytes(s, ni) : 0;
-}
-
-hipError_t copy_state(void* dst, const void* src, size_t bytes, hipStream_t stream) {
-    return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, stream);
 }
 
 // ---- instantiated leapfrog graphs (nbody_step with NB_GRAPH) ---------------
@@ -232,9 +232,10 @@ int sym_from_launch(const nb_launch& l, SymShape lib, SymShape* out) {
 // itself where the policy has one and no launch overrides it; else the
 // one-sided kernel in the library's shape with the launch's fields.
 int resolve_accel(int prec, int64_t ni, int64_t nj, bool self_set, bool pot,
-                  const nb_launch* launch, SymShape* sym, Shape* sh) {
+                  const nb_launch* launch, SymShape* sym, Shape* sh, Shape* least) {
     *sym = (self_set && !launch) ? choose_sym_shape(prec, ni, pot) : SymShape{0, 0};
     *sh = choose_force_shape(prec, ni, nj);
+    *least = choose_force_shape(prec, ni, nj, true);
     if (!launch) return NB_OK;
     if (launch->symmetric) {
         if (!self_set) return NB_EUNSUPPORTED;
@@ -245,13 +246,16 @@ int resolve_accel(int prec, int64_t ni, int64_t nj, bool self_set, bool pot,
     if (launch->i_per_lane) sh->ipl = launch->i_per_lane;
     if (launch->block) sh->block = launch->block;
     if (launch->split) sh->split = launch->split;
+    *least = *sh;
     return shape_supported(*sh) ? NB_OK : NB_EUNSUPPORTED;
 }
 
 // The same for the fused adjoint pass of n particles.
-int resolve_adjoint(int prec, int64_t n, const nb_launch* launch, SymShape* sym, Shape* sh) {
+int resolve_adjoint(int prec, int64_t n, const nb_launch* launch, SymShape* sym, Shape* sh,
+                    Shape* least) {
     *sym = choose_adjoint_sym_shape(prec, n);
     *sh = choose_adjoint_shape(prec, n);
+    *least = choose_adjoint_shape(prec, n, true);
     if (!launch) return NB_OK;
     if (launch->symmetric) {
         const int st = sym_from_launch(*launch, *sym, sym);
@@ -262,6 +266,7 @@ int resolve_adjoint(int prec, int64_t n, const nb_launch* launch, SymShape* sym,
     if (launch->i_per_lane) sh->ipl = launch->i_per_lane;
     if (launch->block) sh->block = launch->block;
     if (launch->split) sh->split = launch->split;
+    *least = *sh;
     return adjoint_shape_supported(*sh) ? NB_OK : NB_EUNSUPPORTED;
 }
 
@@ -300,7 +305,8 @@ int accel_plan(int64_t ni, const void* xi, int64_t nj, const void* xj, const voi
                 overlaps(pot, (size_t)ni * ps, mj, (size_t)nj * ms)))
         return NB_EINVAL;
     Shape sh;
-    const int st = resolve_accel(prec, ni, nj, self_set, pot != nullptr, launch, &plan->sym, &sh);
+    const int st = resolve_accel(prec, ni, nj, self_set, pot != nullptr, launch, &plan->sym, &sh,
+                                 &plan->least);
     if (st != NB_OK) return st;
     plan->sh = sh;
     plan->self_set = self_set;
@@ -309,7 +315,8 @@ int accel_plan(int64_t ni, const void* xi, int64_t nj, const void* xj, const voi
         plan->need = sym_min_bytes(L);
         plan->full = sym_full_bytes(L);
     } else {
-        plan->need = plan->full = accel_ws(sh, ni);
+        plan->need = std::min(accel_ws(plan->least, ni), accel_ws(sh, ni));
+        plan->full = accel_ws(sh, ni);
     }
     return NB_OK;
 }
@@ -337,9 +344,9 @@ hipError_t accel_launch(const AccelPlan& p, int64_t ni, const void* xi, int64_t 
                         void* ws, size_t ws_bytes, hipStream_t s) {
     return timed(NB_PROF_FORCE, s, [&] {
         if (p.sym.waves)
-            return launch_force_sym(prec, p.sym, ni, xi, mj, eps, G, acc, ws, ws_bytes, s,
-                                    nullptr, 0.0, pot);
-        return launch_force(prec, p.sh, ni, xi, nj, xj, mj, eps, G, p.self_set, acc, pot, ws, s);
+            return launch_force_sym(prec, p.sym, ni, xi, mj, eps, G, acc, ws, ws_bytes, s, pot);
+        const Shape& sh = ws_bytes >= accel_ws(p.sh, ni) ? p.sh : p.least;
+        return launch_force(prec, sh, ni, xi, nj, xj, mj, eps, G, p.self_set, acc, pot, ws, s);
     });
 }
 
@@ -356,8 +363,13 @@ int accel_common(int64_t ni, const void* xi, int64_t nj, const void* xj, const v
     if ((st = check_ws(ws, ws_bytes, plan.need)) != NB_OK) return st;
     // the bytes the pass may use: a banded pass uses what it is given, up to
     // every partial at once
-    const size_t used = std::min(ws_bytes, plan.full);
-    if (accel_ws_overlaps(ws, used, ni, xi, nj, xj, mj, prec, acc, pot)) return NB_EINVAL;
+    size_t used = std::min(usable_ws(ws, ws_bytes), plan.full);
+    if (accel_ws_overlaps(ws, used, ni, xi, nj, xj, mj, prec, acc, pot)) {
+        // the one-sided kernel's shape with the least scratch may still fit
+        if (plan.sym.waves || accel_ws_overlaps(ws, plan.need, ni, xi, nj, xj, mj, prec, acc, pot))
+            return NB_EINVAL;
+        used = plan.need;
+    }
     if ((st = check_device()) != NB_OK) return st;
     return hip_status(accel_launch(plan, ni, xi, nj, xj, mj, eps, G, prec, acc, pot, ws, used,
                                    static_cast<hipStream_t>(stream)));
@@ -399,62 +411,67 @@ int nbody_step(int64_t n, void* x, void* v, const void* m, void* acc, double eps
         if (overlaps(ckpt, cb, x, vb) || overlaps(ckpt, cb, v, vb) || overlaps(ckpt, cb, acc, vb))
             return NB_EINVAL;
     }
-    const Shape sh = choose_force_shape(prec, n, n);
+    auto ws_overlaps = [&](size_t bytes) {
+        return bytes && (overlaps(ws, bytes, x, vb) || overlaps(ws, bytes, v, vb) ||
+                         overlaps(ws, bytes, m, (size_t)n * ms) || overlaps(ws, bytes, acc, vb) ||
+                         (ckpt && overlaps(ws, bytes, ckpt, (size_t)(nsteps / ckpt_every + 1) * 3 * vb)));
+    };
+    Shape sh = choose_force_shape(prec, n, n);
+    if (usable_ws(ws, ws_bytes) < accel_ws(sh, n) || ws_overlaps(accel_ws(sh, n)))
+        sh = choose_force_shape(prec, n, n, true);
     const SymShape sym = choose_sym_shape(prec, n);
     const SymLayout L = sym.waves ? sym_layout(prec, sym, n) : SymLayout{};
     const size_t need = sym.waves ? sym_min_bytes(L) : accel_ws(sh, n);
     int st = check_ws(ws, ws_bytes, need);
     if (st != NB_OK) return st;
     const size_t used = sym.waves ? std::min(ws_bytes, sym_full_bytes(L)) : need;
-    if (used && (overlaps(ws, used, x, vb) || overlaps(ws, used, v, vb) ||
-                 overlaps(ws, used, m, (size_t)n * ms) || overlaps(ws, used, acc, vb) ||
-                 (ckpt && overlaps(ws, used, ckpt, (size_t)(nsteps / ckpt_every + 1) * 3 * vb))))
-        return NB_EINVAL;
+    if (ws_overlaps(used)) return NB_EINVAL;
     if ((st = check_device()) != NB_OK) return st;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const double h = 0.5 * dt;
     // Enqueues the whole loop on q.
     auto enqueue = [&](hipStream_t q) -> hipError_t {
-        // force(kick, drift): a <- a(x), and with kick the closing half-kick
-        // v <- v + h a in the same launch group (the pair pass never reads
-        // v); with drift also the next step's kick and drift, in the
-        // finishing kernel, where the pass has one (*drifted tells)
-        auto force = [&](bool kick, bool drift, bool* drifted) {
-            return timed(NB_PROF_FORCE, q, [&] {
-                void* kv = kick ? v : nullptr;
-                void* dx = (kick && drift) ? x : nullptr;
-                if (sym.waves)
-                    return launch_force_sym(prec, sym, n, x, m, eps, G, acc, ws, used, q, kv, h, nullptr,
-                                            dx, dt, drifted);
-                return launch_force(prec, sh, n, x, n, x, m, eps, G, true, acc, nullptr, ws, q, kv,
-                                    h, dx, dt, drifted);
-            });
+        // force(kick, slot, drift): a <- a(x) and, in the same launch group
+        // (the pair pass never reads v), with kick the closing half-kick v <-
+        // v + h a, the checkpoint slot the state goes to, and with drift the
+        // next step's kick and drift, in the finishing kernel, where the
+        // pass has one (*drifted tells)
+        auto slot_at = [&](int64_t slot) -> void* {
+            return static_cast<char*>(ckpt) + (size_t)slot * 3 * vb;
         };
-        auto store = [&](int64_t slot) -> hipError_t {
-            return timed(NB_PROF_COPY, q, [&] {
-                char* base = static_cast<char*>(ckpt) + (size_t)slot * 3 * vb;
-                hipError_t e = copy_state(base, x, vb, q);
-                if (e == hipSuccess) e = copy_state(base + vb, v, vb, q);
-                if (e == hipSuccess) e = copy_state(base + 2 * vb, acc, vb, q);
-                return e;
+        auto force = [&](bool kick, void* slot, bool drift, bool* drifted) {
+            return timed(NB_PROF_FORCE, q, [&] {
+                StepTail t;
+                t.v = kick ? v : nullptr;
+                t.h = h;
+                t.store = slot;
+                t.store_v = v;
+                t.drift_x = drift ? x : nullptr;
+                t.dt = dt;
+                if (sym.waves)
+                    return launch_force_sym(prec, sym, n, x, m, eps, G, acc, ws, used, q, nullptr, t,
+                                            drifted);
+                return launch_force(prec, sh, n, x, n, x, m, eps, G, true, acc, nullptr, ws, q, t,
+                                    drifted);
             });
         };
         hipError_t e = hipSuccess;
-        if (!(flags & NB_ACC_VALID)) e = force(false, false, nullptr);
-        if (e == hipSuccess && ckpt) e = store(0);
+        if (!(flags & NB_ACC_VALID))
+            e = force(false, ckpt ? slot_at(0) : nullptr, false, nullptr);
+        else if (ckpt)
+            e = timed(NB_PROF_COPY, q, [&] { return launch_store(prec, n, x, v, acc, slot_at(0), q); });
         // a step's kick and drift run in the previous force pass's finishing
-        // kernel unless that pass ended the call or a checkpoint slot, whose
-        // stored state is the synchronised one
+        // kernel unless that pass ended the call
         bool drifted = false;
         for (int64_t k = 0; k < nsteps && e == hipSuccess; ++k) {
             if (!drifted)
                 e = timed(NB_PROF_UPDATE, q, [&] { return launch_kick_drift(prec, n, x, v, acc, h, dt, q); });
             const bool stored = ckpt && (k + 1) % ckpt_every == 0;
-            const bool fuse = (k + 1 < nsteps) && !stored;
             drifted = false;
-            if (e == hipSuccess) e = force(true, fuse, &drifted);
-            if (e == hipSuccess && stored) e = store((k + 1) / ckpt_every);
+            if (e == hipSuccess)
+                e = force(true, stored ? slot_at((k + 1) / ckpt_every) : nullptr, k + 1 < nsteps,
+                          &drifted);
         }
         return e;
     };
@@ -534,71 +551,80 @@ int adjoint_common(int64_t n, void* x, void* v, const void* m, void* acc, void* 
         for (int p = 0; p < 6; ++p)
             if (overlaps(ckpt, cb, bufs[p], sizes[p])) return NB_EINVAL;
     }
-    Shape sh;
+    Shape sh, shl;
     SymShape sym;
-    int st = resolve_adjoint(prec, n, launch, &sym, &sh);
+    int st = resolve_adjoint(prec, n, launch, &sym, &sh, &shl);
     if (st != NB_OK) return st;
+    auto ws_overlaps = [&](size_t bytes) {
+        if (!bytes) return false;
+        if (overlaps(ws, bytes, m, (size_t)n * ms)) return true;
+        for (int p = 0; p < 6; ++p)
+            if (overlaps(ws, bytes, bufs[p], sizes[p])) return true;
+        return ckpt && overlaps(ws, bytes, ckpt, (size_t)(step_end / ckpt_every + 1) * 3 * vb);
+    };
+    if (!sym.waves) {
+        const size_t most = adjoint_partials_need(prec, sym, sh, n, true);
+        if (usable_ws(ws, ws_bytes) < most || ws_overlaps(most)) sh = shl;
+    }
     const size_t need = adjoint_partials_need(prec, sym, sh, n, true);
     st = check_ws(ws, ws_bytes, need);
     if (st != NB_OK) return st;
     const size_t used = sym.waves ? std::min(ws_bytes, sym_full_bytes(adjoint_sym_layout(prec, sym, n, true)))
                                   : need;
-    if (used) {
-        if (overlaps(ws, used, m, (size_t)n * ms)) return NB_EINVAL;
-        for (int p = 0; p < 6; ++p)
-            if (overlaps(ws, used, bufs[p], sizes[p])) return NB_EINVAL;
-        if (ckpt && overlaps(ws, used, ckpt, (size_t)(step_end / ckpt_every + 1) * 3 * vb))
-            return NB_EINVAL;
-    }
+    if (ws_overlaps(used)) return NB_EINVAL;
     if ((st = check_device()) != NB_OK) return st;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const double h = 0.5 * dt;
     double* lm = static_cast<double*>(lam_m);
     hipError_t e = hipSuccess;
-    // fused(c, update_state, drift): one adjoint pass; with drift its
-    // finishing kernel (where the pass has one) also applies the next step's
-    // reverse drift, and `drifted` records that it did
-    bool drifted = false;
-    auto fused = [&](double c, bool update_state, bool drift) {
-        drifted = false;
-        return timed(NB_PROF_ADJOINT, s, [&] {
-            void* dx = drift ? x : nullptr;
-            if (sym.waves)
-                return launch_adjoint_sym(prec, sym, n, x, m, lam_v, eps, G, c, update_state, h, acc, v,
-                                          lam_x, lm, ws, used, s, dx, dt, &drifted);
-            return launch_adjoint(prec, sh, n, x, m, lam_v, eps, G, c, update_state, h, acc, v, lam_x,
-                                  lm, ws, s, dx, dt, &drifted);
-        });
-    };
     // the state walked back to at loop index k, and whether it is reloaded
     auto anchor_at = [&](int64_t k) {
         return k < nsteps && ckpt && ((step_end - 1 - k) % ckpt_every == 0);
     };
-    if (flags & NB_ADJ_ENTRY_HALF) e = fused(h, false, nsteps > 0 && !anchor_at(0));
+    // how the walk enters loop index k: by the reverse drift, or by reloading
+    // the slot of the state it reaches (absolute step step_end - 1 - k), with
+    // v and acc where something reads them: the next reverse drift, or the
+    // caller after the last step
+    auto enter_at = [&](int64_t k) {
+        WalkNext w;
+        if (k >= nsteps) return w;
+        w.x = x;
+        w.dt = dt;
+        if (anchor_at(k)) {
+            w.slot = static_cast<const char*>(ckpt) +
+                     (size_t)((step_end - 1 - k) / ckpt_every) * 3 * vb;
+            w.whole = k + 1 == nsteps || !anchor_at(k + 1);
+        }
+        return w;
+    };
+    // fused(c, update_state, k): one adjoint pass whose finishing kernel
+    // (where the pass has one) also enters loop index k; `entered` records
+    // that it did
+    bool entered = false;
+    auto fused = [&](double c, bool update_state, int64_t k) {
+        entered = false;
+        return timed(NB_PROF_ADJOINT, s, [&] {
+            const WalkNext w = enter_at(k);
+            if (sym.waves)
+                return launch_adjoint_sym(prec, sym, n, x, m, lam_v, eps, G, c, update_state, h, acc, v,
+                                          lam_x, lm, ws, used, s, w, &entered);
+            return launch_adjoint(prec, sh, n, x, m, lam_v, eps, G, c, update_state, h, acc, v, lam_x,
+                                  lm, ws, s, w, &entered);
+        });
+    };
+    if (flags & NB_ADJ_ENTRY_HALF) e = fused(h, false, 0);
     for (int64_t k = 0; k < nsteps && e == hipSuccess; ++k) {
-        const int64_t step = step_end - 1 - k;  // absolute index of the state walked back to
-        const bool anchor = anchor_at(k);
-        const bool walked = drifted;  // the previous pass already did this step's reverse drift
-        drifted = false;
-        if (anchor) {
-            e = timed(NB_PROF_UPDATE, s, [&] { return launch_axpy_pos(prec, 3 * n, lam_v, lam_x, dt, s); });
-            const char* base = static_cast<const char*>(ckpt) + (size_t)(step / ckpt_every) * 3 * vb;
-            if (e == hipSuccess)
-                e = timed(NB_PROF_COPY, s, [&] {
-                    hipError_t r = copy_state(x, base, vb, s);
-                    if (r == hipSuccess) r = copy_state(v, base + vb, vb, s);
-                    if (r == hipSuccess) r = copy_state(acc, base + 2 * vb, vb, s);
-                    return r;
-                });
-        } else if (!walked) {
-            e = timed(NB_PROF_UPDATE, s, [&] {
-                return launch_reverse_drift(prec, n, x, v, acc, lam_x, lam_v, h, dt, s);
+        if (!entered) {
+            const WalkNext w = enter_at(k);
+            e = timed(w.slot ? NB_PROF_COPY : NB_PROF_UPDATE, s, [&] {
+                return w.slot ? launch_reload(prec, n, x, v, acc, lam_x, lam_v, dt, w.slot, w.whole, s)
+                              : launch_reverse_drift(prec, n, x, v, acc, lam_x, lam_v, h, dt, s);
             });
         }
         const bool last = (k == nsteps - 1);
         const double c = last ? ((flags & NB_ADJ_EXIT_FULL) ? dt : h) : dt;
-        if (e == hipSuccess) e = fused(c, !anchor, !last && !anchor_at(k + 1));
+        if (e == hipSuccess) e = fused(c, !anchor_at(k), k + 1);
     }
     return hip_status(e);
 }
@@ -665,13 +691,13 @@ size_t nbody_pass_workspace_size(int op, int64_t ni, int64_t nj, int prec, int s
                                  int potential, const nb_launch* launch) {
     if (!valid_prec(prec) || ni < 1 || nj < 1 || ni > kMaxN || nj > kMaxN) return 0;
     SymShape sym;
-    Shape sh;
+    Shape sh, least;
     if (op == NB_OP_ADJOINT) {
-        if (ni != nj || resolve_adjoint(prec, ni, launch, &sym, &sh) != NB_OK) return 0;
+        if (ni != nj || resolve_adjoint(prec, ni, launch, &sym, &sh, &least) != NB_OK) return 0;
         return adjoint_partials_need(prec, sym, sh, ni, false);
     }
     if (op != NB_OP_ACCEL || (self_set && ni != nj)) return 0;
-    if (resolve_accel(prec, ni, nj, self_set != 0, potential != 0, launch, &sym, &sh) != NB_OK)
+    if (resolve_accel(prec, ni, nj, self_set != 0, potential != 0, launch, &sym, &sh, &least) != NB_OK)
         return 0;
     if (sym.waves) return sym_default_bytes(sym_layout(prec, sym, ni, potential != 0));
     return accel_ws(sh, ni);

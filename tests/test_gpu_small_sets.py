@@ -1,0 +1,109 @@
+"""The one-sided passes of small sets: ranges as short as one tile of sources,
+their reduction by four waves a sink, the shape a smaller workspace falls back
+to, and a leapfrog and its reverse walk whose checkpoints are stored and
+reloaded by the passes themselves. Against the oracle at the library's
+accuracy targets, and bitwise against the same calls composed step by step."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2411_18889_amd as nb
+from nbody_inputs import plummer_sphere
+from paper_2411_18889_amd import _lib
+from tests.gpu_util import DEV, PRECS, TOL, host, rel, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("n", (1, 63, 64, 65, 256, 257, 1000, 1025, 4097, 12287))
+def test_force_and_potential(prec, n):
+    x, v, m = plummer_sphere(n, 900 + n)
+    m = m * np.random.default_rng(n).uniform(0.5, 1.5, size=n)
+    eps = 2.0 ** -6
+    xd, _, md = to_dev(x, v, m, prec)
+    a, p = nb.accel(xd, md, eps, prec=prec, potential=True)
+    ao, po = oracle.accel(host(xd), host(md), eps, potential=True)
+    if n > 1:
+        assert rel(host(a), ao) <= TOL[prec] and rel(host(p), po) <= TOL[prec]
+    else:
+        assert float(a.abs().max()) == 0.0 and float(p.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("ni,nj", [(1, 3000), (239, 55708), (70, 257), (5000, 300), (3000, 17000)])
+@pytest.mark.parametrize("prec", ("f64", "f32", "mix_tilec", "mix_acc64"))
+def test_separate_sets_at_every_workspace(prec, ni, nj):
+    """The library's shape, and the one that a workspace too small for it (or
+    none) falls back to."""
+    xj, v, m = plummer_sphere(nj, 31)
+    xi = plummer_sphere(ni, 32)[0] + 0.01
+    eps = 2.0 ** -6
+    xjd, _, md = to_dev(xj, v, m, prec)
+    xid = torch.tensor(xi, dtype=xjd.dtype, device=DEV)
+    ref = oracle.accel(host(xid), host(md), eps, xj=host(xjd))
+    need = int(_lib.lib().nbody_pass_workspace_size(0, ni, nj, _lib.PREC[prec], 0, 0, None))
+    got = 0
+    for w in sorted({need, max(0, need - 1), need // 2, 0}, reverse=True):
+        ws = torch.empty(w, dtype=torch.uint8, device=DEV)
+        try:
+            a = nb.accel(xid, md, eps, prec=prec, xj=xjd, workspace=ws)
+        except _lib.NBodyError as e:
+            assert e.status == _lib.NB_EWORKSPACE and w < need
+            continue
+        got += 1
+        assert rel(host(a), ref) <= TOL[prec]
+    assert got >= 1
+
+
+@pytest.mark.parametrize("prec,n", [("mix_tilec", 40), ("mix_tilec", 700), ("f64", 64), ("f64", 1024),
+                                    ("f32", 700), ("mix_kahan", 3000), ("mix_acc64", 3000),
+                                    ("mix_tilec", 13000), ("f32", 13000)])
+@pytest.mark.parametrize("every", (1, 2, 3))
+def test_checkpoints_are_the_states(prec, n, every):
+    """Every slot holds bitwise the state that separate calls of one step
+    reach, with or without a valid acceleration at the start, and the walk
+    over them ends at the first state with the gradients of a walk that
+    reloads the same slots step by step."""
+    S, eps, dt = 7, 2.0 ** -6, 2.0 ** -7
+    x, v, m = plummer_sphere(n, 77)
+    xd, vd, md = to_dev(x, v, m, prec)
+    acc = torch.empty_like(xd)
+    ckpt = torch.full((S // every + 1, 9 * n), float("nan"), dtype=xd.dtype, device=DEV)
+    nb.step(xd, vd, md, acc, eps, dt, S, prec=prec, ckpt=ckpt, ckpt_every=every)
+    xs, vs, _ = to_dev(x, v, m, prec)
+    a = torch.empty_like(xs)
+    nb.step(xs, vs, md, a, eps, dt, 0, prec=prec)
+    states = [torch.cat([t.reshape(-1) for t in (xs, vs, a)])]
+    for _ in range(S):
+        nb.step(xs, vs, md, a, eps, dt, 1, prec=prec, acc_valid=True)
+        states.append(torch.cat([t.reshape(-1) for t in (xs, vs, a)]))
+    for k in range(S // every + 1):
+        assert torch.equal(ckpt[k], states[k * every]), k
+    assert torch.equal(torch.cat([t.reshape(-1) for t in (xd, vd, acc)]), states[S])
+    valid = torch.full_like(ckpt, float("nan"))
+    x2, v2, _ = to_dev(x, v, m, prec)
+    a2 = states[0][6 * n:].reshape(3, n).clone()
+    nb.step(x2, v2, md, a2, eps, dt, S, prec=prec, ckpt=valid, ckpt_every=every, acc_valid=True)
+    assert torch.equal(valid, ckpt)
+
+    rng = np.random.default_rng(n)
+    lam = [torch.tensor(rng.normal(size=(3, n)), dtype=xd.dtype, device=DEV) for _ in range(2)]
+    out = []
+    for chained in (False, True):
+        st = [t.clone() for t in (xd, vd, acc)]
+        lx, lv = lam[0].clone(), lam[1].clone()
+        lm = torch.zeros(n, dtype=torch.float64, device=DEV)
+        if chained:
+            for k in range(S):
+                nb.step_adjoint(st[0], st[1], md, st[2], lx, lv, lm, eps, dt, 1, prec=prec,
+                                entry_half=(k == 0), exit_full=(k < S - 1), ckpt=ckpt,
+                                ckpt_every=every, step_end=S - k)
+        else:
+            nb.step_adjoint(st[0], st[1], md, st[2], lx, lv, lm, eps, dt, S, prec=prec,
+                            entry_half=True, ckpt=ckpt, ckpt_every=every, step_end=S)
+        out.append(st + [lx, lv, lm])
+    assert torch.equal(torch.cat([t.reshape(-1) for t in out[0][:3]]), states[0])
+    for p, q in zip(*out):
+        assert torch.equal(p, q)
