@@ -89,8 +89,11 @@ __device__ __forceinline__ void finish_adj(const AdjArgs<Pol>& a, int i, const d
 
 // F: also sum the force a (quantities 0..2, for a pass that walks the state
 // back); without it they stay 0 and the pair body is 4 operations shorter.
-template <class Pol, int BS, int K, bool F>
-__global__ __launch_bounds__(BS) void adjoint_kernel(AdjArgs<Pol> a) {
+// FEW: built for few waves in flight (kFewWaves): tile-compensated entry pass
+// 37.0 -> 25.4 us at 2500 particles, 39 -> 33 at 5003 (at 10000 88 against 85,
+// so not there).
+template <class Pol, int BS, int K, bool F, bool FEW>
+__global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void adjoint_kernel(AdjArgs<Pol> a) {
     using calc_t = typename Pol::calc_t;
     using sum_t = typename Pol::sum_t;
     using V4 = typename Vec4<calc_t>::type;
@@ -243,11 +246,17 @@ __global__ __launch_bounds__(256) void adjoint_reduce_kernel(AdjArgs<Pol> a, int
 template <class Pol, int BS, int K>
 hipError_t launch_shape(AdjArgs<Pol> a, int nsplit, hipStream_t stream) {
     dim3 grid((a.n + BS * K - 1) / (BS * K), nsplit);
-    if (a.update_state)
-        hipLaunchKernelGGL((adjoint_kernel<Pol, BS, K, true>), grid, dim3(BS), 0, stream, a);
-    else
-        hipLaunchKernelGGL((adjoint_kernel<Pol, BS, K, false>), grid, dim3(BS), 0, stream, a);
-    return hipGetLastError();
+    auto launch = [&](auto few) {
+        constexpr bool FEW = decltype(few)::value;
+        if (a.update_state)
+            hipLaunchKernelGGL((adjoint_kernel<Pol, BS, K, true, FEW>), grid, dim3(BS), 0, stream, a);
+        else
+            hipLaunchKernelGGL((adjoint_kernel<Pol, BS, K, false, FEW>), grid, dim3(BS), 0, stream, a);
+        return hipGetLastError();
+    };
+    if constexpr (K == 1 && std::is_same<typename Pol::calc_t, float>::value)
+        if ((int64_t)grid.x * nsplit * (BS / 64) < kFewWaves) return launch(std::true_type{});
+    return launch(std::false_type{});
 }
 
 template <class Pol>

@@ -250,6 +250,12 @@ inline int split_ranges(int64_t nj, int64_t split, int block) {
     const int64_t span = split_span(nj, (int)split, block);
     return (int)((nj + span - 1) / span);
 }
+// Few waves in flight (under 4 per SIMD over the whole pass): the one-sided
+// kernels with one sink per lane then run in a build that may spend registers
+// on more sources in flight instead of on more waves.
+constexpr int64_t kFewWaves = 4096;
+#define NB_WAVES_PER_EU(few) __attribute__((amdgpu_waves_per_eu((few) ? 4 : 1, (few) ? 6 : 8)))
+
 // The most ranges of equal numbers of tiles, at most 256, with which `waves`
 // wavefronts a range make at most 8192 (8 per SIMD).
 inline int64_t short_tile_ranges(int64_t nj, int block, int64_t waves) {
