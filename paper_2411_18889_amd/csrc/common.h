@@ -238,6 +238,8 @@ struct Shape {
     int ipl;    // sinks per lane
     int block;  // threads per workgroup = j-tile length
     int split;  // j-ranges per sink
+    bool lanes = false;  // the force kernel with its sources on the lanes (block
+                         // lanes, ipl sinks per workgroup); no partials
 };
 
 // A split of nj sources gives ranges of whole tiles (`block` sources): their
@@ -265,9 +267,11 @@ inline int64_t short_tile_ranges(int64_t nj, int block, int64_t waves) {
     return (tiles + per - 1) / per;
 }
 
-// Library choice of shape for ni sinks, nj sources. least: the shape with the
-// smaller workspace that a call takes when the first one's does not fit.
-Shape choose_force_shape(int prec, int64_t ni, int64_t nj, bool least = false);
+// Library choice of shape for ni sinks, nj sources: of all kernels, of the
+// kernel with split ranges, or of that the shape with the smaller workspace,
+// which a call takes when the first one's does not fit.
+enum class Pick { Best, Split, Least };
+Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick = Pick::Best);
 Shape choose_adjoint_shape(int prec, int64_t n, bool least = false);
 // Shapes the one-sided force / adjoint kernels are built for.
 bool shape_supported(const Shape& s);
@@ -281,15 +285,18 @@ size_t adjoint_partials_bytes(const Shape& s, int64_t n);
 
 // What a leapfrog's force pass does to each particle once its acceleration is
 // stored, in this order (each part optional):
-//   v         closing half-kick v <- v + h acc, with acc as stored;
+//   v, close  closing half-kick v <- v + h acc, with acc as stored (not after
+//             the pass that only evaluates the first acceleration);
 //   store     a checkpoint slot receives (x, v, acc), 3 x 3n elements;
 //   drift_x   (with v) the next step's kick and drift, v <- v + h acc; x <- x +
-//             dt v, in a kernel that runs after every read of x (*drifted).
+//             dt v, written to drift_x: the positions themselves where a
+//             kernel of the pass runs after every read of them, else another
+//             array (*drifted tells whether it was done).
 struct StepTail {
-    void* v = nullptr;
+    void* v = nullptr;  // nullptr: no tail
+    bool close = true;
     double h = 0.0;
     void* store = nullptr;
-    const void* store_v = nullptr;  // v of the slot where v is not kicked
     void* drift_x = nullptr;
     double dt = 0.0;
 };
@@ -299,27 +306,22 @@ template <typename T>
 struct TailArgs {
     T* v = nullptr;
     T* store = nullptr;
-    const T* store_v = nullptr;
     T* x = nullptr;
+    int close = 0;
     T h = T(0), dt = T(0);
     TailArgs() = default;
     explicit TailArgs(const StepTail& t)
         : v(static_cast<T*>(t.v)), store(static_cast<T*>(t.store)),
-          store_v(static_cast<const T*>(t.store_v)), x(static_cast<T*>(t.v ? t.drift_x : nullptr)),
-          h(T(t.h)), dt(T(t.dt)) {}
+          x(static_cast<T*>(t.drift_x)), close(t.close), h(T(t.h)), dt(T(t.dt)) {}
     // particle i of n, at pos (rows of n), with the acceleration as stored
     __device__ __forceinline__ void apply(int n, int i, const T* pos, T ax, T ay, T az) const {
-        if (!v && !store) return;
+        if (!v) return;
         const size_t iy = (size_t)n + i, iz = 2 * (size_t)n + i;
-        T vx = T(0), vy = T(0), vz = T(0);
-        if (v) {  // the same FMAs as the kick-drift kernel's
-            vx = fmat(h, ax, v[i]);
-            vy = fmat(h, ay, v[iy]);
-            vz = fmat(h, az, v[iz]);
-        } else {
-            vx = store_v[i];
-            vy = store_v[iy];
-            vz = store_v[iz];
+        T vx = v[i], vy = v[iy], vz = v[iz];
+        if (close) {  // the same FMAs as the kick-drift kernel's
+            vx = fmat(h, ax, vx);
+            vy = fmat(h, ay, vy);
+            vz = fmat(h, az, vz);
         }
         if (store) {
             const size_t n3 = 3 * (size_t)n;
@@ -333,14 +335,13 @@ struct TailArgs {
             store[2 * n3 + iy] = ay;
             store[2 * n3 + iz] = az;
         }
-        if (!v) return;
         if (x) {
             vx = fmat(h, ax, vx);
             vy = fmat(h, ay, vy);
             vz = fmat(h, az, vz);
-            x[i] = fmat(dt, vx, x[i]);
-            x[iy] = fmat(dt, vy, x[iy]);
-            x[iz] = fmat(dt, vz, x[iz]);
+            x[i] = fmat(dt, vx, pos[i]);
+            x[iy] = fmat(dt, vy, pos[iy]);
+            x[iz] = fmat(dt, vz, pos[iz]);
         }
         v[i] = vx;
         v[iy] = vy;
@@ -592,8 +593,9 @@ hipError_t launch_adjoint_sym(int prec, const SymShape& sh, int64_t n, const voi
                               const WalkNext& next = WalkNext{}, bool* entered = nullptr);
 
 // O(N) leapfrog kernels over the 3n components of a pos array.
-hipError_t launch_kick_drift(int prec, int64_t n, void* x, void* v, const void* acc,
-                             double h, double dt, hipStream_t stream);
+// v <- v + h acc; xout <- x + dt v (xout may be x).
+hipError_t launch_kick_drift(int prec, int64_t n, const void* x, void* xout, void* v,
+                             const void* acc, double h, double dt, hipStream_t stream);
 // A checkpoint slot (3 x 3n elements) receives (x, v, acc).
 hipError_t launch_store(int prec, int64_t n, const void* x, const void* v, const void* acc,
                         void* slot, hipStream_t stream);

@@ -210,6 +210,84 @@ __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int
     finish_sink<Pol, POT, true>(a, i, s[0], s[1], s[2], POT ? s[N - 1] : 0.0);
 }
 
+// Sources on the lanes: a workgroup of LB lanes owns LS sinks and each lane
+// takes every LB-th source, straight from the SoA arrays (coalesced; the sinks
+// are the same for every lane), so that a thousand sinks make 256 workgroups of
+// a few pairs per lane; the lanes' sums meet in LDS, 16 lanes a sum, and the
+// workgroup finishes its sinks: one launch and no partials where the split
+// ranges take two (FP64, 1024 particles: 6.8 us of the pair kernel's latency
+// and 4.2 of the reduction's; 5.9 us a leapfrog step so). For the policies whose sums may be regrouped:
+// FP64, FP32 terms summed in FP64, plain FP32 (one FP32 sum per lane, the
+// lanes' sums added in FP64). The leapfrog's drift goes to another array,
+// since other workgroups still read the positions.
+constexpr int LB = 256, LS = 4;
+
+template <class Pol, bool POT>
+__global__ __launch_bounds__(LB) void force_lanes_kernel(ForceArgs<Pol> a) {
+    using calc_t = typename Pol::calc_t;
+    using sum_t = typename Pol::sum_t;
+    constexpr int N = POT ? 4 : 3, V = LS * N;
+    __shared__ double lsum[V][LB + 1];
+    __shared__ double tot[LS][N];
+    const int tid = threadIdx.x;
+    const int i0 = blockIdx.x * LS;
+    // the origin of the one-sided kernel's 256-sink workgroups
+    double ox = 0.0, oy = 0.0, oz = 0.0;
+    if constexpr (Pol::origin) {
+        __shared__ double org[LB / 64][3];
+        const int b0 = i0 / LB * LB, i = b0 + tid;
+        const bool ok = i < a.ni;
+        sink_block_origin<LB / 64>(ok ? a.xi[i] : 0.0, ok ? a.yi[i] : 0.0, ok ? a.zi[i] : 0.0,
+                                   min(a.ni - b0, LB), org, ox, oy, oz);
+    }
+    calc_t xi[LS], yi[LS], zi[LS];
+    sum_t s[LS][N];
+#pragma unroll
+    for (int k = 0; k < LS; ++k) {
+        const int i = min(i0 + k, a.ni - 1);
+        xi[k] = pair_coord<Pol>(a.xi[i], ox);
+        yi[k] = pair_coord<Pol>(a.yi[i], oy);
+        zi[k] = pair_coord<Pol>(a.zi[i], oz);
+#pragma unroll
+        for (int c = 0; c < N; ++c) s[k][c].init();
+    }
+#pragma unroll 2
+    for (int j = tid; j < a.nj; j += LB) {
+        const calc_t x = pair_coord<Pol>(a.xj[j], ox), y = pair_coord<Pol>(a.yj[j], oy),
+                     z = pair_coord<Pol>(a.zj[j], oz), m = calc_t(a.mj[j]);
+#pragma unroll
+        for (int k = 0; k < LS; ++k) {
+            const calc_t dx = x - xi[k], dy = y - yi[k], dz = z - zi[k];
+            const calc_t ss = fmat(dz, dz, fmat(dy, dy, fmat(dx, dx, a.eps2)));
+            const calc_t r = rsqrt_pair(ss);
+            calc_t w = r * (r * r);
+            w = w * m;
+            s[k][0].add_fma(dx, w);
+            s[k][1].add_fma(dy, w);
+            s[k][2].add_fma(dz, w);
+            if (POT) s[k][3].add_fma(m, r);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < LS; ++k)
+#pragma unroll
+        for (int c = 0; c < N; ++c) lsum[k * N + c][tid] = s[k][c].total();
+    __syncthreads();
+    const int v = tid >> 4, l = tid & 15;  // 16 lanes add sum v
+    if (v < V) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < LB / 16; ++q) t += lsum[v][q * 16 + l];
+#pragma unroll
+        for (int mask = 8; mask >= 1; mask >>= 1) t += __shfl_xor(t, mask, 64);
+        if (l == 0) tot[v / N][v % N] = t;
+    }
+    __syncthreads();
+    if (tid < LS && i0 + tid < a.ni)
+        finish_sink<Pol, POT, true>(a, i0 + tid, tot[tid][0], tot[tid][1], tot[tid][2],
+                                    POT ? tot[tid][N - 1] : 0.0);
+}
+
 // The leapfrog's tail after a pass in one range, whose workgroups finish their
 // own sinks while others still read the positions.
 template <class Pol>
@@ -271,6 +349,20 @@ hipError_t launch_any(const Shape& sh, ForceArgs<Pol> a, int nsplit, hipStream_t
 template <class Pol, bool ACC, bool POT>
 hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_only,
                      hipStream_t stream, bool* drifted = nullptr) {
+    if (sh.lanes) {
+        if constexpr (std::is_same<typename Pol::sum_t, SumKahan>::value ||
+                      std::is_same<typename Pol::sum_t, SumTile>::value ||
+                      std::is_same<Pol, PolMixAcc32>::value) {
+            return hipErrorInvalidValue;
+        } else {
+            if (a.tail.x == a.xi) a.tail.x = nullptr;
+            if (drifted) *drifted = a.tail.x != nullptr;
+            a.part = nullptr;
+            hipLaunchKernelGGL((force_lanes_kernel<Pol, POT>), dim3((a.ni + LS - 1) / LS), dim3(LB), 0,
+                               stream, a);
+            return hipGetLastError();
+        }
+    }
     const int span = split_span(a.nj, sh.split, sh.block);
     const int nsplit = split_ranges(a.nj, sh.split, sh.block);
     a.jspan = span;
@@ -278,7 +370,7 @@ hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_
     if (nsplit == 1 && !partials_only) {
         a.part = nullptr;
         const hipError_t e = launch_any<Pol, ACC, POT>(sh, a, 1, stream);
-        if (e != hipSuccess || (!a.tail.v && !a.tail.store)) return e;
+        if (e != hipSuccess || !a.tail.v) return e;
         hipLaunchKernelGGL(force_tail_kernel<Pol>, dim3((a.ni + 255) / 256), dim3(256), 0, stream, a);
         return hipGetLastError();
     }
@@ -300,6 +392,7 @@ bool shape_supported(const Shape& s) {
 }
 
 size_t force_partials_bytes(const Shape& s, int64_t ni) {
+    if (s.lanes) return 0;
     return (size_t)s.split * NQ * (size_t)ni * sizeof(double);
 }
 
@@ -322,7 +415,25 @@ size_t force_partials_bound(int64_t n) {
     return (size_t)rows * NQ * sizeof(double);
 }
 
-Shape choose_force_shape(int prec, int64_t ni, int64_t nj, bool least) {
+Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
+    // Sources on the lanes (force_lanes_kernel), for the policies whose sums
+    // may be regrouped, as long as a lane has few sources: us per leapfrog
+    // step against the split ranges below, measured on MI355X,
+    //            1024        4001         8000         12000
+    //   FP64     5.9, 10.0   17.4, 24.2   49.5, 58.0   104.8, 112.2
+    //   FP32     5.4, 13.2   10.1, 14.6   24.2, 29.7   47.4, 60.6
+    //   acc64    6.6, 16.7   17.7, 18.7   44.4, 41.7   88.2, 86.4
+    // so up to 6000 sources for FP64 sums of FP32 terms, whose lanes carry
+    // the longest chain, and for few FP64 sinks, where a lane's sources are
+    // the whole time (100 against 12000: 15.3, 14.3; 1000: 16.4, 19.7).
+    // Larger sets on themselves have the symmetric pass in FP64 and FP32.
+    const bool regroup = prec == NB_F64 || prec == NB_F32 || prec == NB_MIX_ACC64;
+    const int64_t most = prec == NB_MIX_ACC64 || (prec == NB_F64 && ni < 512) ? 6000 : 12287;
+    if (pick == Pick::Best && regroup && ni <= 12287 && nj <= most) {
+        Shape s{LS, LB, LB};
+        s.lanes = true;
+        return s;
+    }
     // Measured on MI355X (launch-shape sweeps at N = 2^10 .. 2^20):
     //  * FP32 pair arithmetic: 1 sink per lane in 256-lane workgroups up to
     //    12288 sinks, then 2 sinks per lane, 128-lane workgroups, and
@@ -363,7 +474,7 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, bool least) {
     // arithmetic. With both changes of the reduction and the ranges a pass
     // takes 13.7 us instead of 21.9 at 1000 particles, 20.3 instead of 23.8
     // at 5003 and 49.5 instead of 52.6 at 10000.
-    if (!least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN) {
+    if (pick != Pick::Least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN) {
         split = std::max<int64_t>(split_ranges(nj, split, s.block),
                                   short_tile_ranges(nj, s.block, waves));
     }

@@ -17,16 +17,16 @@ inline dim3 grid_for(int64_t count) {
     return dim3((unsigned)blocks);
 }
 
-// v <- v + h a; x <- x + dt v
+// v <- v + h a; xout <- x + dt v (xout may be x)
 template <typename T>
-__global__ __launch_bounds__(TPB) void kick_drift_kernel(T* __restrict__ x, T* __restrict__ v,
+__global__ __launch_bounds__(TPB) void kick_drift_kernel(const T* x, T* xout, T* __restrict__ v,
                                                          const T* __restrict__ a, T h, T dt,
                                                          int64_t count) {
     for (int64_t k = blockIdx.x * (int64_t)TPB + threadIdx.x; k < count;
          k += (int64_t)gridDim.x * TPB) {
         const T vh = fmat(h, a[k], v[k]);  // the same FMAs as the force epilogue's
         v[k] = vh;
-        x[k] = fmat(dt, vh, x[k]);
+        xout[k] = fmat(dt, vh, x[k]);
     }
 }
 
@@ -81,17 +81,18 @@ __global__ __launch_bounds__(TPB) void reload_kernel(T* __restrict__ x, T* __res
 
 }  // namespace
 
-hipError_t launch_kick_drift(int prec, int64_t n, void* x, void* v, const void* acc, double h,
-                             double dt, hipStream_t stream) {
+hipError_t launch_kick_drift(int prec, int64_t n, const void* x, void* xout, void* v,
+                             const void* acc, double h, double dt, hipStream_t stream) {
     const int64_t c = 3 * n;
     if (prec == NB_F32)
         hipLaunchKernelGGL(kick_drift_kernel<float>, grid_for(c), dim3(TPB), 0, stream,
-                           static_cast<float*>(x), static_cast<float*>(v),
-                           static_cast<const float*>(acc), float(h), float(dt), c);
+                           static_cast<const float*>(x), static_cast<float*>(xout),
+                           static_cast<float*>(v), static_cast<const float*>(acc), float(h),
+                           float(dt), c);
     else
         hipLaunchKernelGGL(kick_drift_kernel<double>, grid_for(c), dim3(TPB), 0, stream,
-                           static_cast<double*>(x), static_cast<double*>(v),
-                           static_cast<const double*>(acc), h, dt, c);
+                           static_cast<const double*>(x), static_cast<double*>(xout),
+                           static_cast<double*>(v), static_cast<const double*>(acc), h, dt, c);
     return hipGetLastError();
 }
 

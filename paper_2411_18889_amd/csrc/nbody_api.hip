@@ -121,6 +121,12 @@ size_t accel_ws(const Shape& s, int64_t ni) {
     return s.split > 1 ? force_partials_bytes(s, ni) : 0;
 }
 
+// What a one-sided pass of n particles on themselves asks for.
+size_t onesided_ws(int prec, int64_t n) {
+    return std::max(accel_ws(choose_force_shape(prec, n, n), n),
+                    accel_ws(choose_force_shape(prec, n, n, Pick::Least), n));
+}
+
 // ---- instantiated leapfrog graphs (nbody_step with NB_GRAPH) ---------------
 // A graph is recorded on a library-owned capture stream of the device (so the
 // caller's stream may be the null stream), instantiated once per distinct
@@ -234,8 +240,8 @@ int sym_from_launch(const nb_launch& l, SymShape lib, SymShape* out) {
 int resolve_accel(int prec, int64_t ni, int64_t nj, bool self_set, bool pot,
                   const nb_launch* launch, SymShape* sym, Shape* sh, Shape* least) {
     *sym = (self_set && !launch) ? choose_sym_shape(prec, ni, pot) : SymShape{0, 0};
-    *sh = choose_force_shape(prec, ni, nj);
-    *least = choose_force_shape(prec, ni, nj, true);
+    *sh = choose_force_shape(prec, ni, nj, launch ? Pick::Split : Pick::Best);
+    *least = choose_force_shape(prec, ni, nj, Pick::Least);
     if (!launch) return NB_OK;
     if (launch->symmetric) {
         if (!self_set) return NB_EUNSUPPORTED;
@@ -315,8 +321,10 @@ int accel_plan(int64_t ni, const void* xi, int64_t nj, const void* xj, const voi
         plan->need = sym_min_bytes(L);
         plan->full = sym_full_bytes(L);
     } else {
-        plan->need = std::min(accel_ws(plan->least, ni), accel_ws(sh, ni));
-        plan->full = accel_ws(sh, ni);
+        // (the kernel that keeps its sums on the lanes uses no scratch, but a
+        // call needs what the other kernel would)
+        plan->need = accel_ws(plan->least, ni);
+        plan->full = std::max(plan->need, accel_ws(sh, ni));
     }
     return NB_OK;
 }
@@ -416,12 +424,12 @@ int nbody_step(int64_t n, void* x, void* v, const void* m, void* acc, double eps
                          overlaps(ws, bytes, m, (size_t)n * ms) || overlaps(ws, bytes, acc, vb) ||
                          (ckpt && overlaps(ws, bytes, ckpt, (size_t)(nsteps / ckpt_every + 1) * 3 * vb)));
     };
+    const Shape least = choose_force_shape(prec, n, n, Pick::Least);
     Shape sh = choose_force_shape(prec, n, n);
-    if (usable_ws(ws, ws_bytes) < accel_ws(sh, n) || ws_overlaps(accel_ws(sh, n)))
-        sh = choose_force_shape(prec, n, n, true);
+    if (usable_ws(ws, ws_bytes) < accel_ws(sh, n) || ws_overlaps(accel_ws(sh, n))) sh = least;
     const SymShape sym = choose_sym_shape(prec, n);
     const SymLayout L = sym.waves ? sym_layout(prec, sym, n) : SymLayout{};
-    const size_t need = sym.waves ? sym_min_bytes(L) : accel_ws(sh, n);
+    const size_t need = sym.waves ? sym_min_bytes(L) : accel_ws(sh.lanes ? least : sh, n);
     int st = check_ws(ws, ws_bytes, need);
     if (st != NB_OK) return st;
     const size_t used = sym.waves ? std::min(ws_bytes, sym_full_bytes(L)) : need;
@@ -440,33 +448,49 @@ int nbody_step(int64_t n, void* x, void* v, const void* m, void* acc, double eps
         auto slot_at = [&](int64_t slot) -> void* {
             return static_cast<char*>(ckpt) + (size_t)slot * 3 * vb;
         };
+        //
+        // The kernel with its sources on the lanes cannot drift in place, so
+        // there the positions alternate between x and the workspace (`other`,
+        // where it has room), every pass reading one and drifting into the
+        // other, such that the last drift ends in x.
+        const bool lanes = !sym.waves && sh.lanes;
+        void* const other = lanes && used >= vb ? ws : nullptr;
+        void* pos = x;
         auto force = [&](bool kick, void* slot, bool drift, bool* drifted) {
             return timed(NB_PROF_FORCE, q, [&] {
                 StepTail t;
-                t.v = kick ? v : nullptr;
+                t.v = kick || slot || drift ? v : nullptr;
+                t.close = kick;
                 t.h = h;
                 t.store = slot;
-                t.store_v = v;
-                t.drift_x = drift ? x : nullptr;
+                void* const to = !lanes ? x : (pos == x ? other : x);
+                t.drift_x = drift ? to : nullptr;
                 t.dt = dt;
                 if (sym.waves)
-                    return launch_force_sym(prec, sym, n, x, m, eps, G, acc, ws, used, q, nullptr, t,
+                    return launch_force_sym(prec, sym, n, pos, m, eps, G, acc, ws, used, q, nullptr, t,
                                             drifted);
-                return launch_force(prec, sh, n, x, n, x, m, eps, G, true, acc, nullptr, ws, q, t,
-                                    drifted);
+                const hipError_t r = launch_force(prec, sh, n, pos, n, pos, m, eps, G, true, acc,
+                                                  nullptr, ws, q, t, drifted);
+                if (*drifted) pos = to;
+                return r;
             });
         };
         hipError_t e = hipSuccess;
-        if (!(flags & NB_ACC_VALID))
-            e = force(false, ckpt ? slot_at(0) : nullptr, false, nullptr);
-        else if (ckpt)
-            e = timed(NB_PROF_COPY, q, [&] { return launch_store(prec, n, x, v, acc, slot_at(0), q); });
         // a step's kick and drift run in the previous force pass's finishing
         // kernel unless that pass ended the call
         bool drifted = false;
+        if (!(flags & NB_ACC_VALID))
+            e = force(false, ckpt ? slot_at(0) : nullptr, other && nsteps > 0 && nsteps % 2 == 0, &drifted);
+        else if (ckpt)
+            e = timed(NB_PROF_COPY, q, [&] { return launch_store(prec, n, x, v, acc, slot_at(0), q); });
         for (int64_t k = 0; k < nsteps && e == hipSuccess; ++k) {
             if (!drifted)
-                e = timed(NB_PROF_UPDATE, q, [&] { return launch_kick_drift(prec, n, x, v, acc, h, dt, q); });
+                e = timed(NB_PROF_UPDATE, q, [&] {
+                    void* const to = other && (nsteps - 1 - k) % 2 ? other : x;
+                    const hipError_t r = launch_kick_drift(prec, n, pos, to, v, acc, h, dt, q);
+                    pos = to;
+                    return r;
+                });
             const bool stored = ckpt && (k + 1) % ckpt_every == 0;
             drifted = false;
             if (e == hipSuccess)
@@ -700,14 +724,14 @@ size_t nbody_pass_workspace_size(int op, int64_t ni, int64_t nj, int prec, int s
     if (resolve_accel(prec, ni, nj, self_set != 0, potential != 0, launch, &sym, &sh, &least) != NB_OK)
         return 0;
     if (sym.waves) return sym_default_bytes(sym_layout(prec, sym, ni, potential != 0));
-    return accel_ws(sh, ni);
+    return std::max(accel_ws(sh, ni), accel_ws(least, ni));
 }
 
 size_t nbody_workspace_size(int op, int64_t n, int prec) {
     if (!valid_prec(prec) || n < 1 || n > kMaxN) return 0;
     switch (op) {
     case NB_OP_ACCEL: {  // any ni, nj <= n; either pass, with or without the potential
-        const size_t a = std::max(accel_ws(choose_force_shape(prec, n, n), n), force_partials_bound(n));
+        const size_t a = std::max(onesided_ws(prec, n), force_partials_bound(n));
         const SymShape s0 = choose_sym_shape(prec, n), s1 = choose_sym_shape(prec, n, true);
         const size_t b = s0.waves ? sym_default_bytes(sym_layout(prec, s0, n)) : 0;
         const size_t c = s1.waves ? sym_default_bytes(sym_layout(prec, s1, n, true)) : 0;
@@ -716,7 +740,7 @@ size_t nbody_workspace_size(int op, int64_t n, int prec) {
     case NB_OP_STEP: {
         const SymShape sym = choose_sym_shape(prec, n);
         return sym.waves ? sym_default_bytes(sym_layout(prec, sym, n))
-                         : accel_ws(choose_force_shape(prec, n, n), n);
+                         : onesided_ws(prec, n);
     }
     case NB_OP_ADJOINT: {
         const SymShape sym = choose_adjoint_sym_shape(prec, n);

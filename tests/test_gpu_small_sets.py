@@ -107,3 +107,45 @@ def test_checkpoints_are_the_states(prec, n, every):
     assert torch.equal(torch.cat([t.reshape(-1) for t in out[0][:3]]), states[0])
     for p, q in zip(*out):
         assert torch.equal(p, q)
+
+
+@pytest.mark.parametrize("prec,n", [("f64", 700), ("f64", 5001), ("f32", 1025), ("mix_acc64", 2050),
+                                    ("mix_tilec", 700)])
+@pytest.mark.parametrize("S", (0, 1, 2, 5, 6))
+def test_steps_compose(prec, n, S):
+    """One call of S steps ends bitwise where S calls of one step do, from a
+    valid acceleration or not, replayed as a graph, and with the least
+    workspace the call accepts (where the positions have no second array to
+    alternate with)."""
+    eps, dt = 2.0 ** -6, 2.0 ** -7
+    x, v, m = plummer_sphere(n, 78)
+    ref = list(to_dev(x, v, m, prec))
+    md = ref.pop()
+    ref.append(torch.empty_like(ref[0]))
+    nb.step(*ref[:2], md, ref[2], eps, dt, 0, prec=prec)
+    a0 = ref[2].clone()
+    for _ in range(S):
+        nb.step(*ref[:2], md, ref[2], eps, dt, 1, prec=prec, acc_valid=True)
+    need = nb.workspace_size(1, n, prec)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    for valid in (False, True):
+        for graph in (False, True, True):
+            st = list(to_dev(x, v, m, prec))[:2] + [a0.clone()]
+            g = [t.clone() for t in st]
+            nb.step(*g[:2], md, g[2], eps, dt, S, prec=prec, acc_valid=valid, graph=graph, workspace=ws)
+            for p, q in zip(g, ref):
+                assert torch.equal(p, q)
+    nb.graph_cache_clear()
+
+
+def test_unsplit_set_without_workspace():
+    """A set of one tile needs no workspace: none is given, and a leapfrog of
+    the kernel that cannot drift in place runs its drifts apart."""
+    n, eps, dt, S = 60, 2.0 ** -6, 2.0 ** -7, 5
+    assert nb.workspace_size(1, n, "f64") == 0
+    x, v, m = plummer_sphere(n, 79)
+    xd, vd, md = to_dev(x, v, m, "f64")
+    acc = torch.empty_like(xd)
+    nb.step(xd, vd, md, acc, eps, dt, S, prec="f64")
+    xo, vo, ao = oracle.kdk(x, v, m, eps, dt, S)
+    assert max(rel(host(xd), xo), rel(host(vd), vo), rel(host(acc), ao)) <= 1e-12
