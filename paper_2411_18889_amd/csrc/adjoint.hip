@@ -224,11 +224,19 @@ __global__ __launch_bounds__(256) void adjoint_reduce_kernel(AdjArgs<Pol> a, int
     const int i = blockIdx.x * 64 + lane;
     double t[NQ] = {0, 0, 0, 0, 0, 0, 0};
     if (i < a.n) {
-#pragma unroll 4
-        for (int sp = g; sp < nsplit; sp += 4) {
-            const double* q = a.part + (size_t)sp * NQ * a.n + i;
+        for (int r0 = g; r0 < nsplit; r0 += 4 * 4) {  // four ranges' loads in flight
+            double p[4][NQ];
 #pragma unroll
-            for (int c = Q0; c < NQ; ++c) t[c] += q[(size_t)c * a.n];
+            for (int u = 0; u < 4; ++u) {
+                const int r = r0 + 4 * u;
+                const double* q = a.part + (size_t)r * NQ * a.n + i;
+#pragma unroll
+                for (int c = Q0; c < NQ; ++c) p[u][c] = r < nsplit ? q[(size_t)c * a.n] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int c = Q0; c < NQ; ++c) t[c] += p[u][c];
         }
     }
     if (g)
@@ -297,7 +305,7 @@ Shape choose_adjoint_shape(int prec, int64_t n, bool least) {
     // instead of 96.5 at 10000
     if (!least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN)
         split = std::max<int64_t>(split_ranges(n, split, s.block),
-                                  short_tile_ranges(n, s.block, waves));
+                                  short_tile_ranges(n, s.block, waves, 8192));
     s.split = (int)split;
     return s;
 }

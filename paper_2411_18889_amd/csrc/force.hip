@@ -76,7 +76,9 @@ __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, doub
 }
 
 // FEW: built for few waves in flight (kFewWaves): 5003 particles, tile-
-// compensated, 20.2 -> 18.9 us a pass, 10000 49.3 -> 47.5.
+// compensated, 20.2 -> 18.9 us a pass, 10000 49.3 -> 47.5. Not with the
+// potential, whose kernel that build makes slower (9558 particles 46 -> 52 us,
+// 128 sinks of 205175 sources 62 -> 89).
 template <class Pol, int BS, int K, bool ACC, bool POT, bool FEW>
 __global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void force_kernel(ForceArgs<Pol> a) {
     using calc_t = typename Pol::calc_t;
@@ -178,35 +180,47 @@ __global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void force_kernel(ForceArg
 }
 
 // Adds the nsplit partial sums of every sink in a fixed order, then finishes:
-// wave g of a workgroup adds ranges g, g + 4, ... of 64 sinks (four ranges'
-// loads in flight together), and the first wave the four sums in wave order.
-// At small ni the kernel is one load latency after another, so four waves
-// share them.
-template <class Pol, bool POT>
+// wave g of a group of W adds ranges g, g + W, ... of 64 sinks (eight ranges'
+// loads in flight together), and the first wave the W sums in wave order. At
+// small ni the kernel is one load latency after another, so four waves share
+// them; from 16384 sinks one wave is as fast.
+template <class Pol, bool POT, int W>
 __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int nsplit) {
     constexpr int N = POT ? 4 : 3;
-    __shared__ double other[3][N][64];
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + lane;
+    __shared__ double other[W > 1 ? W - 1 : 1][N][64];
+    const int lane = threadIdx.x & 63;
+    const int g = W > 1 ? threadIdx.x >> 6 : 0;
+    const int i = W > 1 ? blockIdx.x * 64 + lane : blockIdx.x * 256 + threadIdx.x;
     const size_t stride = (size_t)NQ * a.ni;
     double s[N] = {};
     if (i < a.ni) {
-#pragma unroll 4
-        for (int r = g; r < nsplit; r += 4) {
-            const double* q = a.part + r * stride + i;
+        for (int r0 = g; r0 < nsplit; r0 += W * 8) {
+            double t[8][N];
 #pragma unroll
-            for (int c = 0; c < N; ++c) s[c] += q[(size_t)c * a.ni];
+            for (int u = 0; u < 8; ++u) {
+                const int r = r0 + W * u;
+                const double* q = a.part + r * stride + i;
+#pragma unroll
+                for (int c = 0; c < N; ++c) t[u][c] = r < nsplit ? q[(size_t)c * a.ni] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int c = 0; c < N; ++c) s[c] += t[u][c];
         }
     }
-    if (g)
+    if constexpr (W > 1) {
+        if (g)
 #pragma unroll
-        for (int c = 0; c < N; ++c) other[g - 1][c][lane] = s[c];
-    __syncthreads();
-    if (g || i >= a.ni) return;
+            for (int c = 0; c < N; ++c) other[g - 1][c][lane] = s[c];
+        __syncthreads();
+        if (g) return;
 #pragma unroll
-    for (int v = 0; v < 3; ++v)
+        for (int v = 0; v < W - 1; ++v)
 #pragma unroll
-        for (int c = 0; c < N; ++c) s[c] += other[v][c][lane];
+            for (int c = 0; c < N; ++c) s[c] += other[v][c][lane];
+    }
+    if (i >= a.ni) return;
     finish_sink<Pol, POT, true>(a, i, s[0], s[1], s[2], POT ? s[N - 1] : 0.0);
 }
 
@@ -323,7 +337,7 @@ ForceArgs<Pol> make_args(int64_t ni, const void* xi, int64_t nj, const void* xj,
 template <class Pol, bool ACC, bool POT, int BS, int K>
 hipError_t launch_shape(ForceArgs<Pol> a, int nsplit, hipStream_t stream) {
     dim3 grid((a.ni + BS * K - 1) / (BS * K), nsplit);
-    if constexpr (K == 1 && std::is_same<typename Pol::calc_t, float>::value) {
+    if constexpr (K == 1 && !POT && std::is_same<typename Pol::calc_t, float>::value) {
         if ((int64_t)grid.x * nsplit * (BS / 64) < 2 * kFewWaves) {
             hipLaunchKernelGGL((force_kernel<Pol, BS, K, ACC, POT, true>), grid, dim3(BS), 0, stream, a);
             return hipGetLastError();
@@ -377,8 +391,12 @@ hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_
     a.part = static_cast<double*>(ws);
     hipError_t e = launch_any<Pol, ACC, POT>(sh, a, nsplit, stream);
     if (e != hipSuccess || partials_only) return e;
-    hipLaunchKernelGGL((force_reduce_kernel<Pol, POT>), dim3((a.ni + 63) / 64), dim3(256), 0,
-                       stream, a, nsplit);
+    if (a.ni < 16384)
+        hipLaunchKernelGGL((force_reduce_kernel<Pol, POT, 4>), dim3((a.ni + 63) / 64), dim3(256), 0,
+                           stream, a, nsplit);
+    else
+        hipLaunchKernelGGL((force_reduce_kernel<Pol, POT, 1>), dim3((a.ni + 255) / 256), dim3(256), 0,
+                           stream, a, nsplit);
     return hipGetLastError();
 }
 
@@ -466,17 +484,18 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     if (split > max_ranges) split = max_ranges;
     if (split > 256) split = 256;
     if (split < 1) split = 1;
-    // Ranges as short as one tile, whatever nj, until there are 8192 waves (8
-    // per SIMD): with fewer, the pass takes as long as one range does (the
+    // Ranges as short as one tile, whatever nj, until there are 6 waves per
+    // SIMD: with fewer, the pass takes as long as one range does (the
     // rule above rounds 5003 sources in 19 ranges up to 10 ranges of two
     // tiles on 800 waves). Not for the policies that keep a plain or
     // compensated FP32 sum over the range: its length is part of their
     // arithmetic. With both changes of the reduction and the ranges a pass
-    // takes 13.7 us instead of 21.9 at 1000 particles, 20.3 instead of 23.8
-    // at 5003 and 49.5 instead of 52.6 at 10000.
+    // takes 13.7 us instead of 21.9 at 1000 particles and 20.3 instead of
+    // 23.8 at 5003 (at 11239 with the potential, 44 ranges of one tile are
+    // 2 % slower than 22 of two).
     if (pick != Pick::Least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN) {
         split = std::max<int64_t>(split_ranges(nj, split, s.block),
-                                  short_tile_ranges(nj, s.block, waves));
+                                  short_tile_ranges(nj, s.block, waves, 6144));
     }
     s.split = (int)split;
     return s;
