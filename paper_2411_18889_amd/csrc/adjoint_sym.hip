@@ -42,9 +42,7 @@ struct ASymFinishArgs {
     int n, nb;
     double G, c, h;
     int update_state;
-    pos_t *ax, *ay, *az;
-    pos_t *vx, *vy, *vz;
-    pos_t *gx, *gy, *gz;
+    pos_t *ax, *vx, *gx;  // acc, v, lam_x: 3n each
     double* gm;
     WalkArgs<pos_t> next;  // next.x == nullptr: nothing
 };
@@ -52,61 +50,56 @@ struct ASymFinishArgs {
 // Slot-ordered FP64 sum of the partials, then the reverse-walk epilogue:
 //   lam_x += c G J^T lam;  lam_m += c (-G) G^T-sum;
 //   if update_state (F): acc = G a_sum; v <- v - h acc.
+// A thread does one component (blockIdx.y; 3: the mass adjoint) of a particle,
+// as the force pass's fold.
 template <class Pol, bool F>
-__global__ __launch_bounds__(256) void adjoint_sym_finish_kernel(ASymFinishArgs<Pol> a) {
+__global__ __launch_bounds__(kFoldLanes) void adjoint_sym_finish_kernel(ASymFinishArgs<Pol> a) {
     using pos_t = typename Pol::pos_t;
-    constexpr int Q0 = QRange<F>::lo, NQF = QRange<F>::n;
     const SymBandView& b = a.band;
-    const int i = b.base + blockIdx.x * 256 + threadIdx.x;
+    const int c = blockIdx.y;
+    const int i = b.base + blockIdx.x * kFoldLanes + threadIdx.x;
     if (i >= a.n) return;
-    double q[NQ] = {0, 0, 0, 0, 0, 0, 0};
-    if (!a.first) {
+    // rows of the partials: the component's J^T lam (or the mass adjoint)
+    // and, with F, its force
+    // (for the mass adjoint the second is the first again, and unused)
+    constexpr int NR = F ? 2 : 1;
+    using part_t = typename Pol::calc_t;
+    int row[NR];
+    row[0] = c + (F ? 3 : 0);
+    if (F) row[NR - 1] = c < 3 ? c : row[0];
+    double sum[NR];
+    const part_t* p[NR];
 #pragma unroll
-        for (int c = Q0; c < NQ; ++c) q[c] = a.run[(size_t)(c - Q0) * a.n + i];
+    for (int r = 0; r < NR; ++r) {
+        sum[r] = a.first ? 0.0 : a.run[(size_t)row[r] * a.n + i];
+        p[r] = a.part + b.offset(b.I0, row[r], i);
     }
-    // slots I0 .. I1-1 (region A): eight slots' loads in flight together,
-    // the adds in slot order
-#pragma unroll 8
-    for (int k = b.I0; k < b.I1; ++k) {
-#pragma unroll
-        for (int c = Q0; c < NQ; ++c) q[c] += double(a.part[b.offset(k, c - Q0, i)]);
-    }
+    // slots I0 .. I1-1 (region A)
+    add_slots<NR, kFoldSlots>(sum, p, (size_t)b.nq * b.np, b.I1 - b.I0);
     if (i >= b.base + b.nbp) {  // a later band adds this particle's next slots
 #pragma unroll
-        for (int c = Q0; c < NQ; ++c) a.run[(size_t)(c - Q0) * a.n + i] = q[c];
+        for (int r = 0; r < NR; ++r) a.run[(size_t)row[r] * a.n + i] = sum[r];
         return;
     }
     // the band's own particles: slots I1 .. nb-1 (region B), then finish
-#pragma unroll 8
-    for (int k = b.I1; k < a.nb; ++k) {
 #pragma unroll
-        for (int c = Q0; c < NQ; ++c) q[c] += double(a.part[b.offset(k, c - Q0, i)]);
+    for (int r = 0; r < NR; ++r) p[r] = a.part + b.offset(b.I1, row[r], i);
+    add_slots<NR, kFoldSlots>(sum, p, (size_t)b.nq * b.nbp, a.nb - b.I1);
+    const double s = sum[0], fs = sum[NR - 1];
+    const double G = a.G;
+    if (c == 3) {
+        a.gm[i] = a.gm[i] + a.c * (-G * s);
+        return;
     }
-    const double G = a.G, c = a.c;
-    const pos_t gx = pos_t(double(a.gx[i]) + c * (G * q[3]));
-    const pos_t gy = pos_t(double(a.gy[i]) + c * (G * q[4]));
-    const pos_t gz = pos_t(double(a.gz[i]) + c * (G * q[5]));
-    a.gx[i] = gx;
-    a.gy[i] = gy;
-    a.gz[i] = gz;
-    a.gm[i] = a.gm[i] + c * (-G * q[6]);
+    const size_t k = (size_t)c * a.n + i;
+    const pos_t g = pos_t(double(a.gx[k]) + a.c * (G * s));
+    a.gx[k] = g;
     if (F) {
-        const pos_t ax = pos_t(G * q[0]), ay = pos_t(G * q[1]), az = pos_t(G * q[2]);
-        const pos_t h = pos_t(a.h);
-        a.ax[i] = ax;
-        a.ay[i] = ay;
-        a.az[i] = az;
-        a.vx[i] = fmat(-h, ax, a.vx[i]);
-        a.vy[i] = fmat(-h, ay, a.vy[i]);
-        a.vz[i] = fmat(-h, az, a.vz[i]);
+        const pos_t acc = pos_t(G * fs);
+        a.ax[k] = acc;
+        a.vx[k] = fmat(-pos_t(a.h), acc, a.vx[k]);
     }
-    if (a.next.x) {
-        const size_t n = a.n, n3 = 3 * n;
-        const pos_t h = pos_t(a.h);
-        a.next.apply(i, n3, h, gx, a.vx, a.ax);
-        a.next.apply(n + i, n3, h, gy, a.vx, a.ax);
-        a.next.apply(2 * n + i, n3, h, gz, a.vx, a.ax);
-    }
+    if (a.next.x) a.next.apply(k, 3 * (size_t)a.n, pos_t(a.h), g, a.vx, a.ax);
 }
 
 }  // namespace
@@ -213,7 +206,8 @@ hipError_t launch_adjoint_sym_pol(int prec, const SymShape& sh, int64_t n, const
     // the layout of this pass: seven partial rows with the force sums, four
     // without (the workspace is sized for seven)
     const SymLayout L = adjoint_sym_layout(prec, sh, n, update_state);
-    const SymPlan plan = sym_plan(L, ws_bytes, sh.waves * 64);
+    const int nt = asym::item_threads(sh);
+    const SymPlan plan = sym_plan(L, ws_bytes, nt);
     if (!plan.valid) return hipErrorInvalidValue;
     double* run = plan.one ? nullptr : static_cast<double*>(ws);
     calc_t* parts = reinterpret_cast<calc_t*>(static_cast<char*>(ws) + plan.parts);
@@ -242,9 +236,9 @@ hipError_t launch_adjoint_sym_pol(int prec, const SymShape& sh, int64_t n, const
     pos_t* pa = static_cast<pos_t*>(acc);
     pos_t* pv = static_cast<pos_t*>(v);
     pos_t* pg = static_cast<pos_t*>(lam_x);
-    f.ax = pa; f.ay = pa + n; f.az = pa + 2 * n;
-    f.vx = pv; f.vy = pv + n; f.vz = pv + 2 * n;
-    f.gx = pg; f.gy = pg + n; f.gz = pg + 2 * n;
+    f.ax = pa;
+    f.vx = pv;
+    f.gx = pg;
     f.gm = lam_m;
     // each fold finishes particles after every read of their x and lam_v
     f.next = WalkArgs<pos_t>(next, lam_v);
@@ -252,17 +246,17 @@ hipError_t launch_adjoint_sym_pol(int prec, const SymShape& sh, int64_t n, const
     f.part = parts;
     f.nb = L.nb;
     for (int I0 = 0; I0 < L.nb;) {
-        const int I1 = sym_band_end(L, I0, budget, sh.waves * 64);
+        const int I1 = sym_band_end(L, I0, budget, nt);
         a.band = f.band = sym_band_view(L, I0, I1);
         hipError_t e = update_state ? launch_pairs_shape<Pol, true>(sh, a, stream)
                                     : launch_pairs_shape<Pol, false>(sh, a, stream);
         if (e != hipSuccess) return e;
         f.first = I0 == 0;
-        const dim3 fg((unsigned)((a.band.np + 255) / 256));
+        const dim3 fg((unsigned)((a.band.np + kFoldLanes - 1) / kFoldLanes), 4);
         if (update_state)
-            hipLaunchKernelGGL((adjoint_sym_finish_kernel<Pol, true>), fg, dim3(256), 0, stream, f);
+            hipLaunchKernelGGL((adjoint_sym_finish_kernel<Pol, true>), fg, dim3(kFoldLanes), 0, stream, f);
         else
-            hipLaunchKernelGGL((adjoint_sym_finish_kernel<Pol, false>), fg, dim3(256), 0, stream, f);
+            hipLaunchKernelGGL((adjoint_sym_finish_kernel<Pol, false>), fg, dim3(kFoldLanes), 0, stream, f);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         I0 = I1;
     }

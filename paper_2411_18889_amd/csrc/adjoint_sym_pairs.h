@@ -37,6 +37,59 @@ template <bool F> struct QRange {
     static constexpr int n = NQ - lo;     // partial rows per block
 };
 
+// One pair: sink values against the source record (q, lj), the sink's sums s
+// and, with JSIDE, the source's c (quantities QRange<F>::lo ..).
+template <bool JSIDE, bool F, class Sum, class C, class V4>
+__device__ __forceinline__ void asym_pair(const V4& q, const V4& lj, C xi, C yi, C zi, C mi, C mi3,
+                                          C lxi, C lyi, C lzi, Sum* s, C* c, C eps2) {
+    const C dx = q.x - xi;
+    const C dy = q.y - yi;
+    const C dz = q.z - zi;
+    const C ss = fmat(dz, dz, fmat(dy, dy, fmat(dx, dx, eps2)));
+    const C r = rsqrt_pair(ss);
+    const C r2 = r * r;
+    const C r3 = r2 * r;
+    if (F) {
+        const C wj = r3 * q.w;
+        s[0].add_fma(dx, wj);
+        s[1].add_fma(dy, wj);
+        s[2].add_fma(dz, wj);
+    }
+    const C ux = fmat(mi, lj.x, -(q.w * lxi));
+    const C uy = fmat(mi, lj.y, -(q.w * lyi));
+    const C uz = fmat(mi, lj.z, -(q.w * lzi));
+    const C dl = fmat(dz, lj.z, fmat(dy, lj.y, dx * lj.x));  // d . lam_j
+    C e, dli = C(0);
+    if (JSIDE) {
+        // -3 d . u = (-3 m_i)(d . lam_j) - (-3 m_j)(d . lam_i): both dots are
+        // needed anyway, and the factors -3 m come with the sink and the
+        // source record
+        dli = fmat(dz, lzi, fmat(dy, lyi, dx * lxi));
+        e = r2 * fmat(mi3, dl, -(lj.w * dli));
+    } else {
+        e = (C(-3) * r2) * fmat(dz, uz, fmat(dy, uy, dx * ux));
+    }
+    const C tx = fmat(e, dx, ux);
+    const C ty = fmat(e, dy, uy);
+    const C tz = fmat(e, dz, uz);
+    s[3].add_fma(r3, tx);
+    s[4].add_fma(r3, ty);
+    s[5].add_fma(r3, tz);
+    s[6].add_fma(r3, dl);
+    if (JSIDE) {
+        if (F) {
+            const C wi = r3 * mi;
+            c[0] = fmat(dx, wi, c[0]);
+            c[1] = fmat(dy, wi, c[1]);
+            c[2] = fmat(dz, wi, c[2]);
+        }
+        c[3] = fmat(r3, tx, c[3]);
+        c[4] = fmat(r3, ty, c[4]);
+        c[5] = fmat(r3, tz, c[5]);
+        c[6] = fmat(r3, dli, c[6]);
+    }
+}
+
 template <int K, bool JSIDE, bool F, class Sum, class C, class V4>
 __device__ __forceinline__ void asym_tile(const V4 (*rp)[128], const V4 (*rl)[128], C* jq,
                                           const C* xi, const C* yi, const C* zi, const C* mi,
@@ -62,54 +115,9 @@ __device__ __forceinline__ void asym_tile(const V4 (*rp)[128], const V4 (*rl)[12
             const V4 q = rowp[t];
             const V4 lj = rowl[t];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const C dx = q.x - xi[k];
-                const C dy = q.y - yi[k];
-                const C dz = q.z - zi[k];
-                const C ss = fmat(dz, dz, fmat(dy, dy, fmat(dx, dx, eps2)));
-                const C r = rsqrt_pair(ss);
-                const C r2 = r * r;
-                const C r3 = r2 * r;
-                if (F) {
-                    const C wj = r3 * q.w;
-                    s[k][0].add_fma(dx, wj);
-                    s[k][1].add_fma(dy, wj);
-                    s[k][2].add_fma(dz, wj);
-                }
-                const C ux = fmat(mi[k], lj.x, -(q.w * lxi[k]));
-                const C uy = fmat(mi[k], lj.y, -(q.w * lyi[k]));
-                const C uz = fmat(mi[k], lj.z, -(q.w * lzi[k]));
-                const C dl = fmat(dz, lj.z, fmat(dy, lj.y, dx * lj.x));  // d . lam_j
-                C e, dli = C(0);
-                if (JSIDE) {
-                    // -3 d . u = (-3 m_i)(d . lam_j) - (-3 m_j)(d . lam_i): both dots are
-                    // needed anyway, and the factors -3 m come with the sink and the
-                    // source record
-                    dli = fmat(dz, lzi[k], fmat(dy, lyi[k], dx * lxi[k]));
-                    e = r2 * fmat(mi3[k], dl, -(lj.w * dli));
-                } else {
-                    e = (C(-3) * r2) * fmat(dz, uz, fmat(dy, uy, dx * ux));
-                }
-                const C tx = fmat(e, dx, ux);
-                const C ty = fmat(e, dy, uy);
-                const C tz = fmat(e, dz, uz);
-                s[k][3].add_fma(r3, tx);
-                s[k][4].add_fma(r3, ty);
-                s[k][5].add_fma(r3, tz);
-                s[k][6].add_fma(r3, dl);
-                if (JSIDE) {
-                    if (F) {
-                        const C wi = r3 * mi[k];
-                        c[0] = fmat(dx, wi, c[0]);
-                        c[1] = fmat(dy, wi, c[1]);
-                        c[2] = fmat(dz, wi, c[2]);
-                    }
-                    c[3] = fmat(r3, tx, c[3]);
-                    c[4] = fmat(r3, ty, c[4]);
-                    c[5] = fmat(r3, tz, c[5]);
-                    c[6] = fmat(r3, dli, c[6]);
-                }
-            }
+            for (int k = 0; k < K; ++k)
+                asym_pair<JSIDE, F>(q, lj, xi[k], yi[k], zi[k], mi[k], mi3[k], lxi[k], lyi[k],
+                                    lzi[k], s[k], c, eps2);
             if (JSIDE) {
 #pragma unroll
                 for (int p = Q0; p < NQ; ++p) c[p] = from_next_lane(c[p]);
@@ -239,14 +247,195 @@ __global__ __launch_bounds__(W * 64) void adjoint_sym_kernel(ASymArgs<Pol> a) {
     }
 }
 
+// The same items with one wave per 64-source group, as the symmetric force
+// pass's force_group_kernel, whose comment has the reasons. Measured on
+// MI355X against the kernel above in the same blocks of 256, us per pass at
+// 16384 particles: tile-compensated 136 against 147 (entry pass), 165 against
+// 183 (with the force sums); FP32 121, 140 and 147, 176; FP64 218, 257 and
+// 267, 336.
+template <class Pol, int C, int K, bool F>
+__global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol> a) {
+    using T = typename Pol::calc_t;
+    using V4 = typename Vec4<T>::type;
+    constexpr int Q0 = QRange<F>::lo;
+    constexpr int S = C * K;  // sinks per lane; groups and waves per item
+    constexpr int BI = S * 64;
+    constexpr int QP = 4;     // quantities exchanged at a time
+    constexpr int CH = Pol::origin ? C : 1;  // source-side chains
+    constexpr size_t rec_b = 2 * S * 128 * sizeof(V4), ex_b = QP * S * S * 64 * sizeof(T);
+    __shared__ __align__(16) unsigned char buf[rec_b > ex_b ? rec_b : ex_b];
+    V4(*rec)[2][128] = reinterpret_cast<V4(*)[2][128]>(buf);     // per wave
+    T(*ex)[S][S][64] = reinterpret_cast<T(*)[S][S][64]>(buf);    // [quantity][group][sink / 64]
+
+    int I, J;
+    band_item(blockIdx.x, a.band.I0, a.band.I1, I, J);
+    const int lane = threadIdx.x & 63;
+    const int g = threadIdx.x >> 6;
+    const int ib = I * BI + lane;
+    const int j = J * BI + g * 64 + lane;
+    const bool jok = j < a.n;
+    typename Pol::pos_t rx[S], ry[S], rz[S];
+    T xi[S], yi[S], zi[S], mi[S], mi3[S], lxi[S], lyi[S], lzi[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int i = ib + s * 64;
+        const bool ok = i < a.n;
+        rx[s] = ok ? a.x[i] : 0;
+        ry[s] = ok ? a.y[i] : 0;
+        rz[s] = ok ? a.z[i] : 0;
+        mi[s] = ok ? T(a.m[i]) : T(0);  // a padding sink adds exactly 0 to the j side
+        mi3[s] = T(-3) * mi[s];
+        lxi[s] = ok ? T(a.lx[i]) : T(0);
+        lyi[s] = ok ? T(a.ly[i]) : T(0);
+        lzi[s] = ok ? T(a.lz[i]) : T(0);
+    }
+    typename Pol::pos_t qx = 0, qy = 0, qz = 0;
+    V4 p, l;  // zero mass and adjoint past the end: adds 0
+    p.w = l.x = l.y = l.z = l.w = T(0);
+    if (jok) {
+        qx = a.x[j];
+        qy = a.y[j];
+        qz = a.z[j];
+        p.w = T(a.m[j]);
+        l.x = T(a.lx[j]);
+        l.y = T(a.ly[j]);
+        l.z = T(a.lz[j]);
+        l.w = T(-3) * T(a.m[j]);
+    }
+    double ox = 0.0, oy = 0.0, oz = 0.0;
+    if constexpr (Pol::origin) {
+        double cx = 0.0, cy = 0.0, cz = 0.0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            cx += rx[s];
+            cy += ry[s];
+            cz += rz[s];
+        }
+        const double c = 1.0 / double(min(a.n - I * BI, BI));
+        ox = wave_total(cx) * c;
+        oy = wave_total(cy) * c;
+        oz = wave_total(cz) * c;
+    }
+    SumPlain<T> sum[S][NQ];
+    T c[CH][NQ];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const bool ok = ib + s * 64 < a.n;
+        xi[s] = ok ? pair_coord<Pol>(rx[s], ox) : T(0);
+        yi[s] = ok ? pair_coord<Pol>(ry[s], oy) : T(0);
+        zi[s] = ok ? pair_coord<Pol>(rz[s], oz) : T(0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) sum[s][q].init();
+    }
+#pragma unroll
+    for (int h = 0; h < CH; ++h)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) c[h][q] = T(0);
+    p.x = jok ? pair_coord<Pol>(qx, ox) : T(0);
+    p.y = jok ? pair_coord<Pol>(qy, oy) : T(0);
+    p.z = jok ? pair_coord<Pol>(qz, oz) : T(0);
+    rec[g][0][lane] = p;
+    rec[g][0][lane + 64] = p;
+    rec[g][1][lane] = l;
+    rec[g][1][lane + 64] = l;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+
+    const V4* rowp = rec[g][0] + lane;
+    const V4* rowl = rec[g][1] + lane;
+    auto steps = [&](auto jside) {
+        constexpr bool JSIDE = decltype(jside)::value;
+#pragma unroll 1
+        for (int t = 0; t < 64; ++t) {
+            const V4 q = rowp[t];
+            const V4 lj = rowl[t];
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+                asym_pair<JSIDE, F>(q, lj, xi[s], yi[s], zi[s], mi[s], mi3[s], lxi[s], lyi[s],
+                                    lzi[s], sum[s], c[CH > 1 ? s / K : 0], a.eps2);
+            if (JSIDE) {
+#pragma unroll
+                for (int h = 0; h < CH; ++h)
+#pragma unroll
+                    for (int v = Q0; v < NQ; ++v) c[h][v] = from_next_lane(c[h][v]);
+            }
+        }
+    };
+    if (J * BI + g * 64 < a.n) {
+        if (I != J)
+            steps(std::true_type{});
+        else
+            steps(std::false_type{});
+    }
+    // source side: slot I of particle j
+    if (I != J && jok) {
+#pragma unroll
+        for (int q = Q0; q < NQ; ++q) {
+            T t = T(0);
+#pragma unroll
+            for (int h = 0; h < CH; ++h) t += c[h][q];
+            a.part[a.band.offset(I, q - Q0, j)] = -t;
+        }
+    }
+    // sink side: slot J of the sinks of block I, one per thread, the groups'
+    // sums added in group order in FP64
+    const int i = I * BI + threadIdx.x;
+#pragma unroll
+    for (int q0 = Q0; q0 < NQ; q0 += QP) {
+        __syncthreads();
+#pragma unroll
+        for (int q = q0; q < (q0 + QP < NQ ? q0 + QP : NQ); ++q)
+#pragma unroll
+            for (int s = 0; s < S; ++s) ex[q - q0][g][s][lane] = sum[s][q].s;
+        __syncthreads();
+        if (i < a.n) {
+#pragma unroll
+            for (int q = q0; q < (q0 + QP < NQ ? q0 + QP : NQ); ++q) {
+                double t = 0.0;
+#pragma unroll
+                for (int v = 0; v < S; ++v) t += double(ex[q - q0][v][g][lane]);
+                a.part[a.band.offset(J, q - Q0, i)] = T(t);
+            }
+        }
+    }
+}
+
+// Whether a shape's items run with one wave per source group, and the threads
+// of an item's workgroup.
+constexpr bool by_groups(int waves, int ipl) { return ipl == 2 && waves == 2; }
+inline int item_threads(const SymShape& s) {
+    return s.waves * 64 * (by_groups(s.waves, s.ipl) ? s.ipl : 1);
+}
+
+template <class Pol>
+unsigned band_items(const ASymArgs<Pol>& a) {
+    const int64_t R = a.band.I1 - a.band.I0;
+    return (unsigned)(R * (R + 1) / 2 + R * (a.nb - a.band.I1));  // < 2^31 / threads (sym_band_end)
+}
+
+template <class Pol, bool F>
+hipError_t launch_group(const ASymArgs<Pol>& a, hipStream_t stream) {
+    hipLaunchKernelGGL((adjoint_group_kernel<Pol, 2, 2, F>), dim3(band_items(a)), dim3(256), 0,
+                       stream, a);
+    return hipGetLastError();
+}
+// The plain FP32 and FP64 policies' (adjoint_sym_group.hip).
+hipError_t launch_group_own(const ASymArgs<PolF32>& a, bool force_sums, hipStream_t stream);
+hipError_t launch_group_own(const ASymArgs<PolF64>& a, bool force_sums, hipStream_t stream);
+
 // One band of the pair pass in shape W x K; F: with the force sums.
 template <class Pol, int W, int K, bool F>
 hipError_t launch_pairs(const ASymArgs<Pol>& a, hipStream_t stream) {
-    const int64_t R = a.band.I1 - a.band.I0;
-    const int64_t items = R * (R + 1) / 2 + R * (a.nb - a.band.I1);  // < 2^31 / threads (sym_band_end)
-    hipLaunchKernelGGL((adjoint_sym_kernel<Pol, W, K, F>), dim3((unsigned)items), dim3(W * 64), 0,
-                       stream, a);
-    return hipGetLastError();
+    if constexpr (by_groups(W, K)) {
+        if constexpr (Pol::origin)
+            return launch_group<Pol, F>(a, stream);
+        else
+            return launch_group_own(a, F, stream);
+    } else {
+        hipLaunchKernelGGL((adjoint_sym_kernel<Pol, W, K, F>), dim3(band_items(a)), dim3(W * 64), 0,
+                           stream, a);
+        return hipGetLastError();
+    }
 }
 
 // The force-free pair pass of one band (adjoint_sym_entry.hip).

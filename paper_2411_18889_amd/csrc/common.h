@@ -143,6 +143,26 @@ __device__ __forceinline__ double wave_uniform(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// The lanes' sum of v, the same in every lane, on the vector ALU (DPP row
+// shifts and broadcasts: an inclusive scan whose last lane holds the sum).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+    v += dpp_or_zero<0x111, 0xF>(v);  // row_shr:1
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    v += dpp_or_zero<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+    return __hiloint2double(hi, lo);
+}
+
 template <int NW>
 __device__ __forceinline__ void sink_block_origin(double sx, double sy, double sz, int count,
                                                   double (*lds)[3], double& ox, double& oy,
@@ -315,39 +335,21 @@ struct TailArgs {
     explicit TailArgs(const StepTail& t)
         : v(static_cast<T*>(t.v)), store(static_cast<T*>(t.store)),
           x(static_cast<T*>(t.drift_x)), close(t.close), h(T(t.h)), dt(T(t.dt)) {}
-    // particle i of n, at pos (rows of n), with the acceleration as stored
-    __device__ __forceinline__ void apply(int n, int i, const T* pos, T ax, T ay, T az) const {
-        if (!v) return;
-        const size_t iy = (size_t)n + i, iz = 2 * (size_t)n + i;
-        T vx = v[i], vy = v[iy], vz = v[iz];
-        if (close) {  // the same FMAs as the kick-drift kernel's
-            vx = fmat(h, ax, vx);
-            vy = fmat(h, ay, vy);
-            vz = fmat(h, az, vz);
-        }
+    // component k of 3n, at pos, with the acceleration as stored; the same
+    // FMAs as the kick-drift kernel's
+    __device__ __forceinline__ void apply(size_t k, size_t n3, const T* pos, T a) const {
+        T vk = v[k];
+        if (close) vk = fmat(h, a, vk);
         if (store) {
-            const size_t n3 = 3 * (size_t)n;
-            store[i] = pos[i];
-            store[iy] = pos[iy];
-            store[iz] = pos[iz];
-            store[n3 + i] = vx;
-            store[n3 + iy] = vy;
-            store[n3 + iz] = vz;
-            store[2 * n3 + i] = ax;
-            store[2 * n3 + iy] = ay;
-            store[2 * n3 + iz] = az;
+            store[k] = pos[k];
+            store[n3 + k] = vk;
+            store[2 * n3 + k] = a;
         }
         if (x) {
-            vx = fmat(h, ax, vx);
-            vy = fmat(h, ay, vy);
-            vz = fmat(h, az, vz);
-            x[i] = fmat(dt, vx, pos[i]);
-            x[iy] = fmat(dt, vy, pos[iy]);
-            x[iz] = fmat(dt, vz, pos[iz]);
+            vk = fmat(h, a, vk);
+            x[k] = fmat(dt, vk, pos[k]);
         }
-        v[i] = vx;
-        v[iy] = vy;
-        v[iz] = vz;
+        v[k] = vk;
     }
 };
 
@@ -509,6 +511,34 @@ inline SymBandView sym_band_view(const SymLayout& L, int I0, int I1) {
     const int base = (int)(I0 * L.bi);
     return SymBandView{I0, I1, base, (int)(L.n - base),
                        (int)(std::min<int64_t>(L.n, I1 * L.bi) - base), L.nq};
+}
+
+// The symmetric passes' fold kernels: threads per workgroup, and slots whose
+// loads are in flight together.
+constexpr int kFoldLanes = 256;
+constexpr int kFoldSlots = 16;
+
+// Adds to s[0 .. NR-1] the partials at p[r] + u * stride for u < count, in
+// order of u, with U slots' loads in flight.
+template <int NR, int U, typename T, typename F>
+__device__ __forceinline__ void add_slots(F (&s)[NR], const T* const* p, size_t stride, int count) {
+    size_t off = 0;
+    int u = 0;
+    for (; u + U <= count; u += U) {
+        T t[U][NR];
+#pragma unroll
+        for (int v = 0; v < U; ++v)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) t[v][r] = p[r][off + v * stride];
+#pragma unroll
+        for (int v = 0; v < U; ++v)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) s[r] += F(t[v][r]);
+        off += U * stride;
+    }
+    for (; u < count; ++u, off += stride)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) s[r] += F(p[r][off]);
 }
 
 SymShape choose_sym_shape(int prec, int64_t n, bool pot = false);

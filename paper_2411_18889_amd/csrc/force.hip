@@ -61,7 +61,12 @@ __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, doub
     a.ax[i] = ax;
     a.ay[i] = ay;
     a.az[i] = az;
-    if (TAIL) a.tail.apply(a.ni, i, a.xi, ax, ay, az);
+    if (TAIL && a.tail.v) {
+        const size_t n = a.ni, n3 = 3 * n;
+        a.tail.apply(i, n3, a.xi, ax);
+        a.tail.apply(n + i, n3, a.xi, ay);
+        a.tail.apply(2 * n + i, n3, a.xi, az);
+    }
     if (POT) {
         double self = 0.0;
         if (a.self_pot) {
@@ -306,8 +311,8 @@ __global__ __launch_bounds__(LB) void force_lanes_kernel(ForceArgs<Pol> a) {
 // own sinks while others still read the positions.
 template <class Pol>
 __global__ __launch_bounds__(256) void force_tail_kernel(ForceArgs<Pol> a) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < a.ni) a.tail.apply(a.ni, i, a.xi, a.ax[i], a.ay[i], a.az[i]);
+    const size_t k = blockIdx.x * (size_t)256 + threadIdx.x, n3 = 3 * (size_t)a.ni;
+    if (k < n3) a.tail.apply(k, n3, a.xi, a.ax[k]);
 }
 
 template <class Pol>
@@ -385,7 +390,8 @@ hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_
         a.part = nullptr;
         const hipError_t e = launch_any<Pol, ACC, POT>(sh, a, 1, stream);
         if (e != hipSuccess || !a.tail.v) return e;
-        hipLaunchKernelGGL(force_tail_kernel<Pol>, dim3((a.ni + 255) / 256), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(force_tail_kernel<Pol>, dim3((unsigned)((3 * (int64_t)a.ni + 255) / 256)),
+                           dim3(256), 0, stream, a);
         return hipGetLastError();
     }
     a.part = static_cast<double*>(ws);

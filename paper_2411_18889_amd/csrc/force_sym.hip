@@ -105,8 +105,8 @@ struct SymFinishArgs {
     int n, nb;
     typename Pol::calc_t eps2;
     double G;
-    typename Pol::pos_t *ax, *ay, *az;
-    typename Pol::pos_t* pot;           // or nullptr
+    typename Pol::pos_t* ax;   // 3n
+    typename Pol::pos_t* pot;  // or nullptr
     const typename Pol::pos_t* x;
     TailArgs<typename Pol::pos_t> tail;
 };
@@ -275,70 +275,250 @@ __global__ __launch_bounds__(W * 64) void force_sym_kernel(SymArgs<Pol> a) {
     }
 }
 
+// The same items with one wave per 64-source group: C * K = S groups and sinks
+// per lane, so every wave meets one group with all BI sinks of block I (S per
+// lane instead of K: one LDS record read for S pairs, and more independent
+// chains), stages its group in LDS for itself -- no barrier in the pair loop --
+// and has the group's whole source side in its lanes. The sink sides of the
+// groups meet in LDS once per item and are added there in group order in FP64,
+// so no FP64 sums are held in registers (68 VGPRs with two by two sinks,
+// against 126 for the kernel above). For the tile-compensated policy the
+// source-side sums stay C chains of K sinks, added in chain order: the same
+// FP32 operations in the same order as above. FP32 and FP64 sum all S sinks in
+// one chain, which takes half or a quarter of the lane rotations.
+// Against the kernel above, us per pass (with its fold) on MI355X:
+//                    12288         16384         20011         32768
+//   tile-comp. 2 x 2 49.0,  61.0   75.0,  80.5  103, 119
+//   FP32       2 x 2 45.3,  55.5   68.5,  79.3   96, 115       223, 234 (4 x 2)
+//   FP64       2 x 2 86.3, 100     129,  156    187, 219       472, 503 (4 x 2)
+// (launch and memory latency aside, every SIMD gets 8 or 9 of the 8320 waves at
+// 16384: a tenth is the uneven share.) Shapes by_groups() gives.
+template <class Pol, int C, int K, bool P>
+__global__ __launch_bounds__(C * K * 64) void force_group_kernel(SymArgs<Pol> a) {
+    using T = typename Pol::calc_t;
+    using V4 = typename Vec4<T>::type;
+    constexpr int S = C * K;  // sinks per lane; groups and waves per item
+    constexpr int BI = S * 64;
+    constexpr int NQ = P ? 4 : 3;
+    constexpr int QP = S <= 4 ? NQ : 1;  // quantities exchanged at a time
+    // source-side chains: one for each C of the shape's K sinks where their
+    // FP32 order is part of the policy's results, else one
+    constexpr int CH = Pol::origin ? C : 1;
+    constexpr size_t rec_b = S * 128 * sizeof(V4), ex_b = QP * S * S * 64 * sizeof(T);
+    __shared__ __align__(16) unsigned char buf[rec_b > ex_b ? rec_b : ex_b];
+    V4(*rec)[128] = reinterpret_cast<V4(*)[128]>(buf);           // per wave
+    T(*ex)[S][S][64] = reinterpret_cast<T(*)[S][S][64]>(buf);    // [quantity][group][sink / 64]
+
+    int I, J;
+    band_item(blockIdx.x, a.band.I0, a.band.I1, I, J);
+    const int lane = threadIdx.x & 63;
+    const int g = threadIdx.x >> 6;
+    const int ib = I * BI + lane;
+    const int j = J * BI + g * 64 + lane;
+    const bool jok = j < a.n;
+    // sinks and source, loaded together
+    typename Pol::pos_t rx[S], ry[S], rz[S];
+    T xi[S], yi[S], zi[S], mi[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int i = ib + s * 64;
+        const bool ok = i < a.n;
+        rx[s] = ok ? a.x[i] : 0;
+        ry[s] = ok ? a.y[i] : 0;
+        rz[s] = ok ? a.z[i] : 0;
+        mi[s] = ok ? T(a.m[i]) : T(0);  // a padding sink adds exactly 0 to the j side
+    }
+    typename Pol::pos_t qx = 0, qy = 0, qz = 0;
+    V4 p;
+    p.w = T(0);  // zero-mass padding past the end
+    if (jok) {
+        qx = a.x[j];
+        qy = a.y[j];
+        qz = a.z[j];
+        p.w = T(a.m[j]);
+    }
+    double ox = 0.0, oy = 0.0, oz = 0.0;
+    if constexpr (Pol::origin) {
+        double cx = 0.0, cy = 0.0, cz = 0.0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            cx += rx[s];
+            cy += ry[s];
+            cz += rz[s];
+        }
+        const double c = 1.0 / double(min(a.n - I * BI, BI));
+        ox = wave_total(cx) * c;
+        oy = wave_total(cy) * c;
+        oz = wave_total(cz) * c;
+    }
+    T sum[S][NQ], c[CH][NQ];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const bool ok = ib + s * 64 < a.n;
+        xi[s] = ok ? pair_coord<Pol>(rx[s], ox) : T(0);
+        yi[s] = ok ? pair_coord<Pol>(ry[s], oy) : T(0);
+        zi[s] = ok ? pair_coord<Pol>(rz[s], oz) : T(0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) sum[s][q] = T(0);
+    }
+#pragma unroll
+    for (int h = 0; h < CH; ++h)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) c[h][q] = T(0);
+    p.x = jok ? pair_coord<Pol>(qx, ox) : T(0);
+    p.y = jok ? pair_coord<Pol>(qy, oy) : T(0);
+    p.z = jok ? pair_coord<Pol>(qz, oz) : T(0);
+    rec[g][lane] = p;
+    rec[g][lane + 64] = p;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+
+    const V4* row = rec[g] + lane;
+    auto steps = [&](auto jside) {
+        constexpr bool JSIDE = decltype(jside)::value;
+#pragma unroll 2
+        for (int t = 0; t < 64; ++t) {
+            const V4 q = row[t];
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const T dx = q.x - xi[s];
+                const T dy = q.y - yi[s];
+                const T dz = q.z - zi[s];
+                const T ss = fmat(dz, dz, fmat(dy, dy, fmat(dx, dx, a.eps2)));
+                const T r = rsqrt_pair(ss);
+                const T r3 = r * (r * r);
+                const T wj = r3 * q.w;
+                sum[s][0] = fmat(dx, wj, sum[s][0]);
+                sum[s][1] = fmat(dy, wj, sum[s][1]);
+                sum[s][2] = fmat(dz, wj, sum[s][2]);
+                if (P) sum[s][NQ - 1] = fmat(q.w, r, sum[s][NQ - 1]);
+                if (JSIDE) {
+                    T* ch = c[CH > 1 ? s / K : 0];
+                    const T wi = r3 * mi[s];
+                    ch[0] = fmat(dx, wi, ch[0]);
+                    ch[1] = fmat(dy, wi, ch[1]);
+                    ch[2] = fmat(dz, wi, ch[2]);
+                    if (P) ch[NQ - 1] = fmat(mi[s], r, ch[NQ - 1]);
+                }
+            }
+            if (JSIDE) {
+#pragma unroll
+                for (int h = 0; h < CH; ++h)
+#pragma unroll
+                    for (int q2 = 0; q2 < NQ; ++q2) c[h][q2] = from_next_lane(c[h][q2]);
+            }
+        }
+    };
+    if (J * BI + g * 64 < a.n) {
+        if (I != J)
+            steps(std::true_type{});
+        else
+            steps(std::false_type{});
+    }
+    // source side: slot I of particle j
+    if (I != J && jok) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            T t = T(0);
+#pragma unroll
+            for (int h = 0; h < CH; ++h) t += c[h][q];
+            a.part[a.band.offset(I, q, j)] = q < 3 ? -t : t;
+        }
+    }
+    // sink side: slot J of the sinks of block I, one per thread, the groups'
+    // sums added in group order in FP64
+    const int i = I * BI + threadIdx.x;
+#pragma unroll
+    for (int q0 = 0; q0 < NQ; q0 += QP) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < QP; ++q)
+#pragma unroll
+            for (int s = 0; s < S; ++s) ex[q][g][s][lane] = sum[s][q0 + q];
+        __syncthreads();
+        if (i < a.n) {
+#pragma unroll
+            for (int q = 0; q < QP; ++q) {
+                double t = 0.0;
+#pragma unroll
+                for (int v = 0; v < S; ++v) t += double(ex[q][v][g][lane]);
+                a.part[a.band.offset(J, q0 + q, i)] = T(t);
+            }
+        }
+    }
+}
+
 // The fold of one band (SymFinishArgs): adds a particle's partials in slot
 // order (in fin_t: FP64 for the tile-compensated and FP64 policies, FP32 for
 // the FP32 one) to its running sum; when its slots are complete, stores
 // a = G * sum and applies the leapfrog's tail; with P, also the potential
 // -G (sum - m_i / eps).
-template <class Pol, bool P>
-__global__ __launch_bounds__(256) void force_sym_finish_kernel(SymFinishArgs<Pol> a) {
+// A thread does one component (blockIdx.y; 3: the potential) of a particle:
+// at small n the kernel is one load latency after another, so three threads a
+// particle share them (the adds stay in slot order).
+template <class Pol>
+__global__ __launch_bounds__(kFoldLanes) void force_sym_finish_kernel(SymFinishArgs<Pol> a) {
     using pos_t = typename Pol::pos_t;
     using fin_t = typename Pol::fin_t;
-    using calc_t = typename Pol::calc_t;
-    constexpr int NQ = P ? 4 : 3;
     const SymBandView& b = a.band;
-    const int i = b.base + blockIdx.x * 256 + threadIdx.x;
+    const int c = blockIdx.y;
+    const int i = b.base + blockIdx.x * kFoldLanes + threadIdx.x;
     if (i >= a.n) return;
-    fin_t sx = 0, sy = 0, sz = 0, sp = 0;
-    if (!a.first) {
-        sx = a.run[i];
-        sy = a.run[(size_t)a.n + i];
-        sz = a.run[(size_t)2 * a.n + i];
-        if (P) sp = a.run[(size_t)3 * a.n + i];
-    }
-    // slots I0 .. I1-1 (region A), unrolled so that the loads of eight slots
-    // are in flight together (the adds stay in slot order; at small n the
-    // pass is latency-bound here)
-#pragma unroll 8
-    for (int k = b.I0; k < b.I1; ++k) {
-        sx += fin_t(a.part[b.offset(k, 0, i)]);
-        sy += fin_t(a.part[b.offset(k, 1, i)]);
-        sz += fin_t(a.part[b.offset(k, 2, i)]);
-        if (P) sp += fin_t(a.part[b.offset(k, 3, i)]);
-    }
+    using part_t = typename Pol::calc_t;
+    fin_t sum[1] = {a.first ? fin_t(0) : a.run[(size_t)c * a.n + i]};
+    // slots I0 .. I1-1 (region A)
+    const part_t* const pa[1] = {a.part + b.offset(b.I0, c, i)};
+    add_slots<1, kFoldSlots>(sum, pa, (size_t)b.nq * b.np, b.I1 - b.I0);
     if (i >= b.base + b.nbp) {  // a later band adds this particle's next slots
-        a.run[i] = sx;
-        a.run[(size_t)a.n + i] = sy;
-        a.run[(size_t)2 * a.n + i] = sz;
-        if (P) a.run[(size_t)3 * a.n + i] = sp;
+        a.run[(size_t)c * a.n + i] = sum[0];
         return;
     }
     // the band's own particles: slots I1 .. nb-1 (region B), then finish
-#pragma unroll 8
-    for (int k = b.I1; k < a.nb; ++k) {
-        sx += fin_t(a.part[b.offset(k, 0, i)]);
-        sy += fin_t(a.part[b.offset(k, 1, i)]);
-        sz += fin_t(a.part[b.offset(k, 2, i)]);
-        if (P) sp += fin_t(a.part[b.offset(k, 3, i)]);
-    }
-    if (P) {
+    const part_t* const pb[1] = {a.part + b.offset(b.I1, c, i)};
+    add_slots<1, kFoldSlots>(sum, pb, (size_t)b.nq * b.nbp, a.nb - b.I1);
+    const fin_t s = sum[0];
+    if (c == 3) {
         // the j = i term as the pair loop formed it: m_i times the
         // reciprocal square root of eps^2, one product in the pair type
         const double self = double(a.m[i] * rsqrt_pair(a.eps2));
-        a.pot[i] = pos_t(-a.G * (double(sp) - self));
+        a.pot[i] = pos_t(-a.G * (double(s) - self));
+        return;
     }
-    const pos_t ax = pos_t(a.G * double(sx)), ay = pos_t(a.G * double(sy)),
-                az = pos_t(a.G * double(sz));
-    a.ax[i] = ax;
-    a.ay[i] = ay;
-    a.az[i] = az;
-    a.tail.apply(a.n, i, a.x, ax, ay, az);
+    const pos_t acc = pos_t(a.G * double(s));
+    const size_t k = (size_t)c * a.n + i;
+    a.ax[k] = acc;
+    if (a.tail.v) a.tail.apply(k, 3 * (size_t)a.n, a.x, acc);
+}
+
+// Whether a shape's items run with one wave per source group, and the threads
+// of an item's workgroup.
+// Blocks of 256 for every policy; blocks of 512 in FP64 (65536: 1775 against
+// 1844 us) and, up to 96 blocks, in FP32 (65536, 128 blocks: 895 against 860).
+template <class Pol>
+constexpr bool by_groups(int waves, int ipl, int nb) {
+    return ipl == 2 && (waves == 2 || (waves == 4 && !Pol::origin &&
+                                       (sizeof(typename Pol::calc_t) == 8 || nb <= 96)));
+}
+template <class Pol>
+int item_threads(const SymShape& s, int nb) {
+    return s.waves * 64 * (by_groups<Pol>(s.waves, s.ipl, nb) ? s.ipl : 1);
 }
 
 template <class Pol, int W, int K>
 hipError_t launch_sym(const SymArgs<Pol>& a, bool pot, hipStream_t stream) {
     const int64_t R = a.band.I1 - a.band.I0;
     const int64_t items = R * (R + 1) / 2 + R * (a.nb - a.band.I1);  // < 2^31 / threads (sym_band_end)
+    if constexpr (by_groups<Pol>(W, K, 1)) {
+        if (by_groups<Pol>(W, K, a.nb)) {
+            if (pot)
+                hipLaunchKernelGGL((force_group_kernel<Pol, W, K, true>), dim3((unsigned)items),
+                                   dim3(W * K * 64), 0, stream, a);
+            else
+                hipLaunchKernelGGL((force_group_kernel<Pol, W, K, false>), dim3((unsigned)items),
+                                   dim3(W * K * 64), 0, stream, a);
+            return hipGetLastError();
+        }
+    }
     if (pot)
         hipLaunchKernelGGL((force_sym_kernel<Pol, W, K, true>), dim3((unsigned)items), dim3(W * 64),
                            0, stream, a);
@@ -359,7 +539,8 @@ hipError_t run_sym(const SymShape& sh, int64_t n, const void* x, const void* m, 
     const SymLayout L{n, bi, (int)((n + bi - 1) / bi), pot ? 4 : 3, sizeof(calc_t), sizeof(fin_t)};
     // one band when the workspace holds every partial; else the running sums
     // first, then one band's partials at a time
-    const SymPlan plan = sym_plan(L, ws_bytes, sh.waves * 64);
+    const int nt = item_threads<Pol>(sh, L.nb);
+    const SymPlan plan = sym_plan(L, ws_bytes, nt);
     if (!plan.valid) return hipErrorInvalidValue;
     fin_t* run = plan.one ? nullptr : static_cast<fin_t*>(ws);
     calc_t* parts = reinterpret_cast<calc_t*>(static_cast<char*>(ws) + plan.parts);
@@ -381,17 +562,14 @@ hipError_t run_sym(const SymShape& sh, int64_t n, const void* x, const void* m, 
     f.eps2 = a.eps2;
     f.G = G;
     f.pot = static_cast<pos_t*>(pot);
-    pos_t* po = static_cast<pos_t*>(acc);
-    f.ax = po;
-    f.ay = po + n;
-    f.az = po + 2 * n;
+    f.ax = static_cast<pos_t*>(acc);
     f.x = p;
     f.tail = TailArgs<pos_t>(tail);
     a.part = parts;
     f.part = parts;
     f.nb = L.nb;
     for (int I0 = 0; I0 < L.nb;) {
-        const int I1 = sym_band_end(L, I0, budget, sh.waves * 64);
+        const int I1 = sym_band_end(L, I0, budget, nt);
         a.band = f.band = sym_band_view(L, I0, I1);
         hipError_t e = hipErrorInvalidValue;
 #define NB_SYM_CASE(WV, KV) \
@@ -402,11 +580,8 @@ hipError_t run_sym(const SymShape& sh, int64_t n, const void* x, const void* m, 
 #undef NB_SYM_CASE
         if (e != hipSuccess) return e;
         f.first = I0 == 0;
-        const dim3 fg((unsigned)((a.band.np + 255) / 256));
-        if (pot)
-            hipLaunchKernelGGL((force_sym_finish_kernel<Pol, true>), fg, dim3(256), 0, stream, f);
-        else
-            hipLaunchKernelGGL((force_sym_finish_kernel<Pol, false>), fg, dim3(256), 0, stream, f);
+        const dim3 fg((unsigned)((a.band.np + kFoldLanes - 1) / kFoldLanes), pot ? 4 : 3);
+        hipLaunchKernelGGL((force_sym_finish_kernel<Pol>), fg, dim3(kFoldLanes), 0, stream, f);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         I0 = I1;
     }
