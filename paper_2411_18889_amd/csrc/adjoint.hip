@@ -90,8 +90,9 @@ __device__ __forceinline__ void finish_adj(const AdjArgs<Pol>& a, int i, const d
 // F: also sum the force a (quantities 0..2, for a pass that walks the state
 // back); without it they stay 0 and the pair body is 4 operations shorter.
 // FEW: built for few waves in flight (kFewWaves): tile-compensated entry pass
-// 37.0 -> 25.4 us at 2500 particles, 39 -> 33 at 5003 (at 10000 88 against 85,
-// so not there).
+// 36.5 -> 25.3 us at 2500 particles, 38.4 -> 33.0 at 5003 (at 10000 88 against
+// 85, so not there); with Kahan sums from half as many waves down (walked-back
+// step 85 -> 71 at 5003, but 128 -> 146 at 9377).
 template <class Pol, int BS, int K, bool F, bool FEW>
 __global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void adjoint_kernel(AdjArgs<Pol> a) {
     using calc_t = typename Pol::calc_t;
@@ -213,6 +214,102 @@ __global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void adjoint_kernel(AdjArg
     }
 }
 
+// Sources on the lanes, as the force pass's force_lanes_kernel (which has the
+// reasons): LB lanes, LS sinks per workgroup, every lane with every LB-th
+// source; the lanes' sums meet in LDS and the workgroup finishes its sinks. The
+// walk's next step is entered by a kernel of its own, since other workgroups
+// still read x and lam_v. org_block: sinks per origin block (the one-sided
+// kernel's workgroups). Four sinks, two for FP32 with the force sums (4001
+// particles, us: FP64 25 with four, 31 with two; FP32 with the force sums 23
+// and 21).
+constexpr int LB = 256;
+template <class Pol, bool F>
+constexpr int lane_sinks = std::is_same<Pol, PolF32>::value && F ? 2 : 4;
+
+template <class Pol, bool F>
+__global__ __launch_bounds__(LB) void adjoint_lanes_kernel(AdjArgs<Pol> a, int org_block) {
+    using calc_t = typename Pol::calc_t;
+    using sum_t = typename Pol::sum_t;
+    constexpr int LS = lane_sinks<Pol, F>;
+    constexpr int Q0 = F ? 0 : 3, N = NQ - Q0, V = LS * N;
+    __shared__ double lsum[V][LB + 1];
+    __shared__ double tot[LS][N];
+    const int tid = threadIdx.x;
+    const int i0 = blockIdx.x * LS;
+    double ox = 0.0, oy = 0.0, oz = 0.0;
+    if constexpr (Pol::origin) {
+        __shared__ double org[LB / 64][3];
+        const int b0 = i0 / org_block * org_block, i = b0 + tid;
+        const bool ok = tid < org_block && i < a.n;
+        sink_block_origin<LB / 64>(ok ? a.x[i] : 0.0, ok ? a.y[i] : 0.0, ok ? a.z[i] : 0.0,
+                                   min(a.n - b0, org_block), org, ox, oy, oz);
+    }
+    calc_t xi[LS], yi[LS], zi[LS], mi[LS], lxi[LS], lyi[LS], lzi[LS];
+    sum_t s[LS][NQ];
+#pragma unroll
+    for (int k = 0; k < LS; ++k) {
+        const int i = min(i0 + k, a.n - 1);
+        xi[k] = pair_coord<Pol>(a.x[i], ox);
+        yi[k] = pair_coord<Pol>(a.y[i], oy);
+        zi[k] = pair_coord<Pol>(a.z[i], oz);
+        mi[k] = calc_t(a.m[i]);
+        lxi[k] = calc_t(a.lx[i]);
+        lyi[k] = calc_t(a.ly[i]);
+        lzi[k] = calc_t(a.lz[i]);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) s[k][q].init();
+    }
+#pragma unroll 2
+    for (int j = tid; j < a.n; j += LB) {
+        const calc_t x = pair_coord<Pol>(a.x[j], ox), y = pair_coord<Pol>(a.y[j], oy),
+                     z = pair_coord<Pol>(a.z[j], oz), m = calc_t(a.m[j]);
+        const calc_t lx = calc_t(a.lx[j]), ly = calc_t(a.ly[j]), lz = calc_t(a.lz[j]);
+#pragma unroll
+        for (int k = 0; k < LS; ++k) {
+            const calc_t dx = x - xi[k], dy = y - yi[k], dz = z - zi[k];
+            const calc_t ss = fmat(dz, dz, fmat(dy, dy, fmat(dx, dx, a.eps2)));
+            const calc_t r = rsqrt_pair(ss);
+            const calc_t r2 = r * r;
+            const calc_t r3 = r2 * r;
+            if (F) {
+                const calc_t w = r3 * m;
+                s[k][0].add_fma(dx, w);
+                s[k][1].add_fma(dy, w);
+                s[k][2].add_fma(dz, w);
+            }
+            const calc_t ux = fmat(mi[k], lx, -(m * lxi[k]));
+            const calc_t uy = fmat(mi[k], ly, -(m * lyi[k]));
+            const calc_t uz = fmat(mi[k], lz, -(m * lzi[k]));
+            const calc_t e = (calc_t(-3) * r2) * fmat(dz, uz, fmat(dy, uy, dx * ux));
+            s[k][3].add_fma(r3, fmat(e, dx, ux));
+            s[k][4].add_fma(r3, fmat(e, dy, uy));
+            s[k][5].add_fma(r3, fmat(e, dz, uz));
+            s[k][6].add_fma(r3, fmat(dz, lz, fmat(dy, ly, dx * lx)));
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < LS; ++k)
+#pragma unroll
+        for (int q = 0; q < N; ++q) lsum[k * N + q][tid] = s[k][Q0 + q].total();
+    __syncthreads();
+    const int l = tid & 15;
+    for (int v = tid >> 4; v < V; v += LB / 16) {  // 16 lanes add sum v
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < LB / 16; ++q) t += lsum[v][q * 16 + l];
+#pragma unroll
+        for (int mask = 8; mask >= 1; mask >>= 1) t += __shfl_xor(t, mask, 64);
+        if (l == 0) tot[v / N][v % N] = t;
+    }
+    __syncthreads();
+    if (tid < LS && i0 + tid < a.n) {
+        double t[NQ] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < N; ++q) t[Q0 + q] = tot[tid][q];
+        finish_adj<Pol, false>(a, i0 + tid, t);
+    }
+}
+
 // The partial sums in the fixed order of the force pass's reduction: wave g of
 // a workgroup takes ranges g, g + 4, ... of 64 sinks, the first wave adds the
 // four sums and finishes. F as the pair kernel's.
@@ -262,8 +359,10 @@ hipError_t launch_shape(AdjArgs<Pol> a, int nsplit, hipStream_t stream) {
             hipLaunchKernelGGL((adjoint_kernel<Pol, BS, K, false, FEW>), grid, dim3(BS), 0, stream, a);
         return hipGetLastError();
     };
-    if constexpr (K == 1 && std::is_same<typename Pol::calc_t, float>::value)
-        if ((int64_t)grid.x * nsplit * (BS / 64) < kFewWaves) return launch(std::true_type{});
+    constexpr bool kahan = std::is_same<typename Pol::sum_t, SumKahan>::value;
+    if constexpr (K == 1 && (kahan || std::is_same<typename Pol::sum_t, SumTile>::value))
+        if ((int64_t)grid.x * nsplit * (BS / 64) < (kahan ? kFewWaves / 2 : kFewWaves))
+            return launch(std::true_type{});
     return launch(std::false_type{});
 }
 
@@ -281,7 +380,21 @@ hipError_t launch_any(const Shape& sh, AdjArgs<Pol> a, int nsplit, hipStream_t s
 
 }  // namespace
 
-Shape choose_adjoint_shape(int prec, int64_t n, bool least) {
+Shape choose_adjoint_shape(int prec, int64_t n, Pick pick) {
+    // Sources on the lanes, for the policies whose sums may be regrouped: us
+    // per entry pass and per walked-back step against the split ranges below,
+    // measured on MI355X,
+    //            2000              4001              6000              12287
+    //   FP64     15, 17 / 19, 24   25, 32 / 42, 38   52, 61 / 67, 77   201, 223 / 210, 229
+    //   FP32     15, 18 / 18, 21   16, 21 / 26, 31   29, 38 / 44, 53   103, 132 / 116, 135
+    //   acc64    17, 23 / 17, 25   27, 34 / 29, 48   52, 61 / 52, 67   172, 195 / 142, 183
+    // so up to 6000 particles for FP64 sums of FP32 terms.
+    const bool regroup = prec == NB_F64 || prec == NB_F32 || prec == NB_MIX_ACC64;
+    if (pick == Pick::Best && regroup && n <= (prec == NB_MIX_ACC64 ? 6000 : 12287)) {
+        Shape s{4, LB, LB};
+        s.lanes = true;
+        return s;
+    }
     // Measured on MI355X: one sink per lane (the fused pair body is long
     // enough to hide latency on its own; two sinks per lane run 13 % slower),
     // 512-lane workgroups from 2^19 sinks up, 256 from 4096, 64 below; a
@@ -303,7 +416,7 @@ Shape choose_adjoint_shape(int prec, int64_t n, bool least) {
     // force pass (and not for the same two policies): entry pass 37.0 instead
     // of 56.9 us at 2500 particles, 39.1 instead of 59.6 at 5003, 84.9
     // instead of 96.5 at 10000
-    if (!least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN)
+    if (pick != Pick::Least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN)
         split = std::max<int64_t>(split_ranges(n, split, s.block),
                                   short_tile_ranges(n, s.block, waves, 8192));
     s.split = (int)split;
@@ -316,6 +429,7 @@ bool adjoint_shape_supported(const Shape& s) {
 }
 
 size_t adjoint_partials_bytes(const Shape& s, int64_t n) {
+    if (s.lanes) return 0;
     return (size_t)s.split * NQ * (size_t)n * sizeof(double);
 }
 
@@ -349,6 +463,24 @@ hipError_t launch_adjoint(int prec, const Shape& sh, int64_t n, const void* x, c
         a.vx = pv; a.vy = pv + n; a.vz = pv + 2 * n;
         a.gx = pg; a.gy = pg + n; a.gz = pg + 2 * n;
         a.gm = lam_m;
+        if (sh.lanes) {
+            if constexpr (std::is_same<typename Pol::sum_t, SumKahan>::value ||
+                          std::is_same<typename Pol::sum_t, SumTile>::value ||
+                          std::is_same<Pol, PolMixAcc32>::value) {
+                return;
+            } else {
+                const int org = choose_adjoint_shape(prec, n, Pick::Least).block;
+                auto grid = [&](int sinks) { return dim3((unsigned)((n + sinks - 1) / sinks)); };
+                if (update_state)
+                    hipLaunchKernelGGL((adjoint_lanes_kernel<Pol, true>), grid(lane_sinks<Pol, true>),
+                                       dim3(LB), 0, stream, a, org);
+                else
+                    hipLaunchKernelGGL((adjoint_lanes_kernel<Pol, false>), grid(lane_sinks<Pol, false>),
+                                       dim3(LB), 0, stream, a, org);
+                err = hipGetLastError();
+                return;
+            }
+        }
         const int span = split_span(n, sh.split, sh.block);
         const int nsplit = split_ranges(n, sh.split, sh.block);
         a.jspan = span;

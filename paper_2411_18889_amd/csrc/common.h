@@ -258,8 +258,8 @@ struct Shape {
     int ipl;    // sinks per lane
     int block;  // threads per workgroup = j-tile length
     int split;  // j-ranges per sink
-    bool lanes = false;  // the force kernel with its sources on the lanes (block
-                         // lanes, ipl sinks per workgroup); no partials
+    bool lanes = false;  // the kernel with its sources on the lanes (block lanes,
+                         // ipl sinks per workgroup); no partials
 };
 
 // A split of nj sources gives ranges of whole tiles (`block` sources): their
@@ -294,7 +294,7 @@ inline int64_t short_tile_ranges(int64_t nj, int block, int64_t waves, int64_t m
 // which a call takes when the first one's does not fit.
 enum class Pick { Best, Split, Least };
 Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick = Pick::Best);
-Shape choose_adjoint_shape(int prec, int64_t n, bool least = false);
+Shape choose_adjoint_shape(int prec, int64_t n, Pick pick = Pick::Best);
 // Shapes the one-sided force / adjoint kernels are built for.
 bool shape_supported(const Shape& s);
 bool adjoint_shape_supported(const Shape& s);

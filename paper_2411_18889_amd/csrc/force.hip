@@ -81,7 +81,9 @@ __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, doub
 }
 
 // FEW: built for few waves in flight (kFewWaves): 5003 particles, tile-
-// compensated, 20.2 -> 18.9 us a pass, 10000 49.3 -> 47.5. Not with the
+// compensated, 20.0 -> 19.1 us a pass, 9377 43.7 -> 42.2; with plain FP32 sums
+// 9377 42.9 -> 41.9 (Kahan 60.5 -> 65.6 and FP64 sums 53.9 -> 55.8, so not
+// there). Not with the
 // potential, whose kernel that build makes slower (9558 particles 46 -> 52 us,
 // 128 sinks of 205175 sources 62 -> 89).
 template <class Pol, int BS, int K, bool ACC, bool POT, bool FEW>
@@ -342,7 +344,9 @@ ForceArgs<Pol> make_args(int64_t ni, const void* xi, int64_t nj, const void* xj,
 template <class Pol, bool ACC, bool POT, int BS, int K>
 hipError_t launch_shape(ForceArgs<Pol> a, int nsplit, hipStream_t stream) {
     dim3 grid((a.ni + BS * K - 1) / (BS * K), nsplit);
-    if constexpr (K == 1 && !POT && std::is_same<typename Pol::calc_t, float>::value) {
+    using sum_t = typename Pol::sum_t;
+    if constexpr (K == 1 && !POT && (std::is_same<sum_t, SumTile>::value ||
+                                     std::is_same<sum_t, SumPlain<float>>::value)) {
         if ((int64_t)grid.x * nsplit * (BS / 64) < 2 * kFewWaves) {
             hipLaunchKernelGGL((force_kernel<Pol, BS, K, ACC, POT, true>), grid, dim3(BS), 0, stream, a);
             return hipGetLastError();

@@ -260,8 +260,8 @@ int resolve_accel(int prec, int64_t ni, int64_t nj, bool self_set, bool pot,
 int resolve_adjoint(int prec, int64_t n, const nb_launch* launch, SymShape* sym, Shape* sh,
                     Shape* least) {
     *sym = choose_adjoint_sym_shape(prec, n);
-    *sh = choose_adjoint_shape(prec, n);
-    *least = choose_adjoint_shape(prec, n, true);
+    *sh = choose_adjoint_shape(prec, n, launch ? Pick::Split : Pick::Best);
+    *least = choose_adjoint_shape(prec, n, Pick::Least);
     if (!launch) return NB_OK;
     if (launch->symmetric) {
         const int st = sym_from_launch(*launch, *sym, sym);
@@ -283,6 +283,8 @@ size_t adjoint_partials_need(int prec, const SymShape& sym, const Shape& sh, int
     }
     return sh.split > 1 ? adjoint_partials_bytes(sh, n) : 0;
 }
+// (a call of the kernel that keeps its sums on the lanes needs the scratch that
+// the other kernel would, as the force passes)
 
 }  // namespace
 
@@ -590,7 +592,7 @@ int adjoint_common(int64_t n, void* x, void* v, const void* m, void* acc, void* 
         const size_t most = adjoint_partials_need(prec, sym, sh, n, true);
         if (usable_ws(ws, ws_bytes) < most || ws_overlaps(most)) sh = shl;
     }
-    const size_t need = adjoint_partials_need(prec, sym, sh, n, true);
+    const size_t need = adjoint_partials_need(prec, sym, sh.lanes ? shl : sh, n, true);
     st = check_ws(ws, ws_bytes, need);
     if (st != NB_OK) return st;
     const size_t used = sym.waves ? std::min(ws_bytes, sym_full_bytes(adjoint_sym_layout(prec, sym, n, true)))
@@ -718,7 +720,8 @@ size_t nbody_pass_workspace_size(int op, int64_t ni, int64_t nj, int prec, int s
     Shape sh, least;
     if (op == NB_OP_ADJOINT) {
         if (ni != nj || resolve_adjoint(prec, ni, launch, &sym, &sh, &least) != NB_OK) return 0;
-        return adjoint_partials_need(prec, sym, sh, ni, false);
+        return std::max(adjoint_partials_need(prec, sym, sh, ni, false),
+                        adjoint_partials_need(prec, sym, least, ni, false));
     }
     if (op != NB_OP_ACCEL || (self_set && ni != nj)) return 0;
     if (resolve_accel(prec, ni, nj, self_set != 0, potential != 0, launch, &sym, &sh, &least) != NB_OK)
@@ -745,8 +748,9 @@ size_t nbody_workspace_size(int op, int64_t n, int prec) {
     case NB_OP_ADJOINT: {
         const SymShape sym = choose_adjoint_sym_shape(prec, n);
         if (sym.waves) return sym_default_bytes(adjoint_sym_layout(prec, sym, n, true));
-        const Shape sh = choose_adjoint_shape(prec, n);
-        return sh.split > 1 ? adjoint_partials_bytes(sh, n) : 0;
+        const Shape sh = choose_adjoint_shape(prec, n), least = choose_adjoint_shape(prec, n, Pick::Least);
+        return std::max(adjoint_partials_need(prec, sym, sh, n, false),
+                        adjoint_partials_need(prec, sym, least, n, false));
     }
     case NB_OP_DIAG:
         return diag_workspace_bytes(n);

@@ -149,3 +149,39 @@ def test_unsplit_set_without_workspace():
     nb.step(xd, vd, md, acc, eps, dt, S, prec="f64")
     xo, vo, ao = oracle.kdk(x, v, m, eps, dt, S)
     assert max(rel(host(xd), xo), rel(host(vd), vo), rel(host(acc), ao)) <= 1e-12
+
+
+@pytest.mark.parametrize("prec", ("f64", "f32", "mix_acc64", "mix_tilec"))
+@pytest.mark.parametrize("n", (1, 3, 64, 255, 257, 1000, 2049, 6000, 6001, 12287))
+def test_adjoint_passes(prec, n):
+    """The entry pass and a walked-back step (which also sums the force) of
+    small sets, against the oracle: the FP32 pair arithmetic's bar on sums that
+    cancel is 1e-4, FP64's 1e-12, and on top the j = i term, m_i lam_i - m_i
+    lam_i formed with one FMA: the rounding of one product (half an ulp of
+    m_i lam_i) times eps^-3, which few particles do not outweigh (two FP64
+    particles: 8e-12 of J^T lam)."""
+    x, v, m = plummer_sphere(n, 910 + n % 13)
+    m = m * np.random.default_rng(n).uniform(0.5, 1.5, size=n)
+    eps, dt = 2.0 ** -6, 2.0 ** -8
+    xd, vd, md = to_dev(x, np.zeros_like(x), m, prec)
+    lam = np.random.default_rng(n + 1).normal(size=(3, n))
+    idx = np.unique(np.linspace(0, n - 1, min(n, 300)).astype(np.int64))
+    bar = 1e-12 if prec == "f64" else 1e-4
+    acc = nb.accel(xd, md, eps, prec=prec)
+    ulp = 2.0 ** -53 if prec == "f64" else 2.0 ** -24
+    self_term = ulp * np.linalg.norm((host(md) * lam)[:, idx]) / eps ** 3
+    lx = torch.zeros_like(xd)
+    lv = torch.tensor(lam, dtype=xd.dtype, device=DEV)
+    lm = torch.zeros(n, dtype=torch.float64, device=DEV)
+    nb.step_adjoint(xd, vd, md, acc, lx, lv, lm, eps, dt, 0, prec=prec, entry_half=True)
+    for walked in (False, True):
+        if walked:
+            lx.zero_()
+            lm.zero_()
+            nb.step_adjoint(xd, vd, md, acc, lx, lv, lm, eps, dt, 1, prec=prec)
+            ao = oracle.accel_sampled(host(xd), host(md), eps, idx)
+            assert rel(host(acc)[:, idx], ao) <= TOL[prec]
+        jt, gt = oracle.vjp_sampled(host(xd), host(md), host(lv), eps, idx)
+        ex = np.linalg.norm(host(lx)[:, idx] / (0.5 * dt) - jt)
+        assert ex <= bar * np.linalg.norm(jt) + self_term
+        assert rel(host(lm)[idx], 0.5 * dt * gt) <= bar
