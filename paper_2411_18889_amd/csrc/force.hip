@@ -237,13 +237,19 @@ __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int
 // a few pairs per lane; the lanes' sums meet in LDS, 16 lanes a sum, and the
 // workgroup finishes its sinks: one launch and no partials where the split
 // ranges take two (FP64, 1024 particles: 6.8 us of the pair kernel's latency
-// and 4.2 of the reduction's; 5.9 us a leapfrog step so). For the policies whose sums may be regrouped:
-// FP64, FP32 terms summed in FP64, plain FP32 (one FP32 sum per lane, the
+// and 4.2 of the reduction's; 5.7 us a leapfrog step so). For the policies whose
+// sums may be regrouped: FP64, FP32 terms summed in FP64, plain FP32 (one FP32 sum per lane, the
 // lanes' sums added in FP64). The leapfrog's drift goes to another array,
-// since other workgroups still read the positions.
-constexpr int LB = 256, LS = 4;
+// since other workgroups still read the positions. Up to 3072 sinks (768
+// workgroups, so fewer than 3 waves per SIMD with 256 lanes) 512 lanes, which
+// halve a lane's chain: us per leapfrog step with 256 and with 512 lanes,
+//            500        1024       2000       3000        4001        6000
+//   FP64     5.7, 5.2   6.1, 5.7   8.2, 8.0   12.0, 11.7  16.6, 16.6  32.2, 33.0
+//   FP32     6.7, 6.7   5.1, 4.9   6.6, 6.2   7.9, 7.9    10.4, 11.3  16.5, 16.9
+// (not for the policy with a block origin, which is that of 256 sinks).
+constexpr int LS = 4;
 
-template <class Pol, bool POT>
+template <class Pol, bool POT, int LB>
 __global__ __launch_bounds__(LB) void force_lanes_kernel(ForceArgs<Pol> a) {
     using calc_t = typename Pol::calc_t;
     using sum_t = typename Pol::sum_t;
@@ -255,6 +261,7 @@ __global__ __launch_bounds__(LB) void force_lanes_kernel(ForceArgs<Pol> a) {
     // the origin of the one-sided kernel's 256-sink workgroups
     double ox = 0.0, oy = 0.0, oz = 0.0;
     if constexpr (Pol::origin) {
+        static_assert(LB == 256);
         __shared__ double org[LB / 64][3];
         const int b0 = i0 / LB * LB, i = b0 + tid;
         const bool ok = i < a.ni;
@@ -381,8 +388,14 @@ hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_
             if (a.tail.x == a.xi) a.tail.x = nullptr;
             if (drifted) *drifted = a.tail.x != nullptr;
             a.part = nullptr;
-            hipLaunchKernelGGL((force_lanes_kernel<Pol, POT>), dim3((a.ni + LS - 1) / LS), dim3(LB), 0,
-                               stream, a);
+            const dim3 grid((a.ni + LS - 1) / LS);
+            if constexpr (!Pol::origin) {
+                if (sh.block == 512) {
+                    hipLaunchKernelGGL((force_lanes_kernel<Pol, POT, 512>), grid, dim3(512), 0, stream, a);
+                    return hipGetLastError();
+                }
+            }
+            hipLaunchKernelGGL((force_lanes_kernel<Pol, POT, 256>), grid, dim3(256), 0, stream, a);
             return hipGetLastError();
         }
     }
@@ -448,8 +461,8 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     // may be regrouped, as long as a lane has few sources: us per leapfrog
     // step against the split ranges below, measured on MI355X,
     //            1024        4001         8000         12000
-    //   FP64     5.9, 10.0   17.4, 24.2   49.5, 58.0   104.8, 112.2
-    //   FP32     5.4, 13.2   10.1, 14.6   24.2, 29.7   47.4, 60.6
+    //   FP64     5.7, 10.0   17.4, 24.2   49.5, 58.0   104.8, 112.2
+    //   FP32     4.9, 13.2   10.1, 14.6   24.2, 29.7   47.4, 60.6
     //   acc64    6.6, 16.7   17.7, 18.7   44.4, 41.7   88.2, 86.4
     // so up to 6000 sources for FP64 sums of FP32 terms, whose lanes carry
     // the longest chain, and for few FP64 sinks, where a lane's sources are
@@ -458,7 +471,8 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     const bool regroup = prec == NB_F64 || prec == NB_F32 || prec == NB_MIX_ACC64;
     const int64_t most = prec == NB_MIX_ACC64 || (prec == NB_F64 && ni < 512) ? 6000 : 12287;
     if (pick == Pick::Best && regroup && ni <= 12287 && nj <= most) {
-        Shape s{LS, LB, LB};
+        const int lanes = prec != NB_MIX_ACC64 && ni <= 3072 && nj > 256 ? 512 : 256;
+        Shape s{LS, lanes, lanes};
         s.lanes = true;
         return s;
     }

@@ -185,3 +185,21 @@ def test_adjoint_passes(prec, n):
         ex = np.linalg.norm(host(lx)[:, idx] / (0.5 * dt) - jt)
         assert ex <= bar * np.linalg.norm(jt) + self_term
         assert rel(host(lm)[idx], 0.5 * dt * gt) <= bar
+
+
+@pytest.mark.parametrize("ni,nj", [(3072, 3072), (3073, 3073), (3072, 257), (3071, 256), (5, 511),
+                                   (6, 513), (1, 12287)])
+@pytest.mark.parametrize("prec", ("f64", "f32", "mix_acc64"))
+def test_lane_counts(prec, ni, nj):
+    """256 and 512 lanes a workgroup, on both sides of the bounds between them,
+    with and without the potential."""
+    xj, v, m = plummer_sphere(nj, 41)
+    xi = xj if ni == nj else plummer_sphere(ni, 42)[0] + 0.01
+    xjd, _, md = to_dev(xj, v, m, prec)
+    xid = torch.tensor(xi, dtype=xjd.dtype, device=DEV)
+    sep = {} if ni == nj else {"xj": xjd}
+    ref, pref = oracle.accel(host(xid), host(md), 2.0 ** -6, potential=True,
+                             **({} if ni == nj else {"xj": host(xjd)}))
+    a, p = nb.accel(xid, md, 2.0 ** -6, prec=prec, potential=True, **sep)
+    assert rel(host(a), ref) <= TOL[prec] and rel(host(p), pref) <= TOL[prec]
+    assert rel(host(nb.accel(xid, md, 2.0 ** -6, prec=prec, **sep)), ref) <= TOL[prec]
