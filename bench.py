@@ -144,8 +144,8 @@ KERNEL_SOURCES = {"force_kernel": ["common.h", "force.hip"],
                   "force_sym_kernel": ["common.h", "force_sym.hip"],
                   "adjoint_kernel": ["common.h", "adjoint.hip"],
                   "adjoint_sym_kernel": ["common.h", "adjoint_sym.hip", "adjoint_sym_pairs.h",
-                                         "adjoint_sym_entry.hip"],
-                  "diffusion_kernel4": ["common.h", "diffusion.hip"]}
+                                         "adjoint_sym_entry.hip", "adjoint_sym_group.hip"],
+                  "diffusion_rows_kernel": ["common.h", "diffusion.hip"]}
 
 
 def gpu_clocks():
@@ -304,11 +304,11 @@ def bench_diffusion(args):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
         "data": "synthetic: seeded uniform field",
         "config": {"workload": args.workload, "grid": [n, n, n], **prm},
-        "roofline": {"kernel": "diffusion_kernel4", "bound": "hbm",
+        "roofline": {"kernel": "diffusion_rows_kernel", "bound": "hbm",
                      "achieved": DIFF_BYTES_PER_POINT * pts / (k_ms * 1e-3) / 1e9,
                      "peak": HBM_PEAK / 1e9, "unit": "GB/s",
                      "frac": DIFF_BYTES_PER_POINT * pts / (k_ms * 1e-3) / HBM_PEAK,
-                     "traffic": hbm_traffic("diffusion_kernel4", args.workload),
+                     "traffic": hbm_traffic("diffusion_rows_kernel", args.workload),
                      "bytes_per_point": DIFF_BYTES_PER_POINT, "avg_launch_ms": k_ms},
         "gflops": DIFF_FLOP_PER_POINT * pts / (ms * 1e-3) / 1e9,
         "paper_convention_GBps": 32 * pts / (ms * 1e-3) / 1e9,
@@ -317,13 +317,17 @@ def bench_diffusion(args):
     print(json.dumps(out), flush=True)
 
 
-# kernel families whose HBM traffic is summarised: the pair kernel and its
+# kernel families whose HBM traffic is summarised: the pair kernels of the
+# pass (the family's and those that take its place for small sets) and its
 # fold (finishing) kernel, per pass
-TRAFFIC_KERNELS = {"force_sym_kernel": ("force_sym_kernel", "force_sym_finish_kernel"),
-                   "adjoint_sym_kernel": ("adjoint_sym_kernel", "adjoint_sym_finish_kernel"),
-                   "force_kernel": ("force_kernel", "force_reduce_kernel"),
-                   "adjoint_kernel": ("adjoint_kernel", "adjoint_reduce_kernel"),
-                   "diffusion_kernel4": ("diffusion_kernel4",)}
+TRAFFIC_KERNELS = {"force_sym_kernel": ("force_sym_kernel", "force_group_kernel",
+                                        "force_sym_finish_kernel"),
+                   "adjoint_sym_kernel": ("adjoint_sym_kernel", "adjoint_group_kernel",
+                                          "adjoint_sym_finish_kernel"),
+                   "force_kernel": ("force_kernel", "force_lanes_kernel", "force_reduce_kernel"),
+                   "adjoint_kernel": ("adjoint_kernel", "adjoint_lanes_kernel",
+                                      "adjoint_reduce_kernel"),
+                   "diffusion_rows_kernel": ("diffusion_rows_kernel",)}
 
 
 def _kernel_base(name):
@@ -387,10 +391,11 @@ def traffic_summary(args):
     for fam, names in TRAFFIC_KERNELS.items():
         fk = sum(v for k, v in fetch if _kernel_base(k) in names)
         wk = sum(v for k, v in write if _kernel_base(k) in names)
-        nd = sum(1 for k, _ in fetch if _kernel_base(k) == fam)
+        pair = [k for k in names if not k.endswith(("_finish_kernel", "_reduce_kernel"))]
+        nd = sum(1 for k, _ in fetch if _kernel_base(k) in pair)
         if nd == 0:
             continue
-        if fam == "diffusion_kernel4":
+        if fam == "diffusion_rows_kernel":
             passes = nd
         out["%s@%s" % (fam, args.workload)] = {
             "source_sha256": kernel_source_hash(fam),
@@ -399,7 +404,7 @@ def traffic_summary(args):
             "write_bytes_per_pass": wk * 1024.0 * w_factor / passes,
             "pair_kernel_dispatches": nd, "passes": passes,
             "counter_folders": list(args.traffic_from),
-            **({} if fam == "diffusion_kernel4" else {"rollout": args.rollout})}
+            **({} if fam == "diffusion_rows_kernel" else {"rollout": args.rollout})}
     path = args.traffic_out
     old = {}
     if os.path.exists(path):

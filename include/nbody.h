@@ -242,8 +242,8 @@ int nbody_accel_ex(int64_t ni, const void *xi, int64_t nj, const void *xj,
  *   ws         workspace of nbody_workspace_size(NB_OP_STEP, n, prec) bytes
  *   flags      NB_ACC_VALID, NB_GRAPH
  *
- * NB_GRAPH: the 2 nsteps (+1) launches of the loop are recorded once into a
- * HIP graph on a capture stream owned by the library, instantiated, and
+ * NB_GRAPH: the kernel launches of the loop (one to three per step, no copies
+ * and no fills) are recorded once into a HIP graph on a capture stream owned by the library, instantiated, and
  * launched on `stream`; a later call with the same arguments (device,
  * pointers, sizes, eps, G, dt, nsteps, prec, flags) launches the cached
  * graph again, which saves the per-launch host cost when n is small. The
@@ -354,7 +354,11 @@ int nbody_profile_end(nb_profile *out);
  * more launches. The size asked for holds every partial up to 4 GiB of them,
  * else the running sums and 4 GiB (or one block row, if more) per band; a
  * call rejects a workspace that cannot hold the running sums and one block
- * row (NB_EWORKSPACE), and uses no more than every partial at once. */
+ * row (NB_EWORKSPACE), and uses no more than every partial at once.
+ * The one-sided passes of small sets take less as well: with less than the
+ * size asked for they run in fewer, longer source ranges (the same sums in
+ * another grouping), down to the least size they accept (NB_EWORKSPACE
+ * below it). */
 size_t nbody_workspace_size(int op, int64_t n, int prec);
 
 /* The workspace bytes one call asks for. op NB_OP_ACCEL: nbody_accel

@@ -20,8 +20,10 @@
 // 34 VALU + 1 rsqrt.
 //
 // Tiling, j-split, the origin of the pair arithmetic in the mixed policies
-// and the fixed-order split reduction are as in the force kernel; the LDS record of a source is (x, y, z, m) and (lam_x, lam_y,
-// lam_z, 0).
+// and the fixed-order split reduction are as in the force kernel, and so is
+// the kernel with the sources on the lanes for the smallest sets
+// (adjoint_lanes_kernel); the LDS record of a source is (x, y, z, m) and
+// (lam_x, lam_y, lam_z, 0).
 #include <algorithm>
 
 #include "common.h"

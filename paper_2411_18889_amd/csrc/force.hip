@@ -17,7 +17,9 @@
 //    dense contraction;
 //  * small N: the source range is split over gridDim.y workgroups (j-split).
 //    Each writes its FP64 partial sums to the workspace and a second kernel
-//    adds them in a fixed order: no atomics, bitwise reproducible;
+//    adds them in a fixed order: no atomics, bitwise reproducible; for the
+//    policies whose sums may be regrouped the smallest sets put the sources
+//    on the lanes instead (force_lanes_kernel, one launch);
 //  * the sum over sources includes j = i, which adds exactly 0 to a_i (d = 0)
 //    and m_i / eps to the potential sum; that term is removed at the end.
 #include <algorithm>

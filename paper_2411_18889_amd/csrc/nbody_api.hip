@@ -283,8 +283,6 @@ size_t adjoint_partials_need(int prec, const SymShape& sym, const Shape& sh, int
     }
     return sh.split > 1 ? adjoint_partials_bytes(sh, n) : 0;
 }
-// (a call of the kernel that keeps its sums on the lanes needs the scratch that
-// the other kernel would, as the force passes)
 
 }  // namespace
 
