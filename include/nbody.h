@@ -387,7 +387,10 @@ size_t nbody_pass_workspace_size(int op, int64_t ni, int64_t nj, int prec, int s
  * 1024 at every n; the partials are written and folded in bands of the
  * workspace).
  * symmetric = 0: the one-sided kernel in the shape (i_per_lane, block,
- * split).
+ * split); for the small sets that run with the sources on the lanes
+ * (NB_F64, NB_F32, NB_MIX_ACC64), the shape that stands in for it where the
+ * workspace is smaller. The shape is one that nb_launch takes, and
+ * workspace_bytes holds its partials.
  */
 typedef struct nb_pass_info {
     int32_t symmetric;

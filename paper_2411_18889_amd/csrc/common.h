@@ -289,10 +289,10 @@ inline int64_t short_tile_ranges(int64_t nj, int block, int64_t waves, int64_t m
     return (tiles + per - 1) / per;
 }
 
-// Library choice of shape for ni sinks, nj sources: of all kernels, of the
-// kernel with split ranges, or of that the shape with the smaller workspace,
-// which a call takes when the first one's does not fit.
-enum class Pick { Best, Split, Least };
+// Library choice of shape for ni sinks, nj sources: of all kernels, or the
+// split ranges with the smaller workspace, which a call takes when the first
+// one's does not fit and whose fields an explicit shape leaves as they are.
+enum class Pick { Best, Least };
 Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick = Pick::Best);
 Shape choose_adjoint_shape(int prec, int64_t n, Pick pick = Pick::Best);
 // Shapes the one-sided force / adjoint kernels are built for.

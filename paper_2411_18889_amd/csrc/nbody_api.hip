@@ -240,7 +240,7 @@ int sym_from_launch(const nb_launch& l, SymShape lib, SymShape* out) {
 int resolve_accel(int prec, int64_t ni, int64_t nj, bool self_set, bool pot,
                   const nb_launch* launch, SymShape* sym, Shape* sh, Shape* least) {
     *sym = (self_set && !launch) ? choose_sym_shape(prec, ni, pot) : SymShape{0, 0};
-    *sh = choose_force_shape(prec, ni, nj, launch ? Pick::Split : Pick::Best);
+    *sh = choose_force_shape(prec, ni, nj, launch ? Pick::Least : Pick::Best);
     *least = choose_force_shape(prec, ni, nj, Pick::Least);
     if (!launch) return NB_OK;
     if (launch->symmetric) {
@@ -260,7 +260,7 @@ int resolve_accel(int prec, int64_t ni, int64_t nj, bool self_set, bool pot,
 int resolve_adjoint(int prec, int64_t n, const nb_launch* launch, SymShape* sym, Shape* sh,
                     Shape* least) {
     *sym = choose_adjoint_sym_shape(prec, n);
-    *sh = choose_adjoint_shape(prec, n, launch ? Pick::Split : Pick::Best);
+    *sh = choose_adjoint_shape(prec, n, launch ? Pick::Least : Pick::Best);
     *least = choose_adjoint_shape(prec, n, Pick::Least);
     if (!launch) return NB_OK;
     if (launch->symmetric) {
@@ -773,6 +773,11 @@ int nbody_pass_info(int op, int64_t n, int prec, nb_pass_info* out) {
     } else {
         return NB_EINVAL;
     }
+    // the sources on the lanes are no shape of nb_launch: report the ranges
+    // that a call with an explicit shape or a smaller workspace runs
+    if (sh.lanes)
+        sh = op == NB_OP_STEP ? choose_force_shape(prec, n, n, Pick::Least)
+                              : choose_adjoint_shape(prec, n, Pick::Least);
     if (sym.waves) {
         r.symmetric = 1;
         r.block = sym.waves * 64;

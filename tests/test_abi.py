@@ -449,3 +449,14 @@ def test_explicit_pass_shapes_validated(L):
     # the library's own shapes agree with nbody_workspace_size
     assert q(2, 1 << 20, 1 << 20, TILEC, 1, 0, None) == L.nbody_workspace_size(2, 1 << 20, TILEC)
     assert q(0, 1 << 20, 1 << 20, TILEC, 1, 0, None) == L.nbody_workspace_size(1, 1 << 20, TILEC)
+
+
+@pytest.mark.parametrize("n", (64, 700, 1024, 3072, 5003, 6001, 12287))
+def test_unset_launch_fields_fit_the_workspace(L, n):
+    """An explicit one-sided shape whose fields are left to the library needs
+    no more than what the operation asks for."""
+    for prec in range(6):
+        for op, size in ((0, L.nbody_workspace_size(1, n, prec)), (2, L.nbody_workspace_size(2, n, prec))):
+            for shape in ((0, 0, 0, 0), (1, 0, 0, 0), (0, 64, 0, 0), (0, 128, 0, 0), (0, 256, 0, 0)):
+                ln = nb_launch(*shape)
+                assert L.nbody_pass_workspace_size(op, n, n, prec, 1, 0, ctypes.byref(ln)) <= size

@@ -203,3 +203,31 @@ def test_lane_counts(prec, ni, nj):
     a, p = nb.accel(xid, md, 2.0 ** -6, prec=prec, potential=True, **sep)
     assert rel(host(a), ref) <= TOL[prec] and rel(host(p), pref) <= TOL[prec]
     assert rel(host(nb.accel(xid, md, 2.0 ** -6, prec=prec, **sep)), ref) <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("n", (1, 64, 700, 2048, 3072, 6001, 12287))
+def test_reported_shape_is_taken(prec, n):
+    """The shape and the workspace that pass_info reports make a call of the
+    explicit shape, force and adjoint."""
+    x, v, m = plummer_sphere(n, 43)
+    xd, vd, md = to_dev(x, v, m, prec)
+    eps = 2.0 ** -6
+    ref = oracle.accel(host(xd), host(md), eps)
+    for op in (1, 2):
+        info = nb.pass_info(op, n, prec)
+        launch = {k: info[k] for k in ("i_per_lane", "block", "split", "symmetric")}
+        ws = torch.empty(info["workspace_bytes"], dtype=torch.uint8, device=DEV)
+        if op == 1:
+            a = nb.accel(xd, md, eps, prec=prec, launch=launch, workspace=ws)
+        else:
+            xs, vs, a = xd.clone(), torch.zeros_like(vd), nb.accel(xd, md, eps, prec=prec)
+            lx, lv = torch.zeros_like(xd), vd.clone()
+            lm = torch.zeros(n, dtype=torch.float64, device=DEV)
+            nb.step_adjoint(xs, vs, md, a, lx, lv, lm, eps, 2.0 ** -8, 1, prec=prec, launch=launch,
+                            workspace=ws)
+            ref = oracle.accel(host(xs), host(md), eps)
+        if n > 1:
+            assert rel(host(a), ref) <= TOL[prec]
+        else:
+            assert float(a.abs().max()) == 0.0
