@@ -450,6 +450,8 @@ size_t force_partials_bytes(const Shape& s, int64_t ni) {
 //    ni <= waves * 64 * ipl, so split * ni < 2^23 * ipl <= 2^24 for the
 //    shapes with ipl <= 2; the shape with ipl = 4 serves fewer than 65536
 //    sinks, so there split * ni <= 256 * 65536 = 2^24 as well.
+// The tile-long ranges of few waves (6144 at most, so split * ni < 2^20) stay
+// below it; a call whose workspace is smaller takes the other ranges.
 size_t force_partials_bound(int64_t n) {
     const int64_t short_ranges = std::min<int64_t>(64, std::min<int64_t>(n, 16383) / 64);
     const int64_t split = std::min<int64_t>(256, std::max<int64_t>(n / 512, short_ranges));
