@@ -335,21 +335,36 @@ struct TailArgs {
     explicit TailArgs(const StepTail& t)
         : v(static_cast<T*>(t.v)), store(static_cast<T*>(t.store)),
           x(static_cast<T*>(t.drift_x)), close(t.close), h(T(t.h)), dt(T(t.dt)) {}
-    // component k of 3n, at pos, with the acceleration as stored; the same
-    // FMAs as the kick-drift kernel's
-    __device__ __forceinline__ void apply(size_t k, size_t n3, const T* pos, T a) const {
-        T vk = v[k];
+    // what component k of 3n needs, which a kernel loads ahead of its sums
+    struct In {
+        T v = T(0), p = T(0);
+    };
+    __device__ __forceinline__ In load(size_t k, const T* pos) const {
+        In in;
+        if (v) {
+            in.v = v[k];
+            if (store || x) in.p = pos[k];
+        }
+        return in;
+    }
+    // component k of 3n, with the acceleration as stored; the same FMAs as
+    // the kick-drift kernel's
+    __device__ __forceinline__ void apply(size_t k, size_t n3, const In& in, T a) const {
+        T vk = in.v;
         if (close) vk = fmat(h, a, vk);
         if (store) {
-            store[k] = pos[k];
+            store[k] = in.p;
             store[n3 + k] = vk;
             store[2 * n3 + k] = a;
         }
         if (x) {
             vk = fmat(h, a, vk);
-            x[k] = fmat(dt, vk, pos[k]);
+            x[k] = fmat(dt, vk, in.p);
         }
         v[k] = vk;
+    }
+    __device__ __forceinline__ void apply(size_t k, size_t n3, const T* pos, T a) const {
+        apply(k, n3, load(k, pos), a);
     }
 };
 

@@ -51,35 +51,41 @@ struct ForceArgs {
     double* part;         // [nsplit][NQ][ni] FP64 partial sums, or nullptr
 };
 
-// TAIL: also the leapfrog's tail. The pair kernel leaves it out (it costs
+// The potential of sink i from its sum sp.
+template <class Pol>
+__device__ __forceinline__ void finish_pot(const ForceArgs<Pol>& a, int i, double sp) {
+    using calc_t = typename Pol::calc_t;
+    double self = 0.0;
+    if (a.self_pot) {
+        // the j = i term exactly as the pair loop added it
+        typename Pol::sum_t t;
+        t.init();
+        t.add_fma(calc_t(a.mi[i]), rsqrt_pair(a.eps2));
+        self = t.total();
+    }
+    a.pot[i] = typename Pol::pos_t(-a.G * (sp - self));
+}
+
+// TAIL: also the leapfrog's tail, from what tail.load gave for the three
+// components. The pair kernel leaves it out (it costs
 // registers, and with them waves, there: 46 -> 91 VGPRs and 20 % with Kahan
 // sums at 262144).
 template <class Pol, bool POT, bool TAIL>
 __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, double sx, double sy,
-                                            double sz, double sp) {
+                                            double sz, double sp,
+                                            const typename TailArgs<typename Pol::pos_t>::In* in = nullptr) {
     using pos_t = typename Pol::pos_t;
-    using calc_t = typename Pol::calc_t;
     const pos_t ax = pos_t(a.G * sx), ay = pos_t(a.G * sy), az = pos_t(a.G * sz);
     a.ax[i] = ax;
     a.ay[i] = ay;
     a.az[i] = az;
     if (TAIL && a.tail.v) {
         const size_t n = a.ni, n3 = 3 * n;
-        a.tail.apply(i, n3, a.xi, ax);
-        a.tail.apply(n + i, n3, a.xi, ay);
-        a.tail.apply(2 * n + i, n3, a.xi, az);
+        a.tail.apply(i, n3, in[0], ax);
+        a.tail.apply(n + i, n3, in[1], ay);
+        a.tail.apply(2 * n + i, n3, in[2], az);
     }
-    if (POT) {
-        double self = 0.0;
-        if (a.self_pot) {
-            // the j = i term exactly as the pair loop added it
-            typename Pol::sum_t t;
-            t.init();
-            t.add_fma(calc_t(a.mi[i]), rsqrt_pair(a.eps2));
-            self = t.total();
-        }
-        a.pot[i] = pos_t(-a.G * (sp - self));
-    }
+    if (POT) finish_pot(a, i, sp);
 }
 
 // FEW: built for few waves in flight (kFewWaves): 5003 particles, tile-
@@ -202,6 +208,10 @@ __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int
     const int i = W > 1 ? blockIdx.x * 64 + lane : blockIdx.x * 256 + threadIdx.x;
     const size_t stride = (size_t)NQ * a.ni;
     double s[N] = {};
+    typename TailArgs<typename Pol::pos_t>::In in[3];  // in flight with the partials
+    if (!POT && g == 0 && i < a.ni)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) in[c] = a.tail.load(c * (size_t)a.ni + i, a.xi);
     if (i < a.ni) {
         for (int r0 = g; r0 < nsplit; r0 += W * 8) {
             double t[8][N];
@@ -230,7 +240,7 @@ __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int
             for (int c = 0; c < N; ++c) s[c] += other[v][c][lane];
     }
     if (i >= a.ni) return;
-    finish_sink<Pol, POT, true>(a, i, s[0], s[1], s[2], POT ? s[N - 1] : 0.0);
+    finish_sink<Pol, POT, !POT>(a, i, s[0], s[1], s[2], POT ? s[N - 1] : 0.0, in);
 }
 
 // Sources on the lanes: a workgroup of LB lanes owns LS sinks and each lane
@@ -239,12 +249,13 @@ __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int
 // a few pairs per lane; the lanes' sums meet in LDS, 16 lanes a sum, and the
 // workgroup finishes its sinks: one launch and no partials where the split
 // ranges take two (FP64, 1024 particles: 6.8 us of the pair kernel's latency
-// and 4.2 of the reduction's; 5.7 us a leapfrog step so). For the policies whose
+// and 4.2 of the reduction's; 4.7 us a leapfrog step so). For the policies whose
 // sums may be regrouped: FP64, FP32 terms summed in FP64, plain FP32 (one FP32 sum per lane, the
 // lanes' sums added in FP64). The leapfrog's drift goes to another array,
 // since other workgroups still read the positions. Up to 3072 sinks (768
 // workgroups, so fewer than 3 waves per SIMD with 256 lanes) 512 lanes, which
-// halve a lane's chain: us per leapfrog step with 256 and with 512 lanes,
+// halve a lane's chain: us per leapfrog step with 256 and with 512 lanes
+// (both before the tail's loads went ahead of the sums, which take 1 off),
 //            500        1024       2000       3000        4001        6000
 //   FP64     5.7, 5.2   6.1, 5.7   8.2, 8.0   12.0, 11.7  16.6, 16.6  32.2, 33.0
 //   FP32     6.7, 6.7   5.1, 4.9   6.6, 6.2   7.9, 7.9    10.4, 11.3  16.5, 16.9
@@ -257,9 +268,18 @@ __global__ __launch_bounds__(LB) void force_lanes_kernel(ForceArgs<Pol> a) {
     using sum_t = typename Pol::sum_t;
     constexpr int N = POT ? 4 : 3, V = LS * N;
     __shared__ double lsum[V][LB + 1];
-    __shared__ double tot[LS][N];
     const int tid = threadIdx.x;
     const int i0 = blockIdx.x * LS;
+    // 16 lanes add sum v, component (or potential) qc of sink iv, and the
+    // first of them finishes it; its tail's loads go ahead of everything (one
+    // thread a sink, three components one after another with their loads
+    // behind the sums, was 1.0-1.4 us a leapfrog step longer: FP64 1024 5.9 ->
+    // 4.7, 3000 13.0 -> 10.9, FP32 2000 6.4 -> 5.3)
+    const int v = tid >> 4, l = tid & 15, iv = i0 + v / N, qc = v % N;
+    const bool last = v < V && l == 0 && iv < a.ni;
+    const size_t n = a.ni, kc = qc * n + iv;
+    typename TailArgs<typename Pol::pos_t>::In in;
+    if (!POT && last) in = a.tail.load(kc, a.xi);  // (no leapfrog asks for the potential)
     // the origin of the one-sided kernel's 256-sink workgroups
     double ox = 0.0, oy = 0.0, oz = 0.0;
     if constexpr (Pol::origin) {
@@ -303,19 +323,20 @@ __global__ __launch_bounds__(LB) void force_lanes_kernel(ForceArgs<Pol> a) {
 #pragma unroll
         for (int c = 0; c < N; ++c) lsum[k * N + c][tid] = s[k][c].total();
     __syncthreads();
-    const int v = tid >> 4, l = tid & 15;  // 16 lanes add sum v
-    if (v < V) {
-        double t = 0.0;
+    if (v >= V) return;
+    double t = 0.0;
 #pragma unroll
-        for (int q = 0; q < LB / 16; ++q) t += lsum[v][q * 16 + l];
+    for (int q = 0; q < LB / 16; ++q) t += lsum[v][q * 16 + l];
 #pragma unroll
-        for (int mask = 8; mask >= 1; mask >>= 1) t += __shfl_xor(t, mask, 64);
-        if (l == 0) tot[v / N][v % N] = t;
+    for (int mask = 8; mask >= 1; mask >>= 1) t += __shfl_xor(t, mask, 64);
+    if (!last) return;
+    if (POT && qc == 3) {
+        finish_pot(a, iv, t);
+        return;
     }
-    __syncthreads();
-    if (tid < LS && i0 + tid < a.ni)
-        finish_sink<Pol, POT, true>(a, i0 + tid, tot[tid][0], tot[tid][1], tot[tid][2],
-                                    POT ? tot[tid][N - 1] : 0.0);
+    const typename Pol::pos_t acc = typename Pol::pos_t(a.G * t);
+    a.ax[kc] = acc;
+    if (!POT && a.tail.v) a.tail.apply(kc, 3 * n, in, acc);
 }
 
 // The leapfrog's tail after a pass in one range, whose workgroups finish their
@@ -465,9 +486,9 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     // may be regrouped, as long as a lane has few sources: us per leapfrog
     // step against the split ranges below, measured on MI355X,
     //            1024        4001         8000         12000
-    //   FP64     5.7, 10.0   17.4, 24.2   49.5, 58.0   104.8, 112.2
-    //   FP32     4.9, 13.2   10.1, 14.6   24.2, 29.7   47.4, 60.6
-    //   acc64    6.6, 16.7   17.7, 18.7   44.4, 41.7   88.2, 86.4
+    //   FP64     4.7, 10.0   15.9, 24.2   49.5, 58.0   104.8, 112.2
+    //   FP32     4.5, 13.2    9.1, 14.6   24.2, 29.7   47.4, 60.6
+    //   acc64    6.0, 16.7   16.0, 18.7   44.4, 41.7   88.2, 86.4
     // so up to 6000 sources for FP64 sums of FP32 terms, whose lanes carry
     // the longest chain, and for few FP64 sinks, where a lane's sources are
     // the whole time (100 against 12000: 15.3, 14.3; 1000: 16.4, 19.7).
