@@ -145,7 +145,7 @@ KERNEL_SOURCES = {"force_kernel": ["common.h", "force.hip"],
                   "adjoint_kernel": ["common.h", "adjoint.hip"],
                   "adjoint_sym_kernel": ["common.h", "adjoint_sym.hip", "adjoint_sym_pairs.h",
                                          "adjoint_sym_entry.hip", "adjoint_sym_group.hip"],
-                  "diffusion_rows_kernel": ["common.h", "diffusion.hip"]}
+                  "diffusion_rows_kernel": ["common.h", "diffusion_rows.h", "diffusion.hip"]}
 
 
 def gpu_clocks():

@@ -22,6 +22,7 @@
 // the row's end (where nz is no multiple of 4 it repeats, with the same
 // values, points its neighbour also writes).
 #include "common.h"
+#include "diffusion_rows.h"
 
 namespace nb {
 
@@ -33,17 +34,14 @@ struct Coef {
 
 typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
 
-constexpr int TPB = 256;
+constexpr int TPB = kDiffLanes;
 
 struct DiffArgs {
     int nx, ny, nz;
     Coef c;
     const float* f;
     float* fn;
-    int ci;              // planes per slab
-    int row_lanes;       // lanes per row
-    int lanes;           // lanes per plane
-    int chunks, blocks;  // workgroups per slab, in all
+    DiffRows g;
 };
 
 __device__ __forceinline__ v4f load4(const float* p) { return *reinterpret_cast<const v4f*>(p); }
@@ -54,26 +52,21 @@ __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
     // contiguous run of the grid, so that rows and planes which neighbouring
     // workgroups share are read into one L2 (256^3: 25.4 -> 22.7 us, 512^3
     // 218 -> 203 us)
-    const int per = (a.blocks + 7) / 8;
+    const int per = (a.g.blocks + 7) / 8;
     const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if (b >= a.blocks) return;
-    const int slab = b / a.chunks;
-    const int t = (b - slab * a.chunks) * TPB + threadIdx.x;
-    if (t >= a.lanes) return;
+    if (b >= a.g.blocks) return;
+    const int slab = b / a.g.chunks;
+    const int t = (b - slab * a.g.chunks) * TPB + threadIdx.x;
+    if (t >= a.g.lanes) return;
 
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const Coef c = a.c;
-    const int lane = threadIdx.x & 63;
-    const int jb = t / a.row_lanes, l = t - jb * a.row_lanes;
+    const int jb = t / a.g.row_lanes;
     const int j0 = jb * R;
-    const int k0 = min(4 * l, nz - 4);
-    const bool kfirst = k0 == 0, klast = k0 + 4 == nz;
-    // lanes whose left / right neighbour point is not at the end of the
-    // adjacent lane's 4: loaded
-    const bool left = !kfirst && (lane == 0 || k0 != 4 * l);
-    const bool right = !klast && (lane == 63 || k0 + 8 > nz);
+    const DiffLane d = diff_lane(t - jb * a.g.row_lanes, nz, threadIdx.x & 63);
+    const int k0 = d.k0;
     const int64_t plane = (int64_t)ny * nz;
-    const int i0 = slab * a.ci, i1 = min(i0 + a.ci, nx);
+    const int i0 = slab * a.g.ci, i1 = min(i0 + a.g.ci, nx);
     int off[R + 2];  // rows j0 - 1 .. j0 + R, clamped into the grid
 #pragma unroll
     for (int r = 0; r < R + 2; ++r) off[r] = min(max(j0 - 1 + r, 0), ny - 1) * nz + k0;
@@ -88,8 +81,8 @@ __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
         prev[r] = load4(pm + off[r + 1]);
         cur[r] = load4(p + off[r + 1]);
         next[r] = load4(pn + off[r + 1]);
-        el[r] = left ? p[off[r + 1] - 1] : 0.f;
-        er[r] = right ? p[off[r + 1] + 4] : 0.f;
+        el[r] = d.left ? p[off[r + 1] - 1] : 0.f;
+        er[r] = d.right ? p[off[r + 1] + 4] : 0.f;
     }
     v4f jm = load4(p + off[0]), jp = load4(p + off[R + 1]);
     for (int i = i0; i < i1; ++i) {
@@ -102,8 +95,8 @@ __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
         const v4f jmn = load4(p1 + off[0]), jpn = load4(p1 + off[R + 1]);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            eln[r] = left ? p1[off[r + 1] - 1] : 0.f;
-            ern[r] = right ? p1[off[r + 1] + 4] : 0.f;
+            eln[r] = d.left ? p1[off[r + 1] - 1] : 0.f;
+            ern[r] = d.right ? p1[off[r + 1] + 4] : 0.f;
         }
         float* o = a.fn + (int64_t)i * plane;
 #pragma unroll
@@ -113,8 +106,8 @@ __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
             float kp = __int_as_float(__builtin_amdgcn_update_dpp(
                 0, __float_as_int(cur[r].x), 0x130, 0xF, 0xF, false));  // lane + 1
             // the ends of the grid have themselves as neighbours
-            km = kfirst ? cur[r].x : (left ? el[r] : km);
-            kp = klast ? cur[r].w : (right ? er[r] : kp);
+            km = d.first ? cur[r].x : (d.left ? el[r] : km);
+            kp = d.last ? cur[r].w : (d.right ? er[r] : kp);
             const v4f up = r < R - 1 ? cur[r < R - 1 ? r + 1 : r] : jp;
             const v4f dn = r > 0 ? cur[r > 0 ? r - 1 : 0] : jm;
             v4f q;
@@ -167,12 +160,8 @@ __global__ __launch_bounds__(TPB) void diffusion_point_kernel(int nx, int ny, in
 
 template <int R>
 hipError_t launch_rows(DiffArgs a, int64_t ci, hipStream_t stream) {
-    a.ci = (int)ci;
-    a.row_lanes = (a.nz + 3) / 4;
-    a.lanes = a.row_lanes * ((a.ny + R - 1) / R);
-    a.chunks = (a.lanes + TPB - 1) / TPB;
-    a.blocks = a.chunks * (int)((a.nx + ci - 1) / ci);
-    hipLaunchKernelGGL((diffusion_rows_kernel<R>), dim3((unsigned)((a.blocks + 7) / 8 * 8)),
+    a.g = diff_rows(a.nx, a.ny, a.nz, R, ci);
+    hipLaunchKernelGGL((diffusion_rows_kernel<R>), dim3((unsigned)((a.g.blocks + 7) / 8 * 8)),
                        dim3(TPB), 0, stream, a);
     return hipGetLastError();
 }

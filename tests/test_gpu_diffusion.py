@@ -80,3 +80,25 @@ def test_ragged_rows(shape):
     ref = oracle.diffusion3d(f.astype(np.float64), **PARAMS)
     assert np.abs(fn.cpu().numpy() - ref).max() <= 1e-6 * np.abs(ref).max()
     assert float(guard[0]) == 7.0 and float(guard[-1]) == 7.0
+
+
+@pytest.mark.parametrize("nz", (2 ** 31 - 1, 2 ** 31 - 3, 2 ** 31 - 4))
+def test_longest_rows(nz):
+    """One row of as many points as a grid may have, where 4 points a lane end
+    past an int: every point against the update of the same FP32 values in
+    FP64 (in pieces); j and i have no neighbours, so theirs are the point
+    itself."""
+    f = torch.empty(nz, dtype=torch.float32, device=DEV)
+    torch.manual_seed(nz % 1000)
+    f.uniform_(-1, 1)
+    fn = nb.api.diffusion3d_step(f.view(1, 1, nz), **PARAMS).view(nz)
+    ct = PARAMS["kappa"] * PARAMS["dt"] / PARAMS["dz"] ** 2
+    for k0 in range(0, nz, 1 << 27):
+        k1 = min(nz, k0 + (1 << 27))
+        c = f[k0:k1].double()
+        ref = c * (1 - 2 * ct)
+        ref[1:] += ct * c[:-1]
+        ref[:-1] += ct * c[1:]
+        ref[0] += ct * f[max(k0 - 1, 0)].double()
+        ref[-1] += ct * f[min(k1, nz - 1)].double()
+        assert float((fn[k0:k1] - ref).abs().max()) <= 1e-6
