@@ -338,8 +338,7 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
     rec[g][0][lane + 64] = p;
     rec[g][1][lane] = l;
     rec[g][1][lane + 64] = l;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 
     const V4* rowp = rec[g][0] + lane;
     const V4* rowl = rec[g][1] + lane;

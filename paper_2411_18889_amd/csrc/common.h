@@ -117,6 +117,15 @@ __device__ __forceinline__ double from_next_lane(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// Between a lane's stores to LDS and the reads of them by other lanes of the
+// same wave: the stores stay before it and the reads after it. No instruction:
+// a wave's LDS operations complete in order.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // Origin of the FP32 pair arithmetic in the mixed policies.
 //

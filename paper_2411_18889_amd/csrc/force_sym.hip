@@ -370,8 +370,7 @@ __global__ __launch_bounds__(C * K * 64) void force_group_kernel(SymArgs<Pol> a)
     p.z = jok ? pair_coord<Pol>(qz, oz) : T(0);
     rec[g][lane] = p;
     rec[g][lane + 64] = p;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 
     const V4* row = rec[g] + lane;
     auto steps = [&](auto jside) {
