@@ -460,6 +460,12 @@ size_t force_partials_bytes(const Shape& s, int64_t ni) {
     return (size_t)s.split * NQ * (size_t)ni * sizeof(double);
 }
 
+// Policies whose small passes take ranges as short as one tile: not those
+// that keep a plain or compensated FP32 sum over the range, whose length is
+// part of their arithmetic. And the waves up to which they do, 6 per SIMD.
+static bool tile_ranges(int prec) { return prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN; }
+constexpr int64_t kRangeWaves = 6144;
+
 // Upper bound of force_partials_bytes(choose_force_shape(prec, ni, nj), ni)
 // over every ni, nj <= n (a small sink set against a large source set takes
 // the most ranges). From the rule below:
@@ -471,13 +477,19 @@ size_t force_partials_bytes(const Shape& s, int64_t ni) {
 //    ni <= waves * 64 * ipl, so split * ni < 2^23 * ipl <= 2^24 for the
 //    shapes with ipl <= 2; the shape with ipl = 4 serves fewer than 65536
 //    sinks, so there split * ni <= 256 * 65536 = 2^24 as well.
-// The tile-long ranges of few waves (6144 at most, so split * ni < 2^20) stay
-// below it; a call whose workspace is smaller takes the other ranges.
-size_t force_partials_bound(int64_t n) {
+// and, for the policies with tile-long ranges of few waves (kRangeWaves at
+// most in all, each range 256 sources or more):
+//  * split <= min(256, ceil(n / 256)) and split * waves <= kRangeWaves, where
+//    a wave has 64 * ipl sinks: ipl is 4 at most in FP64, 2 otherwise.
+size_t force_partials_bound(int prec, int64_t n) {
     const int64_t short_ranges = std::min<int64_t>(64, std::min<int64_t>(n, 16383) / 64);
     const int64_t split = std::min<int64_t>(256, std::max<int64_t>(n / 512, short_ranges));
-    if (split <= 1) return 0;
-    const int64_t rows = std::min<int64_t>(split * n, int64_t(1) << 24);  // split * ni
+    int64_t rows = split > 1 ? std::min<int64_t>(split * n, int64_t(1) << 24) : 0;  // split * ni
+    if (tile_ranges(prec)) {
+        const int64_t most = std::min<int64_t>(256, (n + 255) / 256);
+        const int64_t few = std::min<int64_t>(most * n, kRangeWaves * 64 * (prec == NB_F64 ? 4 : 2));
+        if (most > 1) rows = std::max(rows, few);
+    }
     return (size_t)rows * NQ * sizeof(double);
 }
 
@@ -542,9 +554,9 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     // takes 13.7 us instead of 21.9 at 1000 particles and 20.3 instead of
     // 23.8 at 5003 (at 11239 with the potential, 44 ranges of one tile are
     // 2 % slower than 22 of two).
-    if (pick != Pick::Least && prec != NB_MIX_ACC32 && prec != NB_MIX_KAHAN) {
+    if (pick != Pick::Least && tile_ranges(prec)) {
         split = std::max<int64_t>(split_ranges(nj, split, s.block),
-                                  short_tile_ranges(nj, s.block, waves, 6144));
+                                  short_tile_ranges(nj, s.block, waves, kRangeWaves));
     }
     s.split = (int)split;
     return s;

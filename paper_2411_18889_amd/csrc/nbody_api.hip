@@ -732,7 +732,7 @@ size_t nbody_workspace_size(int op, int64_t n, int prec) {
     if (!valid_prec(prec) || n < 1 || n > kMaxN) return 0;
     switch (op) {
     case NB_OP_ACCEL: {  // any ni, nj <= n; either pass, with or without the potential
-        const size_t a = std::max(onesided_ws(prec, n), force_partials_bound(n));
+        const size_t a = std::max(onesided_ws(prec, n), force_partials_bound(prec, n));
         const SymShape s0 = choose_sym_shape(prec, n), s1 = choose_sym_shape(prec, n, true);
         const size_t b = s0.waves ? sym_default_bytes(sym_layout(prec, s0, n)) : 0;
         const size_t c = s1.waves ? sym_default_bytes(sym_layout(prec, s1, n, true)) : 0;

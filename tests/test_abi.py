@@ -460,3 +460,24 @@ def test_unset_launch_fields_fit_the_workspace(L, n):
             for shape in ((0, 0, 0, 0), (1, 0, 0, 0), (0, 64, 0, 0), (0, 128, 0, 0), (0, 256, 0, 0)):
                 ln = nb_launch(*shape)
                 assert L.nbody_pass_workspace_size(op, n, n, prec, 1, 0, ctypes.byref(ln)) <= size
+
+
+def test_documented_accel_workspace_holds_the_library_shape(Lv):
+    """nbody_workspace_size(NB_OP_ACCEL, max(ni, nj)), the size the header
+    names for a call, is no smaller than what nbody_pass_workspace_size asks
+    for any ni, nj up to it, so that a call with it runs the library's shape
+    and not the one with the least scratch."""
+    L = Lv
+    sizes = sorted({64, 255, 256, 257, 511, 1000, 2049, 3071, 3072, 4097, 6001, 9377, 12287, 12288,
+                    12289, 16383, 16384, 16653, 20011, 24577, 30001, 49153, 65535, 65536, 65537,
+                    100003, 1 << 18, (1 << 20) + 1} | set(range(12500, 34000, 1433)))
+    for prec in range(6):
+        for n in sizes + [20522]:
+            w = L.nbody_workspace_size(0, n, prec)
+            for k in [s for s in sizes if s < n] + [n]:
+                for ni, nj in {(k, n), (n, k)}:
+                    for pot in (0, 1):
+                        need = L.nbody_pass_workspace_size(0, ni, nj, prec, 0, pot, None)
+                        assert need <= w, (prec, ni, nj, pot, need, w)
+                        if ni == nj:
+                            assert L.nbody_pass_workspace_size(0, ni, nj, prec, 1, pot, None) <= w
