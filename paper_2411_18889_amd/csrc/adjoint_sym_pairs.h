@@ -261,7 +261,7 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
     constexpr int S = C * K;  // sinks per lane; groups and waves per item
     constexpr int BI = S * 64;
     constexpr int QP = 4;     // quantities exchanged at a time
-    constexpr int CH = Pol::origin ? C : 1;  // source-side chains
+    constexpr int CH = Pol::origin ? C : 1, SEG = Pol::origin ? 1 : C;  // source-side chains
     constexpr size_t rec_b = 2 * S * 128 * sizeof(V4), ex_b = QP * S * S * 64 * sizeof(T);
     __shared__ __align__(16) unsigned char buf[rec_b > ex_b ? rec_b : ex_b];
     V4(*rec)[2][128] = reinterpret_cast<V4(*)[2][128]>(buf);     // per wave
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
         oz = wave_total(cz) * c;
     }
     SumPlain<T> sum[S][NQ];
-    T c[CH][NQ];
+    T c[CH][NQ], home[NQ];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const bool ok = ib + s * 64 < a.n;
@@ -328,9 +328,11 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
         for (int q = 0; q < NQ; ++q) sum[s][q].init();
     }
 #pragma unroll
-    for (int h = 0; h < CH; ++h)
+    for (int q = 0; q < NQ; ++q) {
+        home[q] = T(0);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) c[h][q] = T(0);
+        for (int h = 0; h < CH; ++h) c[h][q] = T(0);
+    }
     p.x = jok ? pair_coord<Pol>(qx, ox) : T(0);
     p.y = jok ? pair_coord<Pol>(qy, oy) : T(0);
     p.z = jok ? pair_coord<Pol>(qz, oz) : T(0);
@@ -342,10 +344,10 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
 
     const V4* rowp = rec[g][0] + lane;
     const V4* rowl = rec[g][1] + lane;
-    auto steps = [&](auto jside) {
+    auto steps = [&](auto jside, int t0, int t1) {
         constexpr bool JSIDE = decltype(jside)::value;
 #pragma unroll 1
-        for (int t = 0; t < 64; ++t) {
+        for (int t = t0; t < t1; ++t) {
             const V4 q = rowp[t];
             const V4 lj = rowl[t];
 #pragma unroll
@@ -361,16 +363,27 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
         }
     };
     if (J * BI + g * 64 < a.n) {
-        if (I != J)
-            steps(std::true_type{});
-        else
-            steps(std::false_type{});
+        if (I == J) {
+            steps(std::false_type{}, 0, 64);
+        } else {
+#pragma unroll 1
+            for (int t1 = 64 / SEG;; t1 += 64 / SEG) {
+                steps(std::true_type{}, t1 - 64 / SEG, t1);
+                if (t1 == 64) break;
+                // after t1 steps the sum of this lane's source is t1 lanes down
+#pragma unroll
+                for (int q = Q0; q < NQ; ++q) {
+                    home[q] += from_lane(c[0][q], (lane - t1) & 63);
+                    c[0][q] = T(0);
+                }
+            }
+        }
     }
     // source side: slot I of particle j
     if (I != J && jok) {
 #pragma unroll
         for (int q = Q0; q < NQ; ++q) {
-            T t = T(0);
+            T t = home[q];
 #pragma unroll
             for (int h = 0; h < CH; ++h) t += c[h][q];
             a.part[a.band.offset(I, q - Q0, j)] = -t;

@@ -117,6 +117,17 @@ __device__ __forceinline__ double from_next_lane(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// Lane l receives the value of lane src (the lane's own number), through the
+// LDS crossbar.
+__device__ __forceinline__ float from_lane(float v, int src) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));
+}
+__device__ __forceinline__ double from_lane(double v, int src) {
+    const int lo = __builtin_amdgcn_ds_bpermute(src << 2, __double2loint(v));
+    const int hi = __builtin_amdgcn_ds_bpermute(src << 2, __double2hiint(v));
+    return __hiloint2double(hi, lo);
+}
+
 // Between a lane's stores to LDS and the reads of them by other lanes of the
 // same wave: the stores stay before it and the reads after it. No instruction:
 // a wave's LDS operations complete in order.

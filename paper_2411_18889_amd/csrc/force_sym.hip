@@ -45,7 +45,8 @@
 //    partials added in FP64), plain FP32 (FP32 state; the i-side a running
 //    FP32 sum over the whole source block; the slots added in FP32: every
 //    sum stays FP32, as the policy asks, only blocked by the third-law
-//    structure) and FP64 (FP64 records, pair arithmetic, source-side sums,
+//    structure; force_group_kernel below sums each 64 sources in FP32 and
+//    joins a block's sums in FP64) and FP64 (FP64 records, pair arithmetic, source-side sums,
 //    partials and slot sums; the source-side sums rotate as two 32-bit
 //    halves). The description above says FP32 where it is the pair type.
 //
@@ -285,7 +286,11 @@ __global__ __launch_bounds__(W * 64) void force_sym_kernel(SymArgs<Pol> a) {
 // against 126 for the kernel above). For the tile-compensated policy the
 // source-side sums stay C chains of K sinks, added in chain order: the same
 // FP32 operations in the same order as above. FP32 and FP64 sum all S sinks in
-// one chain, which takes half or a quarter of the lane rotations.
+// one chain, which takes half or a quarter of the lane rotations, and end it
+// every 64 / C steps: chains of 128 terms, C to a source, as above. (Left to
+// run for the 64 steps, 256 terms, the FP32 mass adjoint of the last eighth of
+// 16384 particles, nearly all source side, was off by 4.7e-7 instead of
+// 2.6e-7.)
 // Against the kernel above, us per pass (with its fold) on MI355X:
 //                    12288         16384         20011         32768
 //   tile-comp. 2 x 2 49.0,  61.0   75.0,  80.5  103, 119
@@ -302,8 +307,8 @@ __global__ __launch_bounds__(C * K * 64) void force_group_kernel(SymArgs<Pol> a)
     constexpr int NQ = P ? 4 : 3;
     constexpr int QP = S <= 4 ? NQ : 1;  // quantities exchanged at a time
     // source-side chains: one for each C of the shape's K sinks where their
-    // FP32 order is part of the policy's results, else one
-    constexpr int CH = Pol::origin ? C : 1;
+    // FP32 order is part of the policy's results, else one, in C stretches
+    constexpr int CH = Pol::origin ? C : 1, SEG = Pol::origin ? 1 : C;
     constexpr size_t rec_b = S * 128 * sizeof(V4), ex_b = QP * S * S * 64 * sizeof(T);
     __shared__ __align__(16) unsigned char buf[rec_b > ex_b ? rec_b : ex_b];
     V4(*rec)[128] = reinterpret_cast<V4(*)[128]>(buf);           // per wave
@@ -351,7 +356,7 @@ __global__ __launch_bounds__(C * K * 64) void force_group_kernel(SymArgs<Pol> a)
         oy = wave_total(cy) * c;
         oz = wave_total(cz) * c;
     }
-    T sum[S][NQ], c[CH][NQ];
+    T sum[S][NQ], c[CH][NQ], home[NQ];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const bool ok = ib + s * 64 < a.n;
@@ -362,9 +367,11 @@ __global__ __launch_bounds__(C * K * 64) void force_group_kernel(SymArgs<Pol> a)
         for (int q = 0; q < NQ; ++q) sum[s][q] = T(0);
     }
 #pragma unroll
-    for (int h = 0; h < CH; ++h)
+    for (int q = 0; q < NQ; ++q) {
+        home[q] = T(0);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) c[h][q] = T(0);
+        for (int h = 0; h < CH; ++h) c[h][q] = T(0);
+    }
     p.x = jok ? pair_coord<Pol>(qx, ox) : T(0);
     p.y = jok ? pair_coord<Pol>(qy, oy) : T(0);
     p.z = jok ? pair_coord<Pol>(qz, oz) : T(0);
@@ -373,10 +380,10 @@ __global__ __launch_bounds__(C * K * 64) void force_group_kernel(SymArgs<Pol> a)
     wave_lds_sync();
 
     const V4* row = rec[g] + lane;
-    auto steps = [&](auto jside) {
+    auto steps = [&](auto jside, int t0, int t1) {
         constexpr bool JSIDE = decltype(jside)::value;
 #pragma unroll 2
-        for (int t = 0; t < 64; ++t) {
+        for (int t = t0; t < t1; ++t) {
             const V4 q = row[t];
 #pragma unroll
             for (int s = 0; s < S; ++s) {
@@ -409,16 +416,27 @@ __global__ __launch_bounds__(C * K * 64) void force_group_kernel(SymArgs<Pol> a)
         }
     };
     if (J * BI + g * 64 < a.n) {
-        if (I != J)
-            steps(std::true_type{});
-        else
-            steps(std::false_type{});
+        if (I == J) {
+            steps(std::false_type{}, 0, 64);
+        } else {
+#pragma unroll 1
+            for (int t1 = 64 / SEG;; t1 += 64 / SEG) {
+                steps(std::true_type{}, t1 - 64 / SEG, t1);
+                if (t1 == 64) break;
+                // after t1 steps the sum of this lane's source is t1 lanes down
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    home[q] += from_lane(c[0][q], (lane - t1) & 63);
+                    c[0][q] = T(0);
+                }
+            }
+        }
     }
     // source side: slot I of particle j
     if (I != J && jok) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            T t = T(0);
+            T t = home[q];
 #pragma unroll
             for (int h = 0; h < CH; ++h) t += c[h][q];
             a.part[a.band.offset(I, q, j)] = q < 3 ? -t : t;

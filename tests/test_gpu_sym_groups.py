@@ -60,3 +60,38 @@ def test_ragged_blocks(prec, n):
         assert rel(host(lm)[idx], 0.5 * dt * gt) <= bar
         ao = oracle.accel_sampled(host(xs), mh, eps, idx)
         assert rel(host(acc)[:, idx], ao) <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", ("mix_tilec", "f32", "f64"))
+@pytest.mark.parametrize("n", (12288, 24576))
+@pytest.mark.parametrize("heavy", (3, 77, 250))
+def test_source_side_chains(prec, n, heavy):
+    """A source-side sum is made of chains of at most 128 terms: with one
+    particle of mass 1 in the first block and half a rounding unit, 2^-25 (FP64:
+    2^-54), in every other, all in one place, each term that follows the heavy
+    one in its chain is lost and no other, so that a particle of the last block
+    misses at most 127 of them in the potential (eps = 1) and in J^T lam of a
+    lam that is 1 there and 0 elsewhere (the sum of the other masses). Joining
+    the chains and the slots rounds a few terms more: 136 in all."""
+    light = 2.0 ** -54 if prec == "f64" else 2.0 ** -25
+    m = np.full(n, light)
+    m[heavy] = 1.0
+    xd, vd, md = to_dev(np.zeros((3, n)), np.zeros((3, n)), m, prec)
+    last = np.arange(n - 256, n)
+    whole = np.longdouble(1.0) + np.longdouble(light) * (n - 2)  # of the others
+
+    def lost(sums):
+        return float(np.max(np.abs(np.asarray(sums, dtype=np.longdouble) - whole)) / light)
+
+    _, p = nb.accel(xd, md, 1.0, prec=prec, potential=True)
+    assert lost(-host(p)[last]) <= 136
+    lam = np.zeros((3, n))
+    lam[:, last] = 1.0
+    acc, lx = torch.zeros_like(xd), torch.zeros_like(xd)
+    lv = torch.tensor(lam, dtype=xd.dtype, device=DEV)
+    lm = torch.zeros(n, dtype=torch.float64, device=DEV)
+    # (the other particles of the last block have the same lam: their terms
+    # m_j lam_i - m_i lam_j cancel)
+    nb.step_adjoint(xd, vd, md, acc, lx, lv, lm, 1.0, 2.0, 0, prec=prec, entry_half=True)
+    whole = np.longdouble(1.0) + np.longdouble(light) * (n - 257)
+    assert lost(-host(lx)[:, last]) <= 136
