@@ -536,13 +536,16 @@ hipError_t launch_sym(const SymArgs<Pol>& a, bool pot, hipStream_t stream) {
             return hipGetLastError();
         }
     }
-    if (pot)
-        hipLaunchKernelGGL((force_sym_kernel<Pol, W, K, true>), dim3((unsigned)items), dim3(W * 64),
-                           0, stream, a);
-    else
-        hipLaunchKernelGGL((force_sym_kernel<Pol, W, K, false>), dim3((unsigned)items),
-                           dim3(W * 64), 0, stream, a);
-    return hipGetLastError();
+    if constexpr (!by_groups<Pol>(W, K, 1 << 30)) {  // block counts that leave it
+        if (pot)
+            hipLaunchKernelGGL((force_sym_kernel<Pol, W, K, true>), dim3((unsigned)items),
+                               dim3(W * 64), 0, stream, a);
+        else
+            hipLaunchKernelGGL((force_sym_kernel<Pol, W, K, false>), dim3((unsigned)items),
+                               dim3(W * 64), 0, stream, a);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 template <class Pol>
