@@ -206,7 +206,7 @@ hipError_t launch_adjoint_sym_pol(int prec, const SymShape& sh, int64_t n, const
     // the layout of this pass: seven partial rows with the force sums, four
     // without (the workspace is sized for seven)
     const SymLayout L = adjoint_sym_layout(prec, sh, n, update_state);
-    const int nt = asym::item_threads(sh);
+    const int nt = asym::item_threads<Pol>(sh, update_state, L.nb);
     const SymPlan plan = sym_plan(L, ws_bytes, nt);
     if (!plan.valid) return hipErrorInvalidValue;
     double* run = plan.one ? nullptr : static_cast<double*>(ws);

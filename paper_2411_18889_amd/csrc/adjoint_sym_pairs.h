@@ -413,10 +413,18 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
 }
 
 // Whether a shape's items run with one wave per source group, and the threads
-// of an item's workgroup.
-constexpr bool by_groups(int waves, int ipl) { return ipl == 2 && waves == 2; }
-inline int item_threads(const SymShape& s) {
-    return s.waves * 64 * (by_groups(s.waves, s.ipl) ? s.ipl : 1);
+// of an item's workgroup. Blocks of 256; the tile-compensated pass without the
+// force sums up to 96 blocks (us against the kernel above: 16384 124, 125;
+// 24576 250, 256; but 28000 324, 309; 32767 430, 404).
+template <class Pol, bool F>
+constexpr bool by_groups(int waves, int ipl, int nb) {
+    return ipl == 2 && waves == 2 && (!Pol::origin || F || nb <= 96);
+}
+template <class Pol>
+int item_threads(const SymShape& s, bool force_sums, int nb) {
+    const bool groups = force_sums ? by_groups<Pol, true>(s.waves, s.ipl, nb)
+                                   : by_groups<Pol, false>(s.waves, s.ipl, nb);
+    return s.waves * 64 * (groups ? s.ipl : 1);
 }
 
 template <class Pol>
@@ -438,16 +446,20 @@ hipError_t launch_group_own(const ASymArgs<PolF64>& a, bool force_sums, hipStrea
 // One band of the pair pass in shape W x K; F: with the force sums.
 template <class Pol, int W, int K, bool F>
 hipError_t launch_pairs(const ASymArgs<Pol>& a, hipStream_t stream) {
-    if constexpr (by_groups(W, K)) {
-        if constexpr (Pol::origin)
-            return launch_group<Pol, F>(a, stream);
-        else
-            return launch_group_own(a, F, stream);
-    } else {
+    if constexpr (by_groups<Pol, F>(W, K, 1)) {
+        if (by_groups<Pol, F>(W, K, a.nb)) {
+            if constexpr (Pol::origin)
+                return launch_group<Pol, F>(a, stream);
+            else
+                return launch_group_own(a, F, stream);
+        }
+    }
+    if constexpr (!by_groups<Pol, F>(W, K, 1 << 30)) {  // block counts that leave it
         hipLaunchKernelGGL((adjoint_sym_kernel<Pol, W, K, F>), dim3(band_items(a)), dim3(W * 64), 0,
                            stream, a);
         return hipGetLastError();
     }
+    return hipErrorInvalidValue;
 }
 
 // The force-free pair pass of one band (adjoint_sym_entry.hip).
