@@ -147,7 +147,7 @@ __global__ __launch_bounds__(W * 64) void adjoint_sym_kernel(ASymArgs<Pol> a) {
     __shared__ C jacc[W][NQ][TJ];
 
     int I, J;
-    band_item(blockIdx.x, a.band.I0, a.band.I1, I, J);
+    band_item<(BI <= kDiagonalLast)>(blockIdx.x, a.band.I0, a.band.I1, I, J);
     const bool jside = I != J;
 
     const int tid = threadIdx.x;
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
     T(*ex)[S][S][64] = reinterpret_cast<T(*)[S][S][64]>(buf);    // [quantity][group][sink / 64]
 
     int I, J;
-    band_item(blockIdx.x, a.band.I0, a.band.I1, I, J);
+    band_item<(BI <= kDiagonalLast)>(blockIdx.x, a.band.I0, a.band.I1, I, J);
     const int lane = threadIdx.x & 63;
     const int g = threadIdx.x >> 6;
     const int ib = I * BI + lane;

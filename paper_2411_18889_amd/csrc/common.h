@@ -506,29 +506,37 @@ inline int sym_band_end(const SymLayout& L, int I0, size_t budget, int nt) {
 }
 
 // Work item t of the band [I0, I1) -> block pair (I, J), I <= J: first the
-// triangle of pairs inside the band (I < J < I1), ordered by J, then I, so
-// that consecutive workgroups share their source block; then the diagonal;
-// then the rectangle of rows I0 .. I1-1 against the blocks J >= I1, in the
-// same order. In one band the diagonal is last: its items have no source side
-// (half to two thirds of a pair's work), so the CUs left with one workgroup
-// more than the others have the short ones (16384 particles are 8.1 items a
-// CU; us with the diagonal among the others and last: tile-compensated force
-// 70.6, 67.6, adjoint 130.6, 124.6, walk 161.7, 156.2; 15360: 66.4, 63.2,
-// 121.3, 113.8, 150.3, 143.8; 65536: 858, 848, 1660, 1647, 2108, 2095; no
-// size slower).
+// triangle of pairs inside the band (J < I1), ordered by J, then I, so that
+// consecutive workgroups share their source block; then the rectangle of rows
+// I0 .. I1-1 against the blocks J >= I1, in the same order. LAST: the diagonal
+// comes after the triangle instead of among it. Its items have no source side
+// (half to two thirds of a pair's work), so in one band the CUs left with one
+// workgroup more than the others have the short ones. For blocks of up to 512
+// particles (kDiagonalLast): us with the diagonal among the others and last,
+// tile-compensated force, entry pass, walked-back step,
+//   14000  56.4, 53.7  104.3, 97.9   123.4, 118.5
+//   16384  70.6, 67.8  128.2, 123.3  153.6, 147.7
+//   32767  244, 233    412, 402      506, 501
+//   60000  729, 731    1211, 1223    1550, 1569  (the largest loss)
+//   65536  869, 858    1459, 1440    1848, 1833
+// For blocks of 1024 and more it gains nothing on average and loses up to 3 %
+// (115000: force 2448, 2488; FP64 entry pass 8367, 8556).
+constexpr int kDiagonalLast = 512;
+template <bool LAST = true>
 __host__ __device__ inline void band_item(int64_t t, int I0, int I1, int& I, int& J) {
+    constexpr int D = LAST ? 0 : 1;  // pairs (j, j) in the triangle
     const int R = I1 - I0;
-    const int64_t tri = (int64_t)R * (R - 1) / 2;
+    const int64_t tri = (int64_t)R * (R - 1 + 2 * D) / 2;
     if (t < tri) {
-        int j = (int)((sqrt(8.0 * (double)t + 1.0) + 1.0) * 0.5);
-        while ((int64_t)j * (j - 1) / 2 > t) --j;
-        while ((int64_t)(j + 1) * j / 2 <= t) ++j;
-        I = I0 + (int)(t - (int64_t)j * (j - 1) / 2);
+        int j = (int)((sqrt(8.0 * (double)t + 1.0) + (LAST ? 1.0 : -1.0)) * 0.5);
+        while ((int64_t)j * (j - 1 + 2 * D) / 2 > t) --j;
+        while ((int64_t)(j + 1) * (j + 2 * D) / 2 <= t) ++j;
+        I = I0 + (int)(t - (int64_t)j * (j - 1 + 2 * D) / 2);
         J = I0 + j;
-    } else if (t - tri < R) {
+    } else if (LAST && t - tri < R) {
         I = J = I0 + (int)(t - tri);
     } else {
-        const int64_t u = t - tri - R;
+        const int64_t u = t - tri - (LAST ? R : 0);
         J = I1 + (int)(u / R);
         I = I0 + (int)(u % R);
     }

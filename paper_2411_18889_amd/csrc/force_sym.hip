@@ -185,7 +185,7 @@ __global__ __launch_bounds__(W * 64) void force_sym_kernel(SymArgs<Pol> a) {
     __shared__ C jacc[W][NQ][TJ];
 
     int I, J;
-    band_item(blockIdx.x, a.band.I0, a.band.I1, I, J);
+    band_item<(BI <= kDiagonalLast)>(blockIdx.x, a.band.I0, a.band.I1, I, J);
     const bool jside = I != J;
 
     const int tid = threadIdx.x;
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(C * K * 64) void force_group_kernel(SymArgs<Pol> a)
     T(*ex)[S][S][64] = reinterpret_cast<T(*)[S][S][64]>(buf);    // [quantity][group][sink / 64]
 
     int I, J;
-    band_item(blockIdx.x, a.band.I0, a.band.I1, I, J);
+    band_item<(BI <= kDiagonalLast)>(blockIdx.x, a.band.I0, a.band.I1, I, J);
     const int lane = threadIdx.x & 63;
     const int g = threadIdx.x >> 6;
     const int ib = I * BI + lane;
