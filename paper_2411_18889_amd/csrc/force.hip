@@ -69,7 +69,9 @@ __device__ __forceinline__ void finish_pot(const ForceArgs<Pol>& a, int i, doubl
 // TAIL: also the leapfrog's tail, from what tail.load gave for the three
 // components. The pair kernel leaves it out (it costs
 // registers, and with them waves, there: 46 -> 91 VGPRs and 20 % with Kahan
-// sums at 262144).
+// sums at 262144) but for the closing half-kick alone (the same registers),
+// which ends a call: a single step of 200 particles, which the pass does in one
+// range, 13.1 us with it, 14.1 with a launch for it.
 template <class Pol, bool POT, bool TAIL>
 __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, double sx, double sy,
                                             double sz, double sp,
@@ -79,11 +81,19 @@ __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, doub
     a.ax[i] = ax;
     a.ay[i] = ay;
     a.az[i] = az;
-    if (TAIL && a.tail.v) {
+    if (!POT && a.tail.v) {
         const size_t n = a.ni, n3 = 3 * n;
-        a.tail.apply(i, n3, in[0], ax);
-        a.tail.apply(n + i, n3, in[1], ay);
-        a.tail.apply(2 * n + i, n3, in[2], az);
+        if (TAIL) {
+            a.tail.apply(i, n3, in[0], ax);
+            a.tail.apply(n + i, n3, in[1], ay);
+            a.tail.apply(2 * n + i, n3, in[2], az);
+        } else {
+            pos_t* const v = a.tail.v;
+            const pos_t h = a.tail.h;
+            v[i] = fmat(h, ax, v[i]);
+            v[n + i] = fmat(h, ay, v[n + i]);
+            v[2 * n + i] = fmat(h, az, v[2 * n + i]);
+        }
     }
     if (POT) finish_pot(a, i, sp);
 }
@@ -340,7 +350,8 @@ __global__ __launch_bounds__(LB) void force_lanes_kernel(ForceArgs<Pol> a) {
 }
 
 // The leapfrog's tail after a pass in one range, whose workgroups finish their
-// own sinks while others still read the positions.
+// own sinks while others still read the positions (where it is more than the
+// half-kick).
 template <class Pol>
 __global__ __launch_bounds__(256) void force_tail_kernel(ForceArgs<Pol> a) {
     const size_t k = blockIdx.x * (size_t)256 + threadIdx.x, n3 = 3 * (size_t)a.ni;
@@ -428,8 +439,11 @@ hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_
     if (drifted) *drifted = a.tail.x != nullptr;
     if (nsplit == 1 && !partials_only) {
         a.part = nullptr;
-        const hipError_t e = launch_any<Pol, ACC, POT>(sh, a, 1, stream);
-        if (e != hipSuccess || !a.tail.v) return e;
+        // a tail of the half-kick alone in the pair kernel, else after it
+        ForceArgs<Pol> pass = a;
+        if (!a.tail.close || a.tail.store || a.tail.x) pass.tail.v = nullptr;
+        const hipError_t e = launch_any<Pol, ACC, POT>(sh, pass, 1, stream);
+        if (e != hipSuccess || pass.tail.v == a.tail.v) return e;
         hipLaunchKernelGGL(force_tail_kernel<Pol>, dim3((unsigned)((3 * (int64_t)a.ni + 255) / 256)),
                            dim3(256), 0, stream, a);
         return hipGetLastError();

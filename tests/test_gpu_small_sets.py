@@ -231,3 +231,46 @@ def test_reported_shape_is_taken(prec, n):
             assert rel(host(a), ref) <= TOL[prec]
         else:
             assert float(a.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("prec,n", [("f64", 100), ("f32", 300), ("mix_acc64", 300), ("f32", 511),
+                                    ("mix_tilec", 200), ("mix_acc32", 300), ("mix_kahan", 511)])
+@pytest.mark.parametrize("S", (0, 1, 2, 5))
+def test_steps_without_workspace(prec, n, S):
+    """Sets whose leapfrog asks for no workspace: those with the sources on the
+    lanes have no second array of positions to alternate with, so every drift is
+    a launch of its own; the others are one range, whose pass ends a call with
+    the half-kick in the pair kernel. One call of S steps, with a valid
+    acceleration or not, with checkpoints or not, eager or replayed as a graph,
+    ends bitwise where S calls of one step do, and its checkpoints are their
+    states."""
+    assert nb.workspace_size(1, n, prec) == 0
+    eps, dt = 2.0 ** -6, 2.0 ** -7
+    x, v, m = plummer_sphere(n, 81)
+    ref = list(to_dev(x, v, m, prec))
+    md = ref.pop()
+    ref.append(torch.empty_like(ref[0]))
+    nb.step(*ref[:2], md, ref[2], eps, dt, 0, prec=prec)
+    a0 = ref[2].clone()
+    states = [torch.cat([t.reshape(-1) for t in ref])]
+    for _ in range(S):
+        nb.step(*ref[:2], md, ref[2], eps, dt, 1, prec=prec, acc_valid=True)
+        states.append(torch.cat([t.reshape(-1) for t in ref]))
+    xo, vo, ao = oracle.kdk(host(to_dev(x, v, m, prec)[0]), host(to_dev(x, v, m, prec)[1]), host(md),
+                            eps, dt, S)
+    bar = 1e-12 if prec == "f64" else 1e-5
+    assert max(rel(host(ref[0]), xo), rel(host(ref[1]), vo), rel(host(ref[2]), ao)) <= bar
+    g = list(to_dev(x, v, m, prec))[:2] + [a0.clone()]
+    for every in (0, 1, 2):
+        for valid in (False, True):
+            for graph in (False, True, True):
+                for t, s in zip(g, states[0].split(3 * n)):
+                    t.copy_(s.view(3, n))
+                ck = torch.full((S // every + 1, 9 * n), float("nan"), dtype=g[0].dtype,
+                                device=DEV) if every else None
+                nb.step(*g[:2], md, g[2], eps, dt, S, prec=prec, acc_valid=valid, graph=graph,
+                        **({"ckpt": ck, "ckpt_every": every} if every else {}))
+                assert torch.equal(torch.cat([t.reshape(-1) for t in g]), states[S])
+                for k in range(S // every + 1 if every else 0):
+                    assert torch.equal(ck[k], states[k * every])
+    nb.graph_cache_clear()
