@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256) void adjoint_reduce_kernel(AdjArgs<Pol> a, int
     constexpr int Q0 = F ? 0 : 3;
     __shared__ double other[3][NQ][64];
     const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + lane;
+    const int i = reduce_first_sink() + lane;
     double t[NQ] = {0, 0, 0, 0, 0, 0, 0};
     if (i < a.n) {
         for (int r0 = g; r0 < nsplit; r0 += 4 * 4) {  // four ranges' loads in flight
@@ -496,7 +496,7 @@ hipError_t launch_adjoint(int prec, const Shape& sh, int64_t n, const void* x, c
         a.part = static_cast<double*>(ws);
         err = launch_any<Pol>(sh, a, nsplit, stream);
         if (err != hipSuccess) return;
-        const dim3 grid((a.n + 63) / 64);
+        const dim3 grid = reduce_grid(sh, n);
         if (update_state)
             hipLaunchKernelGGL((adjoint_reduce_kernel<Pol, true>), grid, dim3(256), 0, stream, a, nsplit);
         else

@@ -292,6 +292,21 @@ inline int split_ranges(int64_t nj, int64_t split, int block) {
     const int64_t span = split_span(nj, (int)split, block);
     return (int)((nj + span - 1) / span);
 }
+// Grid of the one-sided passes' reductions, 64 sinks a workgroup: x the pair
+// workgroups of a range (`per` sinks each), y the 64s of one. Workgroups are
+// dealt to the 8 XCDs round-robin, x first, so where a range has a multiple of
+// 8 workgroups every partial is added on the XCD whose L2 it was written
+// through. us per force pass with consecutive workgroups on consecutive sinks
+// and so: tile-compensated 8192 30.9, 28.6, 12287 61.7, 59.5, with the
+// potential 68.5, 65.5; FP32 sums 16383 95.8, 90.9.
+inline dim3 reduce_grid(const Shape& s, int64_t n) {
+    const int per = s.block * s.ipl;
+    return dim3((unsigned)((n + per - 1) / per), (unsigned)(per / 64));
+}
+__device__ __forceinline__ int reduce_first_sink() {
+    return (int)(blockIdx.x * gridDim.y + blockIdx.y) * 64;
+}
+
 // Few waves in flight (under 4 per SIMD over the whole pass): the one-sided
 // kernels with one sink per lane then run in a build that may spend registers
 // on more sources in flight instead of on more waves.

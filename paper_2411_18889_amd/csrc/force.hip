@@ -208,14 +208,14 @@ __global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void force_kernel(ForceArg
 // wave g of a group of W adds ranges g, g + W, ... of 64 sinks (eight ranges'
 // loads in flight together), and the first wave the W sums in wave order. At
 // small ni the kernel is one load latency after another, so four waves share
-// them; from 16384 sinks one wave is as fast.
+// them; from 16384 sinks, and up to four ranges, one wave is as fast.
 template <class Pol, bool POT, int W>
 __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int nsplit) {
     constexpr int N = POT ? 4 : 3;
     __shared__ double other[W > 1 ? W - 1 : 1][N][64];
     const int lane = threadIdx.x & 63;
     const int g = W > 1 ? threadIdx.x >> 6 : 0;
-    const int i = W > 1 ? blockIdx.x * 64 + lane : blockIdx.x * 256 + threadIdx.x;
+    const int i = W > 1 ? reduce_first_sink() + lane : blockIdx.x * 256 + threadIdx.x;
     const size_t stride = (size_t)NQ * a.ni;
     double s[N] = {};
     typename TailArgs<typename Pol::pos_t>::In in[3];  // in flight with the partials
@@ -451,8 +451,8 @@ hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_
     a.part = static_cast<double*>(ws);
     hipError_t e = launch_any<Pol, ACC, POT>(sh, a, nsplit, stream);
     if (e != hipSuccess || partials_only) return e;
-    if (a.ni < 16384)
-        hipLaunchKernelGGL((force_reduce_kernel<Pol, POT, 4>), dim3((a.ni + 63) / 64), dim3(256), 0,
+    if (a.ni < 16384 && nsplit > 4)
+        hipLaunchKernelGGL((force_reduce_kernel<Pol, POT, 4>), reduce_grid(sh, a.ni), dim3(256), 0,
                            stream, a, nsplit);
     else
         hipLaunchKernelGGL((force_reduce_kernel<Pol, POT, 1>), dim3((a.ni + 255) / 256), dim3(256), 0,
