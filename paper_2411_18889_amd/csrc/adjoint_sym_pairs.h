@@ -363,20 +363,24 @@ __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol>
         }
     };
     if (J * BI + g * 64 < a.n) {
-        if (I == J) {
-            steps(std::false_type{}, 0, 64);
-        } else {
+        if (I != J) {
+            if constexpr (SEG == 1) {
+                steps(std::true_type{}, 0, 64);
+            } else {
 #pragma unroll 1
-            for (int t1 = 64 / SEG;; t1 += 64 / SEG) {
-                steps(std::true_type{}, t1 - 64 / SEG, t1);
-                if (t1 == 64) break;
-                // after t1 steps the sum of this lane's source is t1 lanes down
+                for (int t1 = 64 / SEG;; t1 += 64 / SEG) {
+                    steps(std::true_type{}, t1 - 64 / SEG, t1);
+                    if (t1 == 64) break;
+                    // after t1 steps the sum of this lane's source is t1 lanes down
 #pragma unroll
-                for (int q = Q0; q < NQ; ++q) {
-                    home[q] += from_lane(c[0][q], (lane - t1) & 63);
-                    c[0][q] = T(0);
+                    for (int q = Q0; q < NQ; ++q) {
+                        home[q] += from_lane(c[0][q], (lane - t1) & 63);
+                        c[0][q] = T(0);
+                    }
                 }
             }
+        } else {
+            steps(std::false_type{}, 0, 64);
         }
     }
     // source side: slot I of particle j
