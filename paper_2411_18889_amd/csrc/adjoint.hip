@@ -93,8 +93,9 @@ __device__ __forceinline__ void finish_adj(const AdjArgs<Pol>& a, int i, const d
 // back); without it they stay 0 and the pair body is 4 operations shorter.
 // FEW: built for few waves in flight (kFewWaves): tile-compensated entry pass
 // 36.5 -> 25.3 us at 2500 particles, 38.4 -> 33.0 at 5003 (at 10000 88 against
-// 85, so not there); with Kahan sums from half as many waves down (walked-back
-// step 85 -> 71 at 5003, but 128 -> 146 at 9377).
+// 85, so not there); with Kahan sums from half as many waves down, and with the
+// force sums too up to one wave per SIMD (walked-back step 87 -> 70 at 5003,
+// but 91 -> 99 at 6000, 128 -> 146 at 9377).
 template <class Pol, int BS, int K, bool F, bool FEW>
 __global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void adjoint_kernel(AdjArgs<Pol> a) {
     using calc_t = typename Pol::calc_t;
@@ -362,9 +363,11 @@ hipError_t launch_shape(AdjArgs<Pol> a, int nsplit, hipStream_t stream) {
         return hipGetLastError();
     };
     constexpr bool kahan = std::is_same<typename Pol::sum_t, SumKahan>::value;
-    if constexpr (K == 1 && (kahan || std::is_same<typename Pol::sum_t, SumTile>::value))
-        if ((int64_t)grid.x * nsplit * (BS / 64) < (kahan ? kFewWaves / 2 : kFewWaves))
-            return launch(std::true_type{});
+    if constexpr (K == 1 && (kahan || std::is_same<typename Pol::sum_t, SumTile>::value)) {
+        const int64_t waves = (int64_t)grid.x * nsplit * (BS / 64);
+        const int64_t most = !kahan ? kFewWaves : a.update_state ? kFewWaves / 4 + 1 : kFewWaves / 2;
+        if (waves < most) return launch(std::true_type{});
+    }
     return launch(std::false_type{});
 }
 
