@@ -567,10 +567,15 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     // arithmetic. With both changes of the reduction and the ranges a pass
     // takes 13.7 us instead of 21.9 at 1000 particles and 20.3 instead of
     // 23.8 at 5003 (at 11239 with the potential, 44 ranges of one tile are
-    // 2 % slower than 22 of two).
+    // 2 % slower than 22 of two). From 3.5 waves per SIMD with the rule above on
+    // only if they make 5.5: between, some SIMDs have five waves and others
+    // four (FP64 sums, us without and with them: 15000, 3540 waves, 125.5, 117.0;
+    // 15500, 3782 to 5002, 130.1, 134.3; 16384, 4096 to 5504, 126.5, 133.4;
+    // 17000, 3618 to 6030, 151.8, 140.6).
     if (pick != Pick::Least && tile_ranges(prec)) {
-        split = std::max<int64_t>(split_ranges(nj, split, s.block),
-                                  short_tile_ranges(nj, s.block, waves, kRangeWaves));
+        const int64_t some = split_ranges(nj, split, s.block);
+        const int64_t more = short_tile_ranges(nj, s.block, waves, kRangeWaves);
+        if (some * waves < kFewWaves * 7 / 8 || more * waves >= 5632) split = std::max(some, more);
     }
     s.split = (int)split;
     return s;
