@@ -528,11 +528,13 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     //   acc64    6.0, 16.7   16.0, 18.7   44.4, 41.7   88.2, 86.4
     // so up to 6000 sources for FP64 sums of FP32 terms, whose lanes carry
     // the longest chain, and for few FP64 sinks, where a lane's sources are
-    // the whole time (100 against 12000: 15.3, 14.3; 1000: 16.4, 19.7).
+    // the whole time (100 against 12000: 15.3, 14.3; 1000: 16.4, 19.7), and up
+    // to 12000 sinks and sources in FP64 (12287: 111.3, 109.4).
     // Larger sets on themselves have the symmetric pass in FP64 and FP32.
     const bool regroup = prec == NB_F64 || prec == NB_F32 || prec == NB_MIX_ACC64;
-    const int64_t most = prec == NB_MIX_ACC64 || (prec == NB_F64 && ni < 512) ? 6000 : 12287;
-    if (pick == Pick::Best && regroup && ni <= 12287 && nj <= most) {
+    const int64_t top = prec == NB_F64 ? 12000 : 12287;
+    const int64_t most = prec == NB_MIX_ACC64 || (prec == NB_F64 && ni < 512) ? 6000 : top;
+    if (pick == Pick::Best && regroup && ni <= top && nj <= most) {
         const int lanes = prec != NB_MIX_ACC64 && ni <= 3072 && nj > 256 ? 512 : 256;
         Shape s{LS, lanes, lanes};
         s.lanes = true;
