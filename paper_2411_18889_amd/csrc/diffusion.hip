@@ -12,7 +12,8 @@
 // A lane owns 4 consecutive k points of R rows and marches along i over a
 // slab of CI planes; planes i - 1, i, i + 1 of its points stay in registers,
 // plane i + 2 and the two outer rows (j - 1, j + R) of plane i + 1 are already
-// loading while plane i is computed. There is no LDS and no barrier: rows
+// loading while plane i is computed. There is no LDS, and a barrier only for
+// pace (PACED, large planes): rows
 // above and below come from L1 / L2, where the neighbouring lanes' own loads
 // put them, and the k neighbours of a lane's 4 points from the adjacent
 // lanes (DPP wave shifts).
@@ -34,8 +35,6 @@ struct Coef {
 
 typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
 
-constexpr int TPB = kDiffLanes;
-
 struct DiffArgs {
     int nx, ny, nz;
     Coef c;
@@ -46,7 +45,8 @@ struct DiffArgs {
 
 __device__ __forceinline__ v4f load4(const float* p) { return *reinterpret_cast<const v4f*>(p); }
 
-template <int R>
+// PACED: the workgroup's waves keep to the same plane by a barrier per plane.
+template <int R, int TPB, bool PACED>
 __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
     // workgroups are dealt to the 8 XCDs round-robin: give each XCD one
     // contiguous run of the grid, so that rows and planes which neighbouring
@@ -56,8 +56,10 @@ __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
     const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (b >= a.g.blocks) return;
     const int slab = b / a.g.chunks;
-    const int t = (b - slab * a.g.chunks) * TPB + threadIdx.x;
-    if (t >= a.g.lanes) return;
+    int t = (b - slab * a.g.chunks) * TPB + threadIdx.x;
+    const bool in = t < a.g.lanes;
+    if (!PACED && !in) return;
+    if (PACED) t = min(t, a.g.lanes - 1);  // (every wave comes to the barriers)
 
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const Coef c = a.c;
@@ -98,6 +100,7 @@ __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
             eln[r] = d.left ? p1[off[r + 1] - 1] : 0.f;
             ern[r] = d.right ? p1[off[r + 1] + 4] : 0.f;
         }
+        if (PACED) __builtin_amdgcn_s_barrier();
         float* o = a.fn + (int64_t)i * plane;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -124,7 +127,8 @@ __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
                 q[e] = __builtin_fmaf(c.cb, kme, s);
             }
             // streaming store: fn is not read again by this step
-            if (j0 + r < ny) __builtin_nontemporal_store(q, reinterpret_cast<v4f*>(o + off[r + 1]));
+            if ((!PACED || in) && j0 + r < ny)
+                __builtin_nontemporal_store(q, reinterpret_cast<v4f*>(o + off[r + 1]));
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -140,6 +144,7 @@ __global__ __launch_bounds__(TPB) void diffusion_rows_kernel(DiffArgs a) {
 }
 
 // Rows shorter than one 16-byte access (nz < 4): a thread per point.
+constexpr int TPB = kDiffLanes;
 __global__ __launch_bounds__(TPB) void diffusion_point_kernel(int nx, int ny, int nz, Coef c,
                                                               const float* __restrict__ f,
                                                               float* __restrict__ fn) {
@@ -158,11 +163,11 @@ __global__ __launch_bounds__(TPB) void diffusion_point_kernel(int nx, int ny, in
     fn[t] = __builtin_fmaf(c.cb, f[k > 0 ? t - 1 : t], s);
 }
 
-template <int R>
+template <int R, int WG, bool PACED>
 hipError_t launch_rows(DiffArgs a, int64_t ci, hipStream_t stream) {
-    a.g = diff_rows(a.nx, a.ny, a.nz, R, ci);
-    hipLaunchKernelGGL((diffusion_rows_kernel<R>), dim3((unsigned)((a.g.blocks + 7) / 8 * 8)),
-                       dim3(TPB), 0, stream, a);
+    a.g = diff_rows(a.nx, a.ny, a.nz, R, ci, WG);
+    hipLaunchKernelGGL((diffusion_rows_kernel<R, WG, PACED>),
+                       dim3((unsigned)((a.g.blocks + 7) / 8 * 8)), dim3(WG), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -195,6 +200,11 @@ hipError_t launch_diffusion3d(int64_t nx, int64_t ny, int64_t nz, double dx, dou
     //    201.9 against 245, 700 x 430 x 444 242.9 against 269 (slabs of 64:
     //    126, 203, 289). The former 256 x 16 LDS tile with a barrier per plane
     //    and slabs of 64: 148, 204, 318;
+    //  * of those, planes of which three do not fit an XCD's 4 MB L2: 16 waves a
+    //    workgroup that keep to the same plane, so that the rows its waves share
+    //    are read once (unpaced, with 256 lanes, and the former kernel: 700^3
+    //    574, 606, 606; 1000^3 1573, 1773, 1671; 1200^3 2714, 3213, 2800;
+    //    300 x 640 x 640 180, 195, 250; but 512^3 200, 196, 196);
     //  * within it one row per lane (52 VGPRs against 126: more loads in
     //    flight), 256^3 21.8 against 23.0, 150 x 175 x 201 9.9 against 12.9;
     //    slabs of 16 planes, thinner where that would leave the chip short of
@@ -202,9 +212,13 @@ hipError_t launch_diffusion3d(int64_t nx, int64_t ny, int64_t nz, double dx, dou
     //    9.9, 16 12.6; 128^3: 2 planes 5.0, 4 5.3, 16 13.4; 64^3: one plane
     //    2.8, 16 10.2; former kernel: 79, 42, 67, 63).
     const int64_t points = nx * ny * nz;
-    if (2 * points * (int64_t)sizeof(float) > (int64_t(256) << 20)) return launch_rows<4>(a, 8, stream);
+    if (2 * points * (int64_t)sizeof(float) > (int64_t(256) << 20)) {
+        if (3 * ny * nz * (int64_t)sizeof(float) > (int64_t(4) << 20))
+            return launch_rows<4, kPacedLanes, true>(a, paced_planes(nx, ny, nz, 4), stream);
+        return launch_rows<4, kDiffLanes, false>(a, 8, stream);
+    }
     const int64_t work = (nz + 3) / 4 * ny * nx;  // lanes times planes
-    return launch_rows<1>(a, std::min<int64_t>(16, std::max<int64_t>(1, work / 196608)), stream);
+    return launch_rows<1, kDiffLanes, false>(a, std::min<int64_t>(16, std::max<int64_t>(1, work / 196608)), stream);
 }
 
 }  // namespace nb

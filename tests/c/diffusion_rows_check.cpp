@@ -52,15 +52,15 @@ static void check_row(int64_t nz) {
     }
 }
 
-static void check_grid(int64_t nx, int64_t ny, int64_t nz, int R, int64_t ci) {
-    const DiffRows g = diff_rows(nx, ny, nz, R, ci);
+static void check_grid(int64_t nx, int64_t ny, int64_t nz, int R, int64_t ci, int wg) {
+    const DiffRows g = diff_rows(nx, ny, nz, R, ci, wg);
     const int64_t lanes = (nz + 3) / 4 * ((ny + R - 1) / R), slabs = (nx + ci - 1) / ci;
     if (g.lanes != lanes) fail("lanes of a plane", g.lanes, lanes);
-    if (g.chunks < 1 || (int64_t)g.chunks * kDiffLanes < lanes ||
-        (int64_t)(g.chunks - 1) * kDiffLanes >= lanes)
+    if (g.chunks < 1 || (int64_t)g.chunks * wg < lanes ||
+        (int64_t)(g.chunks - 1) * wg >= lanes)
         fail("workgroups of a slab", g.chunks, lanes);
     if (g.blocks != g.chunks * slabs) fail("workgroups", g.blocks, slabs);
-    if (((int64_t)g.blocks + 7) / 8 * 8 * kDiffLanes >= (int64_t(1) << 32)) fail("threads", g.blocks, 0);
+    if (((int64_t)g.blocks + 7) / 8 * 8 * wg >= (int64_t(1) << 32)) fail("threads", g.blocks, 0);
 }
 
 int main() {
@@ -73,7 +73,8 @@ int main() {
                 for (int64_t ny : {int64_t(1), int64_t(2), int64_t(3), int64_t(524280)})
                     for (int64_t nx : {int64_t(1), int64_t(7), int64_t(1) << 21})
                         if (nx * ny <= (int64_t(1) << 31) && nz <= top / (nx * ny))
-                            check_grid(nx, ny, nz, R, ci);
+                            for (int wg : {kDiffLanes, kPacedLanes})
+                                check_grid(nx, ny, nz, R, ci, wg);
     std::printf("ok\n");
     return 0;
 }

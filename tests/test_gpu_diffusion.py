@@ -102,3 +102,21 @@ def test_longest_rows(nz):
         ref[0] += ct * f[max(k0 - 1, 0)].double()
         ref[-1] += ct * f[min(k1, nz - 1)].double()
         assert float((fn[k0:k1] - ref).abs().max()) <= 1e-6
+
+
+@pytest.mark.parametrize("shape", [(131, 709, 507), (70, 1, 600001), (20, 250001, 7), (5, 5003, 1400),
+                                   (33, 1025, 1024)])
+def test_large_planes(shape):
+    """Grids beyond the last-level cache whose planes do not fit an L2 three at a
+    time: workgroups that keep pace by barriers, with lanes past the end of the
+    plane, slabs that end inside the grid, rows of two lanes and single rows,
+    unaligned input and output, and nothing written outside."""
+    n = int(np.prod(shape))
+    f = np.random.default_rng(n).uniform(-1, 1, size=shape).astype(np.float32)
+    fd = torch.empty(n + 1, dtype=torch.float32, device=DEV)[1:].view(shape)
+    fd.copy_(torch.tensor(f))
+    guard = torch.full((n + 2,), 7.0, dtype=torch.float32, device=DEV)
+    fn = nb.api.diffusion3d_step(fd, out=guard[1:-1].view(shape), **PARAMS)
+    ref = oracle.diffusion3d(f.astype(np.float64), **PARAMS)
+    assert np.abs(fn.cpu().numpy() - ref).max() <= 1e-6 * np.abs(ref).max()
+    assert float(guard[0]) == 7.0 and float(guard[-1]) == 7.0
