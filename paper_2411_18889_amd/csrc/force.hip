@@ -69,10 +69,11 @@ __device__ __forceinline__ void finish_pot(const ForceArgs<Pol>& a, int i, doubl
 // TAIL: also the leapfrog's tail, from what tail.load gave for the three
 // components. The pair kernel leaves it out (it costs
 // registers, and with them waves, there: 46 -> 91 VGPRs and 20 % with Kahan
-// sums at 262144) but for the closing half-kick alone (the same registers),
-// which ends a call: a single step of 200 particles, which the pass does in one
-// range, 13.1 us with it, 14.1 with a launch for it.
-template <class Pol, bool POT, bool TAIL>
+// sums at 262144) but, with one sink per lane, for the closing half-kick alone
+// (the same registers), which ends a call: a single step of 200 particles, which
+// the pass does in one range, 13.1 us with it, 14.1 with a launch for it.
+enum class Tail { None, Kick, All };
+template <class Pol, bool POT, Tail TAIL>
 __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, double sx, double sy,
                                             double sz, double sp,
                                             const typename TailArgs<typename Pol::pos_t>::In* in = nullptr) {
@@ -81,9 +82,9 @@ __device__ __forceinline__ void finish_sink(const ForceArgs<Pol>& a, int i, doub
     a.ax[i] = ax;
     a.ay[i] = ay;
     a.az[i] = az;
-    if (!POT && a.tail.v) {
+    if (TAIL != Tail::None && a.tail.v) {
         const size_t n = a.ni, n3 = 3 * n;
-        if (TAIL) {
+        if (TAIL == Tail::All) {
             a.tail.apply(i, n3, in[0], ax);
             a.tail.apply(n + i, n3, in[1], ay);
             a.tail.apply(2 * n + i, n3, in[2], az);
@@ -199,7 +200,8 @@ __global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void force_kernel(ForceArg
             }
             if (POT) q[(size_t)3 * a.ni + i] = sp[k].total();
         } else if (ACC) {
-            finish_sink<Pol, POT, false>(a, i, sx[k].total(), sy[k].total(), sz[k].total(), sp[k].total());
+            constexpr Tail KICK = !POT && K == 1 ? Tail::Kick : Tail::None;
+            finish_sink<Pol, POT, KICK>(a, i, sx[k].total(), sy[k].total(), sz[k].total(), sp[k].total());
         }
     }
 }
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int
             for (int c = 0; c < N; ++c) s[c] += other[v][c][lane];
     }
     if (i >= a.ni) return;
-    finish_sink<Pol, POT, !POT>(a, i, s[0], s[1], s[2], POT ? s[N - 1] : 0.0, in);
+    finish_sink<Pol, POT, (POT ? Tail::None : Tail::All)>(a, i, s[0], s[1], s[2], POT ? s[N - 1] : 0.0, in);
 }
 
 // Sources on the lanes: a workgroup of LB lanes owns LS sinks and each lane
@@ -452,7 +454,7 @@ hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_
         a.part = nullptr;
         // a tail of the half-kick alone in the pair kernel, else after it
         ForceArgs<Pol> pass = a;
-        if (!a.tail.close || a.tail.store || a.tail.x) pass.tail.v = nullptr;
+        if (sh.ipl > 1 || !a.tail.close || a.tail.store || a.tail.x) pass.tail.v = nullptr;
         const hipError_t e = launch_any<Pol, ACC, POT>(sh, pass, 1, stream);
         if (e != hipSuccess || pass.tail.v == a.tail.v) return e;
         hipLaunchKernelGGL(force_tail_kernel<Pol>, dim3((unsigned)((3 * (int64_t)a.ni + 255) / 256)),
@@ -528,13 +530,14 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     //   acc64    6.0, 16.7   16.0, 18.7   44.4, 41.7   88.2, 86.4
     // so up to 6000 sources for FP64 sums of FP32 terms, whose lanes carry
     // the longest chain, and for few FP64 sinks, where a lane's sources are
-    // the whole time (100 against 12000: 15.3, 14.3; 1000: 16.4, 19.7), and up
-    // to 12000 sinks and sources in FP64 (12287: 111.3, 109.4).
+    // the whole time (100 against 12000: 15.3, 14.3; 1000: 16.4, 19.7), and not
+    // above 12000 sinks and sources in FP64 (12287: 111.3, 109.4).
     // Larger sets on themselves have the symmetric pass in FP64 and FP32.
     const bool regroup = prec == NB_F64 || prec == NB_F32 || prec == NB_MIX_ACC64;
-    const int64_t top = prec == NB_F64 ? 12000 : 12287;
-    const int64_t most = prec == NB_MIX_ACC64 || (prec == NB_F64 && ni < 512) ? 6000 : top;
-    if (pick == Pick::Best && regroup && ni <= top && nj <= most) {
+    const int64_t most = prec == NB_MIX_ACC64 || (prec == NB_F64 && ni < 512) ? 6000
+                         : prec == NB_F64 && ni > 12000                       ? 12000
+                                                                              : 12287;
+    if (pick == Pick::Best && regroup && ni <= 12287 && nj <= most) {
         const int lanes = prec != NB_MIX_ACC64 && ni <= 3072 && nj > 256 ? 512 : 256;
         Shape s{LS, lanes, lanes};
         s.lanes = true;
