@@ -81,7 +81,9 @@ typedef enum nb_status {
  *                 hardware reciprocal square root; per-particle sums are FP32
  *                 running sums, as the paper's listing (in the symmetric
  *                 pass, for a set on itself from 12288 particles, FP32 sums
- *                 over each source block, then over the blocks in FP32).
+ *                 over each source block, then over the blocks in FP32; where
+ *                 several lanes or waves share a sink, each in FP32 and their
+ *                 sums together in FP64).
  *   NB_MIX_ACC32  pos double, mass float. Pair arithmetic in FP32 (as
  *                 NB_F32) on positions taken relative to an origin o, the
  *                 FP64 centroid of the sinks one workgroup owns (a
@@ -330,7 +332,12 @@ int nbody_diag(int64_t n, const void *x, const void *v, const void *m,
  * waits for those events, fills *out (may be NULL) and stops recording.
  * Kinds: the pair-force kernel (with its split reduction), the fused adjoint
  * kernel (with its split reduction), O(N) leapfrog updates, diagnostics,
- * checkpoint copies. Not for use under stream capture.
+ * checkpoint copies. What a pass does to each particle once its sums are
+ * complete counts as the pass: the kicks, drifts and checkpoint slots that a
+ * finishing kernel stores or reloads, i.e. all of them but a call's first (the
+ * slot of an entry state whose acceleration is valid, the first kick and drift,
+ * the first step back) and those of sets too small for a finishing kernel. Not
+ * for use under stream capture.
  */
 enum { NB_PROF_FORCE = 0, NB_PROF_ADJOINT = 1, NB_PROF_UPDATE = 2, NB_PROF_DIAG = 3,
        NB_PROF_COPY = 4, NB_PROF_KINDS = 5 };

@@ -137,25 +137,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// ---------------------------------------------------------------------------
-// Origin of the FP32 pair arithmetic in the mixed policies.
-//
-// There positions are FP64 and the pair arithmetic FP32. Rounding x itself
-// to FP32 would give the separation d = x_j - x_i an absolute error of up to
-// 2^-24 (|x_i| + |x_j|): relative error 2^-24 |x| / |d|, growing with the
-// distance from the coordinate origin. Instead every workgroup subtracts,
-// in FP64, the centroid o of its own sinks (one contiguous index range)
-// from those sinks and from every source it stages, and rounds x - o: the
-// error of d is then at most 2^-24 (|x_i - o| + |x_j - o|), whatever the
-// position of the system, and the same d serves both ends of a pair in the
-// symmetric passes. The centroid is a fixed-order FP64 reduction (xor
-// butterfly within each wave -- every lane ends with bitwise the same sum --
-// then the wave sums in wave order), so results stay reproducible.
-//
-// s*: this thread's FP64 sum over its valid sinks; count: valid sinks of the
-// workgroup (>= 1); lds: NW x 3 doubles of shared memory. Contains a
-// workgroup barrier: every thread of the workgroup must call it.
-// ---------------------------------------------------------------------------
 // A value that every lane of the wave holds, moved to a scalar register.
 __device__ __forceinline__ double wave_uniform(double v) {
     const int lo = __builtin_amdgcn_readfirstlane(__double2loint(v));
@@ -183,6 +164,25 @@ __device__ __forceinline__ double wave_total(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// ---------------------------------------------------------------------------
+// Origin of the FP32 pair arithmetic in the mixed policies.
+//
+// There positions are FP64 and the pair arithmetic FP32. Rounding x itself
+// to FP32 would give the separation d = x_j - x_i an absolute error of up to
+// 2^-24 (|x_i| + |x_j|): relative error 2^-24 |x| / |d|, growing with the
+// distance from the coordinate origin. Instead every workgroup subtracts,
+// in FP64, the centroid o of its own sinks (one contiguous index range)
+// from those sinks and from every source it stages, and rounds x - o: the
+// error of d is then at most 2^-24 (|x_i - o| + |x_j - o|), whatever the
+// position of the system, and the same d serves both ends of a pair in the
+// symmetric passes. The centroid is a fixed-order FP64 reduction (xor
+// butterfly within each wave -- every lane ends with bitwise the same sum --
+// then the wave sums in wave order), so results stay reproducible.
+//
+// s*: this thread's FP64 sum over its valid sinks; count: valid sinks of the
+// workgroup (>= 1); lds: NW x 3 doubles of shared memory. Contains a
+// workgroup barrier: every thread of the workgroup must call it.
+// ---------------------------------------------------------------------------
 template <int NW>
 __device__ __forceinline__ void sink_block_origin(double sx, double sy, double sz, int count,
                                                   double (*lds)[3], double& ox, double& oy,
@@ -307,9 +307,10 @@ __device__ __forceinline__ int reduce_first_sink() {
     return (int)(blockIdx.x * gridDim.y + blockIdx.y) * 64;
 }
 
-// Few waves in flight (under 4 per SIMD over the whole pass): the one-sided
-// kernels with one sink per lane then run in a build that may spend registers
-// on more sources in flight instead of on more waves.
+// Few waves in flight, 4 per SIMD over the whole pass: below it the one-sided
+// adjoint kernels with one sink per lane run in a build that may spend registers
+// on more sources in flight instead of on more waves (with Kahan sums below a
+// half of it, or a quarter), the force kernels below twice it.
 constexpr int64_t kFewWaves = 4096;
 #define NB_WAVES_PER_EU(few) __attribute__((amdgpu_waves_per_eu((few) ? 4 : 1, (few) ? 6 : 8)))
 
