@@ -95,3 +95,50 @@ def test_source_side_chains(prec, n, heavy):
     nb.step_adjoint(xd, vd, md, acc, lx, lv, lm, 1.0, 2.0, 0, prec=prec, entry_half=True)
     whole = np.longdouble(1.0) + np.longdouble(light) * (n - 257)
     assert lost(-host(lx)[:, last]) <= 136
+
+
+@pytest.mark.parametrize("n", (1000, 6001, 12287, 12289, 16384, 24577, 40001))
+def test_fp32_adjoint_rounding(n):
+    """J^T lam and G^T lam of the FP32 policy within the rounding that its terms
+    and sums can leave: with u = 2^-24, the terms' relative errors (a few u:
+    rounding of d and s, one ulp of the reciprocal square root, its third power,
+    the products) and the running sums of some 128 terms of either sign each
+    add about 6 u and 5 u of the root of the sum of the squared term bounds
+    2 r^3 (m_i |lam_j| + m_j |lam_i|) and r^3 |d| |lam_j|; three times their
+    combination, 24 u, over all sampled particles, and over the first and the
+    last eighth, which are nearly all sink side and all source side."""
+    x, v, m = plummer_sphere(n, 960 + n % 13)
+    m = m * np.random.default_rng(n).uniform(0.5, 1.5, size=n)
+    eps, dt, u = 2.0 ** -7, 2.0 ** -9, 2.0 ** -24
+    xd, vd, md = to_dev(x, np.zeros_like(x), m, "f32")
+    lam = np.random.default_rng(n + 1).normal(size=(3, n))
+    rng = np.random.default_rng(n + 2)
+    e8 = n // 8
+    idx = np.concatenate([np.sort(rng.choice(e8, 100, replace=False)),
+                          e8 + np.sort(rng.choice(n - 2 * e8, 100, replace=False)),
+                          n - e8 + np.sort(rng.choice(e8, 100, replace=False))])
+    mh = host(md)
+    acc = nb.accel(xd, md, eps, prec="f32")
+    lx = torch.zeros_like(xd)
+    lv = torch.tensor(lam, dtype=xd.dtype, device=DEV)
+    lm = torch.zeros(n, dtype=torch.float64, device=DEV)
+    nb.step_adjoint(xd, vd, md, acc, lx, lv, lm, eps, dt, 0, prec="f32", entry_half=True)
+    for walked in (False, True):
+        if walked:
+            lx.zero_()
+            lm.zero_()
+            nb.step_adjoint(xd, vd, md, acc, lx, lv, lm, eps, dt, 1, prec="f32")
+        xh, lh = host(xd), host(lv)
+        jt, gt = oracle.vjp_sampled(xh, mh, lh, eps, idx)
+        ej = np.linalg.norm(host(lx)[:, idx] / (0.5 * dt) - jt, axis=0)
+        eg = np.abs(host(lm)[idx] / (0.5 * dt) - gt)
+        ln = np.linalg.norm(lh, axis=0)
+        bj, bg = np.empty(len(idx)), np.empty(len(idx))
+        for q, i in enumerate(idx):
+            d2 = ((xh - xh[:, i:i + 1]) ** 2).sum(0)
+            r3 = (d2 + eps * eps) ** -1.5
+            bj[q] = np.sqrt(((2 * r3 * (mh[i] * ln + mh * ln[i])) ** 2).sum())
+            bg[q] = np.sqrt((r3 * r3 * d2 * ln * ln).sum())
+        for part in (slice(None), slice(0, 100), slice(200, 300)):
+            assert np.linalg.norm(ej[part]) <= 24 * u * np.linalg.norm(bj[part]), (walked, part)
+            assert np.linalg.norm(eg[part]) <= 24 * u * np.linalg.norm(bg[part]), (walked, part)
