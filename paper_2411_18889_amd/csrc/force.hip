@@ -210,9 +210,7 @@ __global__ __launch_bounds__(BS) NB_WAVES_PER_EU(FEW) void force_kernel(ForceArg
 // wave g of a group of W adds ranges g, g + W, ... of 64 sinks (eight ranges'
 // loads in flight together), and the first wave the W sums in wave order. At
 // small ni the kernel is one load latency after another, so four waves share
-// them; from 16384 sinks, and up to four ranges (eight with the potential), one
-// wave is as fast or faster (FP32 sums with the potential, one sink of 4000
-// sources 21.7 against 22.6 us a pass, 1000 sources 21.5, 21.7).
+// them; from 16384 sinks, and up to four ranges, one wave is as fast.
 template <class Pol, bool POT, int W>
 __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int nsplit) {
     constexpr int N = POT ? 4 : 3;
@@ -227,28 +225,19 @@ __global__ __launch_bounds__(256) void force_reduce_kernel(ForceArgs<Pol> a, int
 #pragma unroll
         for (int c = 0; c < 3; ++c) in[c] = a.tail.load(c * (size_t)a.ni + i, a.xi);
     if (i < a.ni) {
-        if constexpr (W == 1) {
-#pragma unroll 8
-            for (int r = 0; r < nsplit; ++r) {
+        for (int r0 = g; r0 < nsplit; r0 += W * 8) {
+            double t[8][N];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int r = r0 + W * u;
                 const double* q = a.part + r * stride + i;
 #pragma unroll
-                for (int c = 0; c < N; ++c) s[c] += q[(size_t)c * a.ni];
+                for (int c = 0; c < N; ++c) t[u][c] = r < nsplit ? q[(size_t)c * a.ni] : 0.0;
             }
-        } else {
-            for (int r0 = g; r0 < nsplit; r0 += W * 8) {
-                double t[8][N];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int r = r0 + W * u;
-                    const double* q = a.part + r * stride + i;
+            for (int u = 0; u < 8; ++u)
 #pragma unroll
-                    for (int c = 0; c < N; ++c) t[u][c] = r < nsplit ? q[(size_t)c * a.ni] : 0.0;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-#pragma unroll
-                    for (int c = 0; c < N; ++c) s[c] += t[u][c];
-            }
+                for (int c = 0; c < N; ++c) s[c] += t[u][c];
         }
     }
     if constexpr (W > 1) {
@@ -464,7 +453,7 @@ hipError_t run_force(const Shape& sh, ForceArgs<Pol> a, void* ws, bool partials_
     a.part = static_cast<double*>(ws);
     hipError_t e = launch_any<Pol, ACC, POT>(sh, a, nsplit, stream);
     if (e != hipSuccess || partials_only) return e;
-    if (a.ni < 16384 && nsplit > (POT ? 8 : 4))
+    if (a.ni < 16384 && nsplit > 4)
         hipLaunchKernelGGL((force_reduce_kernel<Pol, POT, 4>), reduce_grid(sh, a.ni), dim3(256), 0,
                            stream, a, nsplit);
     else
