@@ -27,9 +27,9 @@ SOURCES = ["force.hip", "force_sym.hip", "adjoint.hip", "adjoint_sym.hip", "adjo
 # measured against the default on MI355X (the figures are in the files'
 # headers): the force-free symmetric adjoint kernels with the memory-clause
 # strategy, which interleaves the sinks of a lane (5 % faster at 2^20); the
-# one-wave-per-group adjoint kernels of FP32 and FP64 with the maximum-ILP
-# strategy (9-11 % faster in FP32 at 16384); the symmetric force kernels with
-# the iterative ILP strategy (1-1.5 % faster).
+# one-wave-per-group adjoint kernels of FP32 with the maximum-ILP strategy (8 %
+# faster entry passes at 16384); the symmetric force kernels with the iterative
+# ILP strategy (1-1.5 % faster).
 FILE_FLAGS = {"adjoint_sym_entry.hip": ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause"],
               "adjoint_sym_group.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
               "force_sym.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]}

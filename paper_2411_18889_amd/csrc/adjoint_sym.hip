@@ -25,6 +25,12 @@
 
 namespace nb {
 
+namespace asym {
+hipError_t launch_group_own(const ASymArgs<PolF64>& a, bool force_sums, hipStream_t stream) {
+    return force_sums ? launch_group<PolF64, true>(a, stream) : launch_group<PolF64, false>(a, stream);
+}
+}  // namespace asym
+
 namespace {
 
 using asym::ASymArgs;

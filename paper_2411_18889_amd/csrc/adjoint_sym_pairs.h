@@ -250,9 +250,9 @@ __global__ __launch_bounds__(W * 64) void adjoint_sym_kernel(ASymArgs<Pol> a) {
 // The same items with one wave per 64-source group, as the symmetric force
 // pass's force_group_kernel, whose comment has the reasons. Measured on
 // MI355X against the kernel above in the same blocks of 256, us per pass at
-// 16384 particles: tile-compensated 136 against 147 (entry pass), 165 against
-// 183 (with the force sums); FP32 121, 140 and 147, 176; FP64 218, 257 and
-// 267, 336.
+// 16384 particles (with its fold; the second with the force sums and the step's
+// reverse drift): tile-compensated 121 against 125, 148 against 159; FP32 111,
+// 137 and 120, 151; FP64 191, 238 and 229, 309.
 template <class Pol, int C, int K, bool F>
 __global__ __launch_bounds__(C * K * 64) void adjoint_group_kernel(ASymArgs<Pol> a) {
     using T = typename Pol::calc_t;
@@ -443,7 +443,7 @@ hipError_t launch_group(const ASymArgs<Pol>& a, hipStream_t stream) {
                        stream, a);
     return hipGetLastError();
 }
-// The plain FP32 and FP64 policies' (adjoint_sym_group.hip).
+// The plain FP32 policy's (adjoint_sym_group.hip) and FP64's (adjoint_sym.hip).
 hipError_t launch_group_own(const ASymArgs<PolF32>& a, bool force_sums, hipStream_t stream);
 hipError_t launch_group_own(const ASymArgs<PolF64>& a, bool force_sums, hipStream_t stream);
 

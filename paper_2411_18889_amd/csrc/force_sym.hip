@@ -293,9 +293,9 @@ __global__ __launch_bounds__(W * 64) void force_sym_kernel(SymArgs<Pol> a) {
 // 2.6e-7.)
 // Against the kernel above, us per pass (with its fold) on MI355X:
 //                    12288         16384         20011         32768
-//   tile-comp. 2 x 2 49.0,  61.0   75.0,  80.5  103, 119
-//   FP32       2 x 2 45.3,  55.5   68.5,  79.3   96, 115       223, 234 (4 x 2)
-//   FP64       2 x 2 86.3, 100     129,  156    187, 219       472, 503 (4 x 2)
+//   tile-comp. 2 x 2 43.6, 53.9    66.1, 69.5    98.1, 115.9
+//   FP32       2 x 2 40.1, 50.3    61.2, 66.9    90.6, 112.4   220, 217 (4 x 2)
+//   FP64       2 x 2 75.1, 92.8   121.6, 151.7  181.3, 212.4   460, 482 (4 x 2)
 // (launch and memory latency aside, every SIMD gets 8 or 9 of the 8320 waves at
 // 16384: a tenth is the uneven share.) Shapes by_groups() gives.
 template <class Pol, int C, int K, bool P>
@@ -513,8 +513,9 @@ __global__ __launch_bounds__(kFoldLanes) void force_sym_finish_kernel(SymFinishA
 
 // Whether a shape's items run with one wave per source group, and the threads
 // of an item's workgroup.
-// Blocks of 256 for every policy; blocks of 512 in FP64 (65536: 1775 against
-// 1844 us) and, up to 96 blocks, in FP32 (65536, 128 blocks: 895 against 860).
+// Blocks of 256 for every policy; blocks of 512 in FP64 (65536: 1729 against
+// 1805 us) and, up to 96 blocks, in FP32 (24576 132, 140; 28000 172, 170; 36000
+// 253, 263; 44000 374, 382; but 65536, 128 blocks, 895, 860).
 template <class Pol>
 constexpr bool by_groups(int waves, int ipl, int nb) {
     return ipl == 2 && (waves == 2 || (waves == 4 && !Pol::origin &&
