@@ -13,10 +13,9 @@
 // slab of CI planes; planes i - 1, i, i + 1 of its points stay in registers,
 // plane i + 2 and the two outer rows (j - 1, j + R) of plane i + 1 are already
 // loading while plane i is computed. There is no LDS, and a barrier only for
-// pace (PACED, large planes): rows
-// above and below come from L1 / L2, where the neighbouring lanes' own loads
-// put them, and the k neighbours of a lane's 4 points from the adjacent
-// lanes (DPP wave shifts).
+// pace (PACED, large planes): rows above and below come from L1 / L2, where the
+// neighbouring lanes' own loads put them, and the k neighbours of a lane's 4
+// points from the adjacent lanes (DPP wave shifts).
 //
 // 16-byte accesses need only 4-byte alignment here, so every nz >= 4 and every
 // array alignment takes them: the last lane of a row is shifted back to end at
