@@ -520,11 +520,14 @@ Shape choose_force_shape(int prec, int64_t ni, int64_t nj, Pick pick) {
     // so up to 6000 sources for FP64 sums of FP32 terms, whose lanes carry
     // the longest chain, and for few FP64 sinks, where a lane's sources are
     // the whole time (100 against 12000: 15.3, 14.3; 1000: 16.4, 19.7), and not
-    // above 12000 sinks and sources in FP64 (12287: 111.3, 109.4).
+    // above 12032 sinks and sources in FP64, where a range of 256 sources has 48
+    // workgroups, a multiple of the XCDs (a pass alone and with the potential:
+    // 12287 109.1, 101.3 and 110.8, 106.8; but 12001 105.7, 103.8 and 107.5,
+    // 111.0).
     // Larger sets on themselves have the symmetric pass in FP64 and FP32.
     const bool regroup = prec == NB_F64 || prec == NB_F32 || prec == NB_MIX_ACC64;
     const int64_t most = prec == NB_MIX_ACC64 || (prec == NB_F64 && ni < 512) ? 6000
-                         : prec == NB_F64 && ni > 12000                       ? 12000
+                         : prec == NB_F64 && ni > 12032                       ? 12032
                                                                               : 12287;
     if (pick == Pick::Best && regroup && ni <= 12287 && nj <= most) {
         const int lanes = prec != NB_MIX_ACC64 && ni <= 3072 && nj > 256 ? 512 : 256;
